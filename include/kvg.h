@@ -260,11 +260,10 @@ size_t kvg_prefill_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs,
  * index n = ctx_lens[b] + i) computes, per query head h,
  *   out = softmax_j( (R(pos_n) q_h . K_{h/group, j}) * scale ) V_{h/group, j},  j <= n
  * with fp32 softmax and accumulation (j > n - W as well in a layer with window W).
- * bf16 and fp8 caches with at most 4 query heads per KV head use bf16 MFMA for Q K^T and
- * P V (each rotated query carried as a bf16 high part and a bf16 low part, both multiplied
- * with every key, so a score is as accurate as with the fp32 query; P rounded to bf16; fp8
- * rows widened to bf16 exactly); fp32 caches, and 8 query heads per KV head, use fp32
- * vector arithmetic (bf16 and fp8 caches there: the same query parts, P rounded to bf16).
+ * bf16 and fp8 caches use bf16 MFMA for Q K^T and P V (each rotated query carried as a bf16
+ * high part and a bf16 low part, both multiplied with every key, so a score is as accurate as
+ * with the fp32 query; P rounded to bf16; fp8 rows widened to bf16 exactly); fp32 caches use
+ * fp32 vector arithmetic.
  * q_raw_dev: [n_layers][batch][chunk_len][n_q_heads][head_dim] of the raw dtype (the cache
  * dtype, bf16 for an fp8 cache), pre-rotation;
  * k_raw_dev, v_raw_dev as kvg_append; out_dev: [n_layers][batch][chunk_len][n_q_heads]

@@ -20,10 +20,6 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 size_t elem_bytes(const kvg_cache* c) { return c->dtype == KVG_BF16 ? 2 : c->dtype == KVG_FP8_E4M3 ? 1 : 4; }
 
-// bytes of one raw q/k/v element (an fp8 cache takes bf16 inputs) and of a rotated query
-// in the attention workspace (bf16 for bf16 and fp8 caches)
-size_t raw_bytes(const kvg_cache* c) { return c->dtype == KVG_F32 ? 4 : 2; }
-
 int check_cache(const kvg_cache* c) {
   if (c == nullptr || c->k_pool == nullptr || c->v_pool == nullptr) return KVG_E_INVAL;
   if (c->dtype != KVG_F32 && c->dtype != KVG_BF16 && c->dtype != KVG_FP8_E4M3) return KVG_E_DTYPE;
@@ -83,18 +79,16 @@ int n_split_max(const kvg_seqs* s, int32_t chunk) {
   return (int)(((int64_t)s->max_ctx_len + chunk + kSplit - 1) / kSplit);
 }
 
-// Workspace of the vector-ALU attention path: rotated queries (fp32, or bf16 hi and lo
-// planes for bf16 and fp8 caches), split partials.
+// Workspace of the vector-ALU attention path (fp32 caches): rotated queries, split partials.
 struct ValuWs {
-  size_t q, q_plane, acc, ml, total;
+  size_t q, acc, ml, total;
 };
 
 ValuWs valu_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows) {
   ValuWs w;
   const size_t nrow_heads = (size_t)n_layers * s->batch * rows * c->n_q_heads;
   const size_t ns = (size_t)n_split_max(s, rows);
-  w.q_plane = align_up(nrow_heads * c->head_dim * raw_bytes(c));
-  w.q = c->dtype == KVG_F32 ? w.q_plane : 2 * w.q_plane;
+  w.q = align_up(nrow_heads * c->head_dim * sizeof(float));
   w.acc = align_up(nrow_heads * ns * c->head_dim * sizeof(float));
   w.ml = align_up(nrow_heads * ns * 2 * sizeof(float));
   w.total = w.q + w.acc + w.ml;
@@ -147,7 +141,7 @@ int check_raw(const void* k_raw, const void* v_raw) {
   return (k_raw == nullptr || v_raw == nullptr) ? KVG_E_INVAL : KVG_OK;
 }
 
-// Shared body of the vector-ALU attention calls: append, rotate queries, partials, merge.
+// Prefill of an fp32 cache: append, rotate queries, partials, merge.
 int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t layer0, int32_t n_layers,
               int32_t rows, const void* q_raw, const void* k_raw, const void* v_raw, float scale,
               float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
@@ -157,16 +151,13 @@ int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   const int64_t n_rows = (int64_t)n_layers * s->batch * rows * c->n_q_heads;
   if (!fits_grid(n_blocks, 256) || !fits_grid(n_rows, 256) || !append_fits(s, rows)) return KVG_E_SHAPE;
   char* base = static_cast<char*>(ws);
-  void* q = base;
+  float* q = reinterpret_cast<float*>(base);
   float* acc = reinterpret_cast<float*>(base + w.q);
   float* ml = reinterpret_cast<float*>(base + w.q + w.acc);
 
-  void* q_lo = c->dtype == KVG_F32 ? nullptr : base + w.q_plane;
   kvg::AppendArgs ap = append_args(c, s, r, layer0, n_layers, rows, k_raw, v_raw);
   ap.q_raw = q_raw;
   ap.q_out = q;
-  ap.q_out_lo = q_lo;
-  ap.q_out_bf16 = c->dtype != KVG_F32;
   int st = hip_status(kvg::launch_append(ap, c->dtype, stream));
   if (st != KVG_OK) return st;
 
@@ -179,7 +170,6 @@ int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   a.block_tables = s->block_tables;
   a.ctx_lens = s->ctx_lens;
   a.q = q;
-  a.q_lo = q_lo;
   a.part_acc = acc;
   a.part_ml = ml;
   a.out = out;
@@ -196,21 +186,20 @@ int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   a.max_ctx_len = s->max_ctx_len;
   a.n_split_max = n_split_max(s, rows);
   fill_windows(c, layer0, n_layers, a.window);
-  return hip_status(kvg::launch_attn_valu(a, c->dtype, stream));
+  return hip_status(kvg::launch_attn_valu(a, stream));
 }
 
 // Workspace of the decode kernels: the split partials.
-// bf16 and fp8 caches with up to 4 query heads per KV head prefill on MFMA; others on the
-// VALU path.
-bool use_mfma(const kvg_cache* c) {
-  return (c->dtype == KVG_BF16 || c->dtype == KVG_FP8_E4M3) && c->n_q_heads / c->n_kv_heads <= 4;
-}
+// bf16 and fp8 caches prefill on MFMA, fp32 caches on the VALU path.  8 query heads per KV
+// head (31B-like heads, 2 layers x 3 x 300 rows over 1.6k keys): 1,153 us on the VALU path,
+// which reads every key again for every row, 93 us on MFMA.
+bool use_mfma(const kvg_cache* c) { return c->dtype == KVG_BF16 || c->dtype == KVG_FP8_E4M3; }
 
 // Decode splits served by the shared-split kernel: the whole 512-key splits inside the
 // leading pages every sequence shares (kvg_seqs.shared_tokens), when several sequences
 // share them and the cache takes the MFMA path; 0 otherwise.
 int shared_splits(const kvg_cache* c, const kvg_seqs* s) {
-  if (s->shared_tokens <= 0 || s->batch < 2 || !use_mfma(c)) return 0;
+  if (s->shared_tokens <= 0 || s->batch < 2 || !use_mfma(c) || c->n_q_heads / c->n_kv_heads > 4) return 0;
   return std::min(s->shared_tokens / kSplit, n_split_max(s, 1));
 }
 
@@ -257,7 +246,8 @@ size_t mfma_q_bytes(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int
 
 // Rows per head of one q-tile of the MFMA prefill kernel.
 int prefill_tile_rows(const kvg_cache* c) {
-  return 32 * kvg::prefill_mfma_waves(c->head_dim) / (c->n_q_heads / c->n_kv_heads);
+  const int group = c->n_q_heads / c->n_kv_heads;
+  return 32 * kvg::prefill_mfma_waves(c->head_dim) * kvg::prefill_head_sets(c->head_dim, group) / group;
 }
 
 // Keys of the shared pages a suffix prefill attends once for the batch: only when the chunk
@@ -283,7 +273,7 @@ int attn_mfma(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   const int group = c->n_q_heads / c->n_kv_heads;
   const int bm = prefill_tile_rows(c);
   const int n_qt = (chunk + bm - 1) / bm;
-  const int64_t n_wg = (int64_t)n_layers * s->batch * c->n_kv_heads * n_qt;
+  const int64_t n_wg = (int64_t)n_layers * s->batch * c->n_kv_heads * kvg::prefill_head_sets(c->head_dim, group) * n_qt;
   const int threads = 64 * kvg::prefill_mfma_waves(c->head_dim);
   if (!fits_grid(n_wg, threads) || !append_fits(s, chunk)) return KVG_E_SHAPE;
   if (prefill_shared_keys(c, s, chunk) > 0) {

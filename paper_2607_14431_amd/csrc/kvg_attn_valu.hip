@@ -462,9 +462,9 @@ __device__ __forceinline__ float combine_splits(const float* ml, const float* ac
 // ------------------------------------------------------------------------------------
 // Multi-row calls (fp32 prefill): queries pre-rotated by the append kernel; each work item
 // writes its split partial, combined by attn_merge_kernel.
-template <typename T, int D, int G>
+template <int D, int G>
 __global__ __launch_bounds__(kThreads) void attn_partial_kernel(const AttnArgs a) {
-  using W = SplitWorker<T, D, G>;
+  using W = SplitWorker<float, D, G>;
   int64_t w = blockIdx.x;
   const int s = (int)(w % a.n_split_max);  w /= a.n_split_max;
   const int g = (int)(w % a.Hkv);          w /= a.Hkv;
@@ -484,19 +484,19 @@ __global__ __launch_bounds__(kThreads) void attn_partial_kernel(const AttnArgs a
   W wk;
   wk.init();
   const int64_t row_id = ((int64_t)l * a.batch + b) * a.rows + r;
-  constexpr int kQWordsPerRow = W::kBf16 ? D / 2 : D;
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-    const int64_t qoff = (row_id * a.Hq + (int64_t)g * G + h) * kQWordsPerRow;
-    const uint32_t* qp = reinterpret_cast<const uint32_t*>(a.q) + qoff;
-    const uint32_t* qlp = reinterpret_cast<const uint32_t*>(W::kBf16 ? a.q_lo : a.q) + qoff;
+    const float* qp = a.q + (row_id * a.Hq + (int64_t)g * G + h) * D;
 #pragma unroll
-    for (int j = 0; j < W::CPL * W::QC; ++j) wk.set_q(h, j, ld16(qp + wk.q_chunk(j) * 4), ld16(qlp + wk.q_chunk(j) * 4));
+    for (int j = 0; j < W::CPL; ++j) {
+      const uint4 v = ld16(qp + wk.q_chunk(j) * 4);
+      wk.set_q(h, j, v, v);
+    }
   }
 
   const int64_t lbase = (int64_t)(a.layer0 + l) * a.layer_elems;
-  const T* kpool = reinterpret_cast<const T*>(a.k_pool) + lbase;
-  const T* vpool = reinterpret_cast<const T*>(a.v_pool) + lbase;
+  const float* kpool = reinterpret_cast<const float*>(a.k_pool) + lbase;
+  const float* vpool = reinterpret_cast<const float*>(a.v_pool) + lbase;
   const int32_t* bt = a.block_tables + (int64_t)b * a.max_pages;
   SplitPages sp;
   sp.init(bt, kb / kPage, a.max_pages, wk.lane);
@@ -902,27 +902,17 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
     a.out[row_head * a.D + d] = combine_splits(ml, acc + d, a.D, n_split);
 }
 
-template <typename T, int D>
+template <int D>
 hipError_t launch_partial_g(const AttnArgs& a, hipStream_t stream) {
   const int64_t n_blocks = (int64_t)a.n_layers * a.batch * a.rows * a.Hkv * a.n_split_max;
   switch (a.group) {
-    case 1: attn_partial_kernel<T, D, 1><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 2: attn_partial_kernel<T, D, 2><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 4: attn_partial_kernel<T, D, 4><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 8: attn_partial_kernel<T, D, 8><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 1: attn_partial_kernel<D, 1><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 2: attn_partial_kernel<D, 2><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 4: attn_partial_kernel<D, 4><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 8: attn_partial_kernel<D, 8><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_partial_d(const AttnArgs& a, hipStream_t stream) {
-  switch (a.D) {
-    case 64: return launch_partial_g<T, 64>(a, stream);
-    case 128: return launch_partial_g<T, 128>(a, stream);
-    case 256: return launch_partial_g<T, 256>(a, stream);
-    default: return hipErrorInvalidValue;
-  }
 }
 
 template <typename T, int D>
@@ -968,10 +958,14 @@ __global__ __launch_bounds__(kThreads) void prefill_combine_kernel(const Prefill
 
 }  // namespace
 
-hipError_t launch_attn_valu(const AttnArgs& a, int dtype, hipStream_t stream) {
-  hipError_t e = dtype == kDtypeBf16  ? launch_partial_d<uint16_t>(a, stream)
-                 : dtype == kDtypeFp8 ? launch_partial_d<uint8_t>(a, stream)
-                                      : launch_partial_d<float>(a, stream);
+hipError_t launch_attn_valu(const AttnArgs& a, hipStream_t stream) {
+  hipError_t e;
+  switch (a.D) {
+    case 64: e = launch_partial_g<64>(a, stream); break;
+    case 128: e = launch_partial_g<128>(a, stream); break;
+    case 256: e = launch_partial_g<256>(a, stream); break;
+    default: return hipErrorInvalidValue;
+  }
   if (e != hipSuccess) return e;
   const int64_t n_rows = (int64_t)a.n_layers * a.batch * a.rows * a.Hq;
   attn_merge_kernel<<<dim3((unsigned)n_rows), kThreads, 0, stream>>>(a);

@@ -166,8 +166,7 @@ struct AttnArgs {
   int64_t n_pages;
   const int32_t* block_tables;
   const int32_t* ctx_lens;
-  const void* q;              // rotated queries [n_layers][batch][rows][Hq][D]: bf16 hi for bf16 caches, else fp32
-  const void* q_lo;           // bf16 caches: the queries' bf16 lo parts, same layout (null for fp32)
+  const float* q;             // rotated queries [n_layers][batch][rows][Hq][D]
   float* part_acc;            // [n_layers][batch][rows][Hq][n_split_max][D]
   float* part_ml;             // [n_layers][batch][rows][Hq][n_split_max][2]
   float* out;                 // [n_layers][batch][rows][Hq][D]

@@ -15,11 +15,15 @@ hipError_t launch_graft(const CopyArgs& a, int dtype, hipStream_t stream);
 // workgroups (256 threads each) of the deposit's and of the graft's launch (own position or
 // relocated), for the host's launch-size checks
 int64_t copy_workgroups(const CopyArgs& a, int dtype);
-hipError_t launch_attn_valu(const AttnArgs& a, int dtype, hipStream_t stream);
+// the prefill of an fp32 cache on the vector ALUs
+hipError_t launch_attn_valu(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int dtype, hipStream_t stream);
 // waves (32 query rows each) per workgroup of the MFMA prefill at head_dim D; a workgroup
 // covers 32 * waves / group rows of each of the group's query heads
 int prefill_mfma_waves(int D);
+// workgroups that share the query heads of one KV head (more than one where a workgroup has
+// fewer waves than the KV head has query heads)
+int prefill_head_sets(int D, int group);
 // decode partials of splits [0, a.n_shared_split) of every full-attention layer, for a batch
 // whose sequences share those pages; a.q holds the rotated queries [n_layers][batch][Hq][D]
 hipError_t launch_shared_splits(const PrefillArgs& a, int dtype, hipStream_t stream);

@@ -52,6 +52,7 @@
 #include <limits.h>
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 namespace kvg {
@@ -142,7 +143,8 @@ __device__ __forceinline__ uint4 widen_fp8x8(uint32_t lo, uint32_t hi) {
 // T: cache storage (uint16_t bf16, uint8_t fp8 E4M3).  fp8 tiles are staged as bytes (half the
 // HBM, DMA and LDS traffic) and widened to bf16 fragments exactly before the MFMAs.
 // NW: waves per workgroup (prefill_mfma_waves), 32 query rows each.
-template <typename T, int D, int NW, bool kShared>
+// kTight: 8 query heads per KV head (kRaise 0 and the sum of the rounded weights, see soft_piece).
+template <typename T, int D, int NW, bool kShared, bool kTight>
 __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs a) {
   constexpr bool kFp8 = sizeof(T) == 1;
   constexpr int RB = D * (int)sizeof(T);   // bytes per cache row
@@ -174,7 +176,8 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
   int id = blockIdx.x;
   const int per_xcd = nwg / 8;
   if (id < per_xcd * 8) id = (id % 8) * per_xcd + id / 8;
-  const int G = a.group;
+  const int G = a.group < NW ? a.group : NW;   // query heads of this workgroup
+  const int n_hs = a.group / G;                // workgroups that share a KV head's query heads
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
@@ -191,6 +194,8 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     // (q-tile, KV head, sequence, layer), heavy (late) q-tiles first
     int qt = id % a.n_qt;
     int rest = id / a.n_qt;
+    const int hs = rest % n_hs;                         // which G of the KV head's query heads
+    rest /= n_hs;
     g = rest % a.Hkv;
     rest /= a.Hkv;
     b = rest % a.batch;
@@ -202,7 +207,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     const int i0 = qt * BM;
     const int h_local = (wave * 32) / BM;
     const int r0 = (wave * 32) % BM;
-    h = g * G + h_local;
+    h = g * a.group + hs * G + h_local;
     row = i0 + r0 + lrow;                               // chunk row of this lane
     row_ok = row < a.chunk;
     row_n = ctx + row;                                  // its logical index: keys [0, row_n]
@@ -468,6 +473,14 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     // scores each; 4: the max of both halves of the row, the reference and the factor; 5-12:
     // two exponentials each and their running sum (in key order); 13: the sum of both halves
     // and the running sum of the row; 14-15: the bf16 packing of eight values each.
+    // With 8 query heads per KV head (kTight) these calls used to run on the vector path, whose
+    // sixteen teams' references follow the largest score closely and whose sum takes the rounded
+    // weights.  To be as exact, the reference there is raised to every new maximum (the
+    // heaviest weight of a peaked row is then exactly 1, with no rounding error) and the sum
+    // takes the rounded weights (v_dot2_f32_bf16 with (1, 1)): at scores of std 2 the outputs are
+    // 0.89e-3 off the 64-bit result against 1.02e-3 on the vector path and 1.55e-3 with the lazy
+    // reference.  The other groups keep the lazy reference and the fp32 sum (taking the rounded
+    // weights there measured 0.5% slower on the 31B-class suffix).
     // Branch-free: exp2(-inf - finite) = 0 for a first raise, and the value of an unraised
     // lane (possibly NaN) is discarded by the select.
     uint4 pf[4];
@@ -483,7 +496,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
       } else if (j == 4) {
         const float2 mh = halves32(st.mx);
         const float mx2 = fmaxf(mh.x, mh.y) * a.scale_log2;
-        st.raised = mx2 > m_run + kRescale;
+        st.raised = mx2 > m_run + (kTight ? 0.0f : kRescale);
         st.alpha = st.raised ? __builtin_amdgcn_exp2f(m_run - mx2) : 1.0f;
         m_run = st.raised ? mx2 : m_run;
         // a row that has not seen a key yet (a windowed row whose window starts past this
@@ -495,11 +508,13 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
         for (int r = 2 * (j - 5); r < 2 * (j - 5) + 2; ++r) {
           const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], a.scale_log2, -st.m_ref));
           s[kb][r] = p;
-          st.psum += p;
+          if constexpr (!kTight) st.psum += p;
         }
       } else if (j == 13) {
-        const float2 ph = halves32(st.psum);
-        l_run = l_run * st.alpha + (ph.x + ph.y);
+        if constexpr (!kTight) {
+          const float2 ph = halves32(st.psum);
+          l_run = l_run * st.alpha + (ph.x + ph.y);
+        }
       } else {
         const int hs = j - 14;
         uint4& f = pf[2 * kb + hs];
@@ -507,6 +522,16 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
         f.y = pack_bf16_rne(s[kb][8 * hs + 2], s[kb][8 * hs + 3]);
         f.z = pack_bf16_rne(s[kb][8 * hs + 4], s[kb][8 * hs + 5]);
         f.w = pack_bf16_rne(s[kb][8 * hs + 6], s[kb][8 * hs + 7]);
+        if constexpr (kTight) {
+          const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+          for (int w = 0; w < 4; ++w)
+            st.psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (&f.x)[w]), ones, st.psum, false);
+          if (hs == 1) {
+            const float2 ph = halves32(st.psum);
+            l_run = l_run * st.alpha + (ph.x + ph.y);
+          }
+        }
       }
     };
     auto rescale_o = [&](bool raised, float alpha) {
@@ -634,15 +659,16 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
 
 }  // namespace
 
-template <typename T, bool kShared>
+template <typename T, bool kShared, bool kTight>
 hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t stream) {
   const int64_t n_wg = kShared ? (int64_t)a.n_layers * a.Hkv * a.n_shared_split * a.n_qt
-                               : (int64_t)a.n_layers * a.batch * a.Hkv * a.n_qt;
+                               : (int64_t)a.n_layers * a.batch * a.Hkv * prefill_head_sets(a.D, a.group) * a.n_qt;
   if (n_wg <= 0) return hipSuccess;
+  const dim3 grid((unsigned)n_wg);
   switch (a.D) {
-    case 64: prefill_mfma_kernel<T, 64, 8, kShared><<<dim3((unsigned)n_wg), 64 * 8, 0, stream>>>(a); break;
-    case 128: prefill_mfma_kernel<T, 128, 8, kShared><<<dim3((unsigned)n_wg), 64 * 8, 0, stream>>>(a); break;
-    case 256: prefill_mfma_kernel<T, 256, 4, kShared><<<dim3((unsigned)n_wg), 64 * 4, 0, stream>>>(a); break;
+    case 64: prefill_mfma_kernel<T, 64, 8, kShared, kTight><<<grid, 64 * 8, 0, stream>>>(a); break;
+    case 128: prefill_mfma_kernel<T, 128, 8, kShared, kTight><<<grid, 64 * 8, 0, stream>>>(a); break;
+    case 256: prefill_mfma_kernel<T, 256, 4, kShared, kTight><<<grid, 64 * 4, 0, stream>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -653,15 +679,22 @@ hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t stream) {
 // hi and lo parts alone take 256 registers per lane).
 int prefill_mfma_waves(int D) { return D <= 128 ? 8 : 4; }
 
+// A wave owns rows of one query head, so a workgroup serves at most one head per wave: 8 heads
+// per KV head at head_dim 256 take two workgroups of 4 heads.
+int prefill_head_sets(int D, int group) { return std::max(1, group / prefill_mfma_waves(D)); }
+
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int dtype, hipStream_t stream) {
-  if (dtype == kDtypeBf16) return launch_prefill_t<uint16_t, false>(a, stream);
-  if (dtype == kDtypeFp8) return launch_prefill_t<uint8_t, false>(a, stream);
+  const bool tight = a.group > 4;
+  if (dtype == kDtypeBf16)
+    return tight ? launch_prefill_t<uint16_t, false, true>(a, stream) : launch_prefill_t<uint16_t, false, false>(a, stream);
+  if (dtype == kDtypeFp8)
+    return tight ? launch_prefill_t<uint8_t, false, true>(a, stream) : launch_prefill_t<uint8_t, false, false>(a, stream);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_shared_splits(const PrefillArgs& a, int dtype, hipStream_t stream) {
-  if (dtype == kDtypeBf16) return launch_prefill_t<uint16_t, true>(a, stream);
-  if (dtype == kDtypeFp8) return launch_prefill_t<uint8_t, true>(a, stream);
+  if (dtype == kDtypeBf16) return launch_prefill_t<uint16_t, true, false>(a, stream);
+  if (dtype == kDtypeFp8) return launch_prefill_t<uint8_t, true, false>(a, stream);
   return hipErrorInvalidValue;
 }
 
