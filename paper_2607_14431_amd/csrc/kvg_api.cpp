@@ -192,7 +192,7 @@ int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
 // Workspace of the decode kernels: the split partials.
 // bf16 and fp8 caches prefill on MFMA, fp32 caches on the VALU path.  8 query heads per KV
 // head (31B-like heads, 2 layers x 3 x 300 rows over 1.6k keys): 1,153 us on the VALU path,
-// which reads every key again for every row, 93 us on MFMA.
+// which reads every key again for every row, 115 us on MFMA.
 bool use_mfma(const kvg_cache* c) { return c->dtype == KVG_BF16 || c->dtype == KVG_FP8_E4M3; }
 
 // Decode splits served by the shared-split kernel: the whole 512-key splits inside the
@@ -257,12 +257,19 @@ int prefill_shared_keys(const kvg_cache* c, const kvg_seqs* s, int32_t chunk) {
   return chunk < prefill_tile_rows(c) ? shared_splits(c, s) * kSplit : 0;
 }
 
+// Partials per (row, query head) of an MFMA prefill: the shared pages' and the sequence's own;
+// with 8 query heads per KV head one per kSplit-key segment; 0 when rows are finished in place.
+int prefill_partials(const kvg_cache* c, const kvg_seqs* s, int32_t chunk) {
+  if (prefill_shared_keys(c, s, chunk) > 0) return 2;
+  const int segments = c->n_q_heads / c->n_kv_heads > 4 ? n_split_max(s, chunk) : 1;
+  return segments > 1 ? segments : 0;
+}
+
 size_t mfma_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t chunk) {
   const size_t rows = (size_t)n_layers * s->batch * chunk * c->n_q_heads;
-  const size_t part = prefill_shared_keys(c, s, chunk) > 0 ? align_up(rows * 2 * 2 * sizeof(float)) +
-                                                                 align_up(rows * 2 * c->head_dim * sizeof(float))
-                                                           : 0;
-  return mfma_q_bytes(c, s, n_layers, chunk) + part;
+  const size_t parts = prefill_partials(c, s, chunk);
+  return mfma_q_bytes(c, s, n_layers, chunk) + align_up(rows * parts * 2 * sizeof(float)) +
+         align_up(rows * parts * c->head_dim * sizeof(float));
 }
 
 // MFMA prefill: append (queries rotated to bf16 into the workspace), then the attention.
@@ -273,7 +280,10 @@ int attn_mfma(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   const int group = c->n_q_heads / c->n_kv_heads;
   const int bm = prefill_tile_rows(c);
   const int n_qt = (chunk + bm - 1) / bm;
-  const int64_t n_wg = (int64_t)n_layers * s->batch * c->n_kv_heads * kvg::prefill_head_sets(c->head_dim, group) * n_qt;
+  const int parts = prefill_partials(c, s, chunk);
+  const bool segments = group > 4;
+  const int64_t n_wg = (int64_t)n_layers * s->batch * c->n_kv_heads * kvg::prefill_head_sets(c->head_dim, group) * n_qt *
+                       (segments ? std::max(parts, 1) : 1);
   const int threads = 64 * kvg::prefill_mfma_waves(c->head_dim);
   if (!fits_grid(n_wg, threads) || !append_fits(s, chunk)) return KVG_E_SHAPE;
   if (prefill_shared_keys(c, s, chunk) > 0) {
@@ -314,17 +324,22 @@ int attn_mfma(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   a.max_ctx_len = s->max_ctx_len;
   a.n_qt = n_qt;
   fill_windows(c, layer0, n_layers, a.window);
-  const int shared_keys = prefill_shared_keys(c, s, chunk);
-  if (shared_keys == 0) return hip_status(kvg::launch_prefill_mfma(a, c->dtype, stream));
+  a.n_split_max = std::max(parts, 1);
+  const size_t rows = (size_t)n_layers * s->batch * chunk * c->n_q_heads;
+  if (parts > 0) {
+    char* base = static_cast<char*>(ws) + mfma_q_bytes(c, s, n_layers, chunk);
+    a.part_ml = reinterpret_cast<float*>(base);
+    a.part_acc = reinterpret_cast<float*>(base + align_up(rows * parts * 2 * sizeof(float)));
+  }
+  if (segments || parts == 0) {
+    st = hip_status(kvg::launch_prefill_mfma(a, c->dtype, stream));
+    return st == KVG_OK && parts > 0 ? hip_status(kvg::launch_prefill_segments(a, stream)) : st;
+  }
   // Shared pages (kvg_seqs.shared_tokens): on full-attention layers the rows' attention over
   // keys [0, shared_keys) is computed once per page for the whole batch (shared-split mode,
   // partial slot 0) and over their own keys by the per-sequence kernel (slot 1); the two
   // partials are then combined.
-  const size_t rows = (size_t)n_layers * s->batch * chunk * c->n_q_heads;
-  char* base = static_cast<char*>(ws) + mfma_q_bytes(c, s, n_layers, chunk);
-  a.part_ml = reinterpret_cast<float*>(base);
-  a.part_acc = reinterpret_cast<float*>(base + align_up(rows * 2 * 2 * sizeof(float)));
-  a.n_split_max = 2;
+  const int shared_keys = prefill_shared_keys(c, s, chunk);
   kvg::PrefillArgs sh = a;
   sh.n_shared_split = 1;
   sh.shared_keys = shared_keys;

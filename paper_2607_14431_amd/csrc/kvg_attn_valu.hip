@@ -956,7 +956,31 @@ __global__ __launch_bounds__(kThreads) void prefill_combine_kernel(const Prefill
   }
 }
 
+// Prefill with 8 query heads per KV head: each row's partials over the kSplit-key segments (absolute
+// multiples) that hold its visible keys, combined in ascending order.  One element per lane.
+__global__ __launch_bounds__(kThreads) void prefill_segments_kernel(const PrefillArgs a, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+    const int64_t row_head = i / a.D;
+    const int row = (int)((row_head / a.Hq) % a.chunk);
+    const int b = (int)((row_head / ((int64_t)a.Hq * a.chunk)) % a.batch);
+    const int l = (int)(row_head / ((int64_t)a.Hq * a.chunk * a.batch));
+    const int ctx = a.ctx_lens[b];
+    if (ctx < 0 || ctx > a.max_ctx_len) continue;
+    const int n_keys = ctx + row + 1;
+    const int s0 = window_start(layer_window(a, l), n_keys) / kSplit;
+    const int64_t p0 = row_head * a.n_split_max + s0;
+    a.out[i] = combine_splits(a.part_ml + p0 * 2, a.part_acc + p0 * a.D + i % a.D, a.D, (n_keys - 1) / kSplit - s0 + 1);
+  }
+}
+
 }  // namespace
+
+hipError_t launch_prefill_segments(const PrefillArgs& a, hipStream_t stream) {
+  const int64_t n = (int64_t)a.n_layers * a.batch * a.chunk * a.Hq * a.D;
+  const unsigned n_wg = (unsigned)std::min<int64_t>((n + kThreads - 1) / kThreads, int64_t(1) << 22);
+  prefill_segments_kernel<<<dim3(n_wg), kThreads, 0, stream>>>(a, n);
+  return hipGetLastError();
+}
 
 hipError_t launch_attn_valu(const AttnArgs& a, hipStream_t stream) {
   hipError_t e;

@@ -29,6 +29,8 @@ int prefill_head_sets(int D, int group);
 hipError_t launch_shared_splits(const PrefillArgs& a, int dtype, hipStream_t stream);
 // a suffix prefill over shared pages: out = the rows' n_split_max partials combined in order
 hipError_t launch_prefill_combine(const PrefillArgs& a, hipStream_t stream);
+// 8 query heads per KV head: out = each row's partials of the kSplit-key segments it sees
+hipError_t launch_prefill_segments(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream);
 
 

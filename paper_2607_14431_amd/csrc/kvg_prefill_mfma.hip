@@ -143,7 +143,10 @@ __device__ __forceinline__ uint4 widen_fp8x8(uint32_t lo, uint32_t hi) {
 // T: cache storage (uint16_t bf16, uint8_t fp8 E4M3).  fp8 tiles are staged as bytes (half the
 // HBM, DMA and LDS traffic) and widened to bf16 fragments exactly before the MFMAs.
 // NW: waves per workgroup (prefill_mfma_waves), 32 query rows each.
-// kTight: 8 query heads per KV head (kRaise 0 and the sum of the rounded weights, see soft_piece).
+// kTight: 8 query heads per KV head.  Their softmax is the exact variant described at soft_piece,
+// and their keys are cut into segments of kSplit (absolute multiples of 512), a workgroup each,
+// whose partials prefill_segments_kernel combines: one row over 8k keys takes 33 us, 259 us when
+// a workgroup walks all keys (43 us on the vector path it replaces).
 template <typename T, int D, int NW, bool kShared, bool kTight>
 __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs a) {
   constexpr bool kFp8 = sizeof(T) == 1;
@@ -196,6 +199,10 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     int rest = id / a.n_qt;
     const int hs = rest % n_hs;                         // which G of the KV head's query heads
     rest /= n_hs;
+    if constexpr (kTight) {
+      split = rest % a.n_split_max;
+      rest /= a.n_split_max;
+    }
     g = rest % a.Hkv;
     rest /= a.Hkv;
     b = rest % a.batch;
@@ -264,7 +271,12 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     kt_begin = split * (a.shared_keys / kTileKeys);
     bt = a.block_tables;
   }
-  const int n_tiles = (n_hi + kTileKeys - 1) / kTileKeys;
+  int n_tiles = (n_hi + kTileKeys - 1) / kTileKeys;
+  if constexpr (kTight) {
+    kt_begin = max(kt_begin, split * (kSplit / kTileKeys));
+    n_tiles = min(n_tiles, (split + 1) * (kSplit / kTileKeys));
+    if (kt_begin >= n_tiles) return;
+  }
   const int last_page = (n_hi - 1) / kPage;
 
   const int64_t lbase = (int64_t)(a.layer0 + l) * a.layer_elems;
@@ -624,9 +636,9 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
   // ---- shared split: the partial (reference, sum, unnormalised O) of this lane's row in the
   // decode's layout, for the combine kernel
   // (or, for the per-sequence part of a suffix prefill over shared pages, slot part_slot)
-  if (kShared || (a.part_acc != nullptr && layer_window(a, l) == 0)) {
+  if (kShared || (a.part_acc != nullptr && (kTight || layer_window(a, l) == 0))) {
     if (row_ok) {
-      const int slot = kShared ? split : a.part_slot;
+      const int slot = kShared || kTight ? split : a.part_slot;
       const int64_t pidx = ((((int64_t)l * a.batch + b) * a.chunk + row) * a.Hq + h) * a.n_split_max + slot;
       float* op = a.part_acc + pidx * D;
 #pragma unroll
@@ -642,16 +654,18 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
   // ---- normalise and store: lane owns row `row`, dims d*32 + (r/4)*8 + half*4 + r%4
   if (row_ok) {
     const float inv = 1.0f / l_run;
+    // a kTight row divides, as the combine of its segments does for a single one
+    auto norm = [&](float x) { return kTight ? x / l_run : x * inv; };
     float* op = a.out + ((((int64_t)l * a.batch + b) * a.chunk + row) * a.Hq + h) * D;
 #pragma unroll
     for (int d = 0; d < ND; ++d)
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         float4 v;
-        v.x = o[d][r4 * 4 + 0] * inv;
-        v.y = o[d][r4 * 4 + 1] * inv;
-        v.z = o[d][r4 * 4 + 2] * inv;
-        v.w = o[d][r4 * 4 + 3] * inv;
+        v.x = norm(o[d][r4 * 4 + 0]);
+        v.y = norm(o[d][r4 * 4 + 1]);
+        v.z = norm(o[d][r4 * 4 + 2]);
+        v.w = norm(o[d][r4 * 4 + 3]);
         *reinterpret_cast<float4*>(op + d * 32 + r4 * 8 + half * 4) = v;
       }
   }
@@ -662,7 +676,8 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
 template <typename T, bool kShared, bool kTight>
 hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t stream) {
   const int64_t n_wg = kShared ? (int64_t)a.n_layers * a.Hkv * a.n_shared_split * a.n_qt
-                               : (int64_t)a.n_layers * a.batch * a.Hkv * prefill_head_sets(a.D, a.group) * a.n_qt;
+                               : (int64_t)a.n_layers * a.batch * a.Hkv * prefill_head_sets(a.D, a.group) * a.n_qt *
+                                     (kTight ? a.n_split_max : 1);
   if (n_wg <= 0) return hipSuccess;
   const dim3 grid((unsigned)n_wg);
   switch (a.D) {

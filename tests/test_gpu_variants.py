@@ -20,6 +20,9 @@ GROUP8_CASES = [
     ("fp8", 256, 8, 1, [64], 32, -1, 0, (0,)),
     ("fp8", 128, 16, 2, [0, 31], 64, -1, 0, (0, 33)),
     ("fp8", 64, 8, 1, [200], 5, -1, 0, (0,)),
+    # several 512-key segments: boundaries inside the chunk, windows starting inside a segment
+    ("bf16", 128, 8, 1, [1023, 511], 2, -1, 0, (0, 600)),
+    ("bf16", 256, 8, 1, [1100], 40, -1, 0, (0, 513)),
 ]
 
 
