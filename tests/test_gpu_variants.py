@@ -29,3 +29,41 @@ GROUP8_CASES = [
 @pytest.mark.parametrize("dtype,D,Hq,Hkv,ctxs,chunk,qsig,div,windows", GROUP8_CASES)
 def test_group8_prefill(dtype, D, Hq, Hkv, ctxs, chunk, qsig, div, windows):
     _prefill_case(dtype, D, Hq, Hkv, ctxs, chunk, qsig, windows, div)
+
+
+# The comparison's single pass: rows read as vectors and element by element, fewer elements than
+# lanes, references that have to be raised (spread > e^300), infinities.
+@pytest.mark.parametrize("rows,V,scale", [(1, 1, 1.0), (3, 7, 1.0), (2, 64, 1.0), (3, 4095, 5.0), (2, 4100, 5.0),
+                                          (2, 33_000, 300.0), (1, 10_001, 2000.0)])
+def test_logit_compare_pass(rows, V, scale):
+    import numpy as np
+    import torch
+
+    from oracle.logits import argmax, kl_divergence, log_softmax
+    from paper_2607_14431_amd import harness as h
+    rng = np.random.default_rng(V)
+    a = (rng.normal(size=(rows, V)) * scale).astype(np.float32)
+    b = (a + rng.normal(size=(rows, V)) * 0.1).astype(np.float32)
+    kl, ia, ib = h.compare_logits(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda())
+    want = kl_divergence(a.astype(np.float64), b.astype(np.float64))
+    # T / A and lse_a - lse_b are each off by at most gamma_V of their terms' magnitudes (u = 2^-53):
+    # sum p |a - b| and |max| + log V for the two references and logarithms
+    p = np.exp(log_softmax(a.astype(np.float64)))
+    mag = (p * np.abs(a.astype(np.float64) - b)).sum(axis=1) + np.abs(a).max(axis=1) + np.abs(b).max(axis=1) + np.log(V)
+    assert np.all(np.abs(kl - want) <= 4 * (V + 16) * 2.0 ** -53 * mag)
+    assert np.array_equal(ia, argmax(a)) and np.array_equal(ib, argmax(b))
+
+
+def test_logit_compare_special_values():
+    import numpy as np
+    import torch
+
+    from paper_2607_14431_amd import harness as h
+    inf = np.inf
+    a = np.array([[-inf] * 8, [1, 2, -inf, 0, 0, 0, 0, 0], [1, 2, 3, 4, 5, 6, 7, 7], [np.nan] * 8, [1, inf, 0, 0, 0, 0, 0, 0],
+                  [3, 1, 2, 0, 0, 0, 0, 0]], np.float32)
+    b = np.array([[0] * 8, [1, 2, 0, 0, 0, 0, 0, 0], [1, 2, 3, 4, 5, 6, 7, 7], [0] * 8, [1, 2, 0, 0, 0, 0, 0, 0],
+                  [3, -inf, 2, 0, 0, 0, 0, 0]], np.float32)
+    kl, ia, ib = h.compare_logits(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda())
+    assert np.isnan(kl[[0, 1, 3, 4]]).all() and kl[2] == 0.0 and kl[5] == inf
+    assert list(ia) == [0, 1, 6, 8, 1, 0] and list(ib) == [0, 1, 6, 0, 1, 0]
