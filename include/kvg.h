@@ -284,15 +284,16 @@ size_t kvg_decode_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs, 
  * kvg_append with chunk_len = 1, then attended inclusively over keys [0, ctx_lens[b]]
  * (the last W of them in a layer with window W; ranges entirely before the window are
  * skipped).
- * Grouped-query split-K over fixed 512-token ranges of logical index: each range yields a
- * partial (reference max, sum, weighted V) in fp32 and the partials are combined in
- * ascending range order, so the bytes depend neither on the batch nor on which path filled
- * the cache.  bf16 and fp8 caches hold the rotated query as a bf16 high and low part (each
- * score the sum of both products) and round the softmax weights to bf16 (as the MFMA prefill
- * rounds P), the sum of weights taking the rounded values; fp32 caches keep fp32 queries and
- * weights.  Two
- * launches: the split kernel (which also rotates the queries and appends the new token)
- * and the combine kernel.  Layouts as kvg_prefill_attn with chunk_len = 1.
+ * Grouped-query split-K over fixed 512-token ranges of logical index (in a windowed layer
+ * counted from the page of the first visible key): each range yields a partial (reference
+ * max, sum, weighted V) in fp32 and the partials are combined in ascending range order, so the
+ * bytes depend neither on the batch nor on which path filled the cache.  bf16 and fp8 caches
+ * take a range as four units of 128 tokens, each a softmax state of its own on MFMA, merged in
+ * order; they hold the rotated query as a bf16 high and low part (each score the sum of both
+ * products) and round the softmax weights to bf16 (as the MFMA prefill rounds P), the sum of
+ * weights taking the rounded values; fp32 caches use fp32 vector arithmetic.  Two launches: the
+ * split kernel (which also rotates the queries and appends the new token) and the combine
+ * kernel.  Layouts as kvg_prefill_attn with chunk_len = 1.
  * ws_dev: kvg_decode_workspace_bytes() bytes of scratch (contents undefined after the call).
  * Errors: as kvg_prefill_attn. */
 int kvg_decode_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope,

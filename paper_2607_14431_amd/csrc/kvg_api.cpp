@@ -203,30 +203,52 @@ int shared_splits(const kvg_cache* c, const kvg_seqs* s) {
   return std::min(s->shared_tokens / kSplit, n_split_max(s, 1));
 }
 
-// Splits per (layer, sequence, KV head) in the decode kernel's grid: every split, less the
-// shared ones of full-attention layers (the shared-split kernel's), but at least as many as
-// a windowed layer of the range can have (its splits count from the window's first key).
-int decode_grid_splits(const kvg_cache* c, const kvg_seqs* s, int32_t layer0, int32_t n_layers) {
+// The layers and splits of a decode's grid (DecodeArgs): every split of full-attention layers, less the
+// shared ones (the shared-split kernel's), and of windowed layers as many as the longest of
+// their windows can touch from the page of its first key on.
+struct DecodeGrid {
+  int n_full = 0, n_split_full = 0, n_split_win = 0;
+  uint8_t order[kvg::kMaxWindowLayers] = {};
+  int64_t items = 0;
+};
+
+DecodeGrid decode_grid(const kvg_cache* c, const kvg_seqs* s, int32_t layer0, int32_t n_layers) {
+  DecodeGrid d;
   const int n_split = n_split_max(s, 1);
-  const int shared = shared_splits(c, s);
-  if (shared == 0) return n_split;
-  int grid = n_split - shared;
-  if (c->layer_window != nullptr)
-    for (int l = 0; l < n_layers; ++l) {
-      const int64_t W = c->layer_window[layer0 + l];
-      if (W > 0) grid = std::max<int64_t>(grid, std::min<int64_t>(n_split, (W + kSplit - 1) / kSplit));
-    }
-  return grid;
+  d.n_split_full = n_split - shared_splits(c, s);
+  auto window = [&](int l) -> int64_t { return c->layer_window != nullptr ? c->layer_window[layer0 + l] : 0; };
+  for (int l = 0; l < n_layers; ++l)
+    if (window(l) == 0)
+      ++d.n_full;
+    else
+      d.n_split_win = std::max<int64_t>(d.n_split_win, std::min<int64_t>(n_split, (window(l) + kPage - 1 + kSplit - 1) / kSplit));
+  if (d.n_full != n_layers) {                 // windows: at most kMaxWindowLayers layers (checked)
+    int full = 0, windowed = d.n_full;
+    for (int l = 0; l < n_layers && l < kvg::kMaxWindowLayers; ++l) d.order[window(l) == 0 ? full++ : windowed++] = (uint8_t)l;
+  }
+  d.items = (int64_t)s->batch * c->n_kv_heads * ((int64_t)d.n_full * d.n_split_full + (int64_t)(n_layers - d.n_full) * d.n_split_win);
+  return d;
+}
+
+// Decodes that leave the chip idle give every 128-key unit of a split a wave (DecodeArgs.solo)
+// instead of every split: as long as the waves of all units are resident at once, five on each of 256
+// CUs.  One 12B-class layer over 4.6k keys (72 splits): 36 us with a wave per split, 20 with a
+// wave per unit; 4 sequences (296): 43 and 41; 8 (592): 56 and 63.  A windowed layer's
+// splits are those its window can touch.
+constexpr int kSoloWaves = 5 * 256;
+bool decode_solo(const kvg_cache* c, const kvg_seqs* s, const DecodeGrid& grid) {
+  return c->dtype != KVG_F32 && shared_splits(c, s) == 0 && grid.items * 4 <= kSoloWaves && n_split_max(s, 1) <= kSoloWaves / 4;
 }
 
 struct DecodeWs {
   size_t ml, acc, q, total;
 };
 
-// Split partials, and the rotated bf16 queries of the shared-split kernel when it runs.
-DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
+// Split partials (`per_split` of each), and the rotated bf16 queries of the shared-split kernel when
+// it runs.
+DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, size_t per_split = 1) {
   DecodeWs w;
-  const size_t ns = (size_t)n_split_max(s, 1);
+  const size_t ns = (size_t)n_split_max(s, 1) * per_split;
   const size_t heads = (size_t)n_layers * s->batch * c->n_q_heads;
   w.ml = align_up(heads * ns * 2 * sizeof(float));
   w.acc = align_up(heads * ns * c->head_dim * sizeof(float));
@@ -536,7 +558,14 @@ int kvg_prefill_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rop
 
 size_t kvg_decode_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs, int32_t n_layers) {
   if (check_cache(cache) != KVG_OK || seqs == nullptr || n_layers <= 0 || seqs->batch <= 0) return 0;
-  return decode_ws(cache, seqs, n_layers).total;
+  // Also enough for a wave per unit wherever a call no larger than this one takes it: four partials
+  // per split of every row, which only windowed layers (whose rows hold more splits than
+  // their windows touch) let exceed the resident waves.
+  const size_t unit_bytes = (size_t)(cache->n_q_heads / cache->n_kv_heads) * (cache->head_dim + 2) * sizeof(float);
+  const size_t layout = (size_t)n_layers * seqs->batch * cache->n_kv_heads * n_split_max(seqs, 1) * 4;
+  const size_t most = cache->layer_window != nullptr ? 4 * kSoloWaves : kSoloWaves;
+  const size_t units = cache->dtype == KVG_F32 ? 0 : std::min(most, layout);
+  return std::max(decode_ws(cache, seqs, n_layers).total, units * unit_bytes + 2 * kAlign);
 }
 
 int kvg_decode_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope, int32_t layer0,
@@ -568,8 +597,8 @@ int decode_attn_launch(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_r
   const DecodeWs w = decode_ws(cache, seqs, n_layers);
   if (ws == nullptr || ws_bytes < w.total) return KVG_E_WORKSPACE;
   const int n_split = n_split_max(seqs, 1);
-  const int n_grid = decode_grid_splits(cache, seqs, layer0, n_layers);
-  const int64_t n_blocks = (int64_t)n_layers * seqs->batch * cache->n_kv_heads * n_grid;
+  const DecodeGrid grid = decode_grid(cache, seqs, layer0, n_layers);
+  const int64_t n_blocks = grid.items;
   const int64_t n_rows = (int64_t)n_layers * seqs->batch * cache->n_q_heads;
   if (!fits_grid(n_blocks, 256) || !fits_grid(n_rows, 256) || !append_fits(seqs, 1)) return KVG_E_SHAPE;
   if (shared_splits(cache, seqs) > 0) {
@@ -607,7 +636,14 @@ int decode_attn_launch(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_r
   a.n_split_max = n_split;
   a.shared_order = seqs->shared_tokens > 0 && seqs->batch > 1;
   a.n_shared_split = shared_splits(cache, seqs);
-  a.n_split_grid = n_grid;
+  a.n_full = grid.n_full;
+  a.n_split_full = grid.n_split_full;
+  a.n_split_win = grid.n_split_win;
+  std::memcpy(a.layer_order, grid.order, sizeof(a.layer_order));
+  // the bytes are the same either way, so a workspace that only holds a partial per split is enough
+  const DecodeWs wu = decode_ws(cache, seqs, n_layers, 4);
+  a.solo = decode_solo(cache, seqs, grid) && ws_bytes >= wu.total;
+  if (a.solo) a.part_acc = reinterpret_cast<float*>(base + wu.ml);
   a.pairing = rope->pairing;
   for (int i = 0; i < cache->head_dim / 2; ++i) a.theta[i] = std::pow(rope->base, -2.0 * i / cache->head_dim);
   if (fill_windows(cache, layer0, n_layers, a.window) != KVG_OK) return KVG_E_SHAPE;

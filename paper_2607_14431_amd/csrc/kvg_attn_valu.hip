@@ -1,21 +1,18 @@
-// Grouped-query attention on the vector ALUs, split over keys ("split-K"): the fused decode
-// kernel (one new token per sequence) and the fp32 caches' prefill rows.
+// Grouped-query attention of fp32 caches on the vector ALUs, split over keys ("split-K"): the fused
+// decode kernel (one new token per sequence) and the prefill rows; and the kernels that combine
+// the split partials of every cache type.
 //
-// Work item = (layer, sequence, row, KV head g, split s).  A split is the fixed logical
-// key range [512 s, 512 s + 512) of the row's visible keys [0, n]; the split plan is a
-// function of the row's own length only.  One 256-thread workgroup per work item:
-//   - teams of TL lanes (16, or fewer for narrow rows) each own every NT-th key of the
-//     split (key k0 + team + NT i); lane tl of a team holds 16-byte chunks tl, tl + TL, ...
-//     of the D-wide K and V rows, so a team reads whole rows with 16-byte loads, and each
-//     team keeps up to four keys' rows in flight while it computes.
-//   - q for the `group` query heads that share KV head g sits in registers: for bf16 and
-//     fp8 caches as packed bf16 hi and lo parts (each rotated value is hi + lo to 16
-//     significant bits; a score is two v_dot2_f32_bf16 chains, hi and lo, with fp32
-//     accumulation, added at the end), fp32 otherwise.  fp8 rows are widened to bf16 pairs when consumed (exact: every E4M3 value
-//     is a bf16 value), so an fp8 cache reads half the bytes and computes like a bf16 one.
+// Work item = (layer, sequence, row, KV head g, split s).  A split is a fixed logical key range of
+// the row's visible keys; the split plan is a function of the row's own length and window only.
+// One 256-thread workgroup per work item:
+//   - teams of TL lanes (16) each own every NT-th key of the split (key k0 + team + NT i); lane
+//     tl of a team holds 16-byte chunks tl, tl + TL, ... of the D-wide K and V rows, so a team
+//     reads whole rows with 16-byte loads, and each team keeps up to four keys' rows in flight
+//     while it computes.
+//   - q for the `group` query heads that share KV head g sits in registers.
 //   - per key: partial dot products, an xor butterfly inside the team (every lane ends
 //     with identical bits because each step adds the same two values), then an online
-//     softmax update of the team's running (reference m, sum l, weighted V acc) in fp32
+//     softmax update of the team's running (reference m, sum l, weighted V acc)
 //     with exp2 of pre-scaled scores; the reference m is raised only when a score exceeds
 //     it by more than 2^8, so most keys cost one exp2 and one FMA per element.
 //   - the team states are merged with a fixed xor tree inside each wavefront, then waves
@@ -25,6 +22,7 @@
 // fresh path produce the same bytes.
 #include "kvg_device.h"
 #include "kvg_launch.h"
+#include "kvg_rows.h"
 
 #include <math.h>
 
@@ -38,10 +36,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr float kRescale = 8.0f;     // lazy-rescale threshold of the running reference (log2 units)
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint4 ld16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
 // Cached K/V rows are read once per call: streaming (nontemporal) loads.  Measured on the
 // 12B-class decode (1.83 GB per call over random pages): 326 -> 300 us per call.
 typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
@@ -54,8 +48,6 @@ __device__ __forceinline__ uint4 ld16_stream(const void* p) {
 __device__ __forceinline__ uint4 sel4(bool c, const uint4& a, const uint4& b) {
   return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
 }
-__device__ __forceinline__ void st16(void* p, const uint4& v) { *reinterpret_cast<uint4*>(p) = v; }
-
 struct Soft {
   float m, l;
 };
@@ -98,50 +90,20 @@ struct SplitPages {
   }
 };
 
-// Merge factor exp2(m_part - m_new); a part that saw no key has m = -inf and weight 0.
-__device__ __forceinline__ float merge_factor(float m_part, float m_new) {
-  return (m_part == -INFINITY) ? 0.0f : exp2f(m_part - m_new);
-}
-
-// Chunk of a cache row as bf16 pairs (32-bit words, element order): bf16 chunks are
-// already that; an fp8 chunk (16 values) widens to 8 words, exactly.
-template <typename T>
-__device__ __forceinline__ void bf16_words(const uint4& c, uint32_t* w) {
-  if constexpr (sizeof(T) == 1) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int x = (int)(&c.x)[j];
-      w[2 * j] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x, 1.0f, false));
-      w[2 * j + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x, 1.0f, true));
-    }
-  } else {
-    w[0] = c.x;
-    w[1] = c.y;
-    w[2] = c.z;
-    w[3] = c.w;
-  }
-}
-
-template <typename T, int D, int G>
+template <int D, int G>
 struct SplitWorker {
-  static constexpr int CH = Elem<T>::kPerVec;     // elements per 16-byte chunk
+  static constexpr int CH = Elem<float>::kPerVec; // elements per 16-byte chunk
   static constexpr int NCH = D / CH;              // chunks per row
   static constexpr int TL = NCH < 16 ? NCH : 16;  // lanes per key ("team")
   static constexpr int CPL = NCH / TL;            // chunks per lane
   static constexpr int EPL = CPL * CH;            // elements per lane
   static constexpr int NT = kThreads / TL;        // teams per workgroup
-  static constexpr bool kBf16 = sizeof(T) <= 2;   // packed bf16 arithmetic (bf16 and fp8 caches)
-  static constexpr int WPC = CH / 2;              // bf16 pairs per chunk (packed arithmetic)
-  using QD = typename RawOf<T>::type;             // query dtype: bf16 for fp8 caches
-  static constexpr int QC = CH / Elem<QD>::kPerVec;   // query chunks per cache chunk
-  static constexpr int QW = kBf16 ? CPL * WPC : EPL;
   // key pairs in flight per team (the consumption order, and so the arithmetic, does not
-  // depend on it; four pairs for fp8 rows measured no faster than two)
+  // depend on it)
   static constexpr int kPairs = 2;
   static_assert(CPL >= 1 && (64 % TL) == 0 && TL >= 4, "unsupported head_dim");
   // a wave's teams never straddle a logical page: (64 / TL) teams per wave divide 16
   static_assert(kThreads / TL >= kPage, "teams per workgroup");
-  using QT = typename std::conditional<kBf16, uint32_t, float>::type;
 
   struct Row {
     uint4 k[CPL], v[CPL];
@@ -149,8 +111,7 @@ struct SplitWorker {
     bool lds;          // the new decode token: rows come from LDS when consumed
   };
 
-  QT q[G][QW];
-  uint32_t ql[kBf16 ? G : 1][kBf16 ? QW : 1];   // bf16 caches: the queries' lo parts
+  float q[G][EPL];
   float acc[G][EPL];
   Soft st[G];
   int tl, team, lane, wave;
@@ -171,26 +132,13 @@ struct SplitWorker {
     }
   }
 
-  // Query chunk j of this lane (16 bytes of QD): the lane's cache chunk j / QC, part
-  // j % QC.  q_chunk(j) is its index among the row's D / kPerVec(QD) query chunks.
-  __device__ __forceinline__ int q_chunk(int j) const { return (tl + TL * (j / QC)) * QC + j % QC; }
-  // v: the chunk (bf16 hi parts for bf16 and fp8 caches), vl: the lo parts (bf16 only)
-  __device__ __forceinline__ void set_q(int h, int j, const uint4& v, const uint4& vl) {
-    if constexpr (kBf16) {
-      q[h][j * 4 + 0] = v.x;
-      q[h][j * 4 + 1] = v.y;
-      q[h][j * 4 + 2] = v.z;
-      q[h][j * 4 + 3] = v.w;
-      ql[h][j * 4 + 0] = vl.x;
-      ql[h][j * 4 + 1] = vl.y;
-      ql[h][j * 4 + 2] = vl.z;
-      ql[h][j * 4 + 3] = vl.w;
-    } else {
-      q[h][j * 4 + 0] = __uint_as_float(v.x);
-      q[h][j * 4 + 1] = __uint_as_float(v.y);
-      q[h][j * 4 + 2] = __uint_as_float(v.z);
-      q[h][j * 4 + 3] = __uint_as_float(v.w);
-    }
+  // Query chunk j of this lane is chunk q_chunk(j) of the row's.
+  __device__ __forceinline__ int q_chunk(int j) const { return tl + TL * j; }
+  __device__ __forceinline__ void set_q(int h, int j, const uint4& v) {
+    q[h][j * 4 + 0] = __uint_as_float(v.x);
+    q[h][j * 4 + 1] = __uint_as_float(v.y);
+    q[h][j * 4 + 2] = __uint_as_float(v.z);
+    q[h][j * 4 + 3] = __uint_as_float(v.w);
   }
 
   // Branches in the consume functions are uniform over the wavefront (ballots), so the
@@ -211,36 +159,17 @@ struct SplitWorker {
 
   // the key's scores for the G heads (log2 units), -inf for a key that is not ok
   __device__ __forceinline__ void scores(const Row& rw, float scale_log2, float (&s2)[G]) {
-    float sc[G], sl[G];
+    float sc[G];
 #pragma unroll
-    for (int h = 0; h < G; ++h) sc[h] = sl[h] = 0.0f;
+    for (int h = 0; h < G; ++h) sc[h] = 0.0f;
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      if constexpr (kBf16) {
-        uint32_t kw[WPC];
-        bf16_words<T>(rw.k[i], kw);
+    for (int i = 0; i < CPL; ++i)
 #pragma unroll
-        for (int dw = 0; dw < WPC; ++dw)
+      for (int e = 0; e < CH; ++e) {
+        const float kf = Elem<float>::get(rw.k[i], e);
 #pragma unroll
-          for (int h = 0; h < G; ++h) {
-            sc[h] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[h][i * WPC + dw]),
-                                                    __builtin_bit_cast(bf16x2, kw[dw]), sc[h], false);
-            sl[h] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, ql[h][i * WPC + dw]),
-                                                    __builtin_bit_cast(bf16x2, kw[dw]), sl[h], false);
-          }
-      } else {
-#pragma unroll
-        for (int e = 0; e < CH; ++e) {
-          const float kf = Elem<T>::get(rw.k[i], e);
-#pragma unroll
-          for (int h = 0; h < G; ++h) sc[h] = fmaf(q[h][i * CH + e], kf, sc[h]);
-        }
+        for (int h = 0; h < G; ++h) sc[h] = fmaf(q[h][i * CH + e], kf, sc[h]);
       }
-    }
-    if constexpr (kBf16) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) sc[h] += sl[h];
-    }
 #pragma unroll
     for (int h = 0; h < G; ++h) s2[h] = rw.ok ? team_sum<TL>(sc[h]) * scale_log2 : -INFINITY;
   }
@@ -259,7 +188,7 @@ struct SplitWorker {
     }
   }
 
-  // fp32 caches: one key, p and the weighted V in fp32
+  // one key, p and the weighted V in fp32
   __device__ __forceinline__ void consume(Row& rw, float scale_log2) {
     fix_row(rw);
     float s2[G];
@@ -272,57 +201,8 @@ struct SplitWorker {
 #pragma unroll
       for (int i = 0; i < CPL; ++i) {
 #pragma unroll
-        for (int e = 0; e < CH; ++e) acc[h][i * CH + e] = fmaf(p, Elem<T>::get(rw.v[i], e), acc[h][i * CH + e]);
+        for (int e = 0; e < CH; ++e) acc[h][i * CH + e] = fmaf(p, Elem<float>::get(rw.v[i], e), acc[h][i * CH + e]);
       }
-    }
-  }
-
-  // bf16 caches: two keys a, b.  Their weights are rounded to bf16 (as the MFMA prefill
-  // rounds P) and the sum takes the rounded values, so the output stays a normalised
-  // average; acc[e] += pa v_a[e] + pb v_b[e] is one v_dot2_f32_bf16 on (pa, pb) and the
-  // pair (v_a[e], v_b[e]) assembled by one byte permute.
-  __device__ __forceinline__ void consume_pair(Row& ra, Row& rb, float scale_log2) {
-    fix_row(ra);
-    fix_row(rb);
-    float sa[G], sb[G];
-    scores(ra, scale_log2, sa);
-    scores(rb, scale_log2, sb);
-    uint32_t va[CPL][WPC], vb[CPL][WPC];            // V rows as bf16 pairs, shared by the heads
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      bf16_words<T>(ra.v[i], va[i]);
-      bf16_words<T>(rb.v[i], vb[i]);
-    }
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      raise_to(h, fmaxf(sa[h], sb[h]));
-      const float pa = ra.ok ? __builtin_amdgcn_exp2f(sa[h] - st[h].m) : 0.0f;
-      const float pb = rb.ok ? __builtin_amdgcn_exp2f(sb[h] - st[h].m) : 0.0f;
-      const bf16x2 pp = __builtin_convertvector((f32x2){pa, pb}, bf16x2);
-      st[h].l += (float)pp.x;
-      st[h].l += (float)pp.y;
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-#pragma unroll
-        for (int dw = 0; dw < WPC; ++dw) {
-          // (v_a[2dw], v_b[2dw]) and (v_a[2dw+1], v_b[2dw+1]) as bf16 pairs
-          const uint32_t lo = __builtin_amdgcn_perm(vb[i][dw], va[i][dw], 0x05040100u);
-          const uint32_t hi = __builtin_amdgcn_perm(vb[i][dw], va[i][dw], 0x07060302u);
-          float& a0 = acc[h][i * CH + 2 * dw];
-          float& a1 = acc[h][i * CH + 2 * dw + 1];
-          a0 = __builtin_amdgcn_fdot2_f32_bf16(pp, __builtin_bit_cast(bf16x2, lo), a0, false);
-          a1 = __builtin_amdgcn_fdot2_f32_bf16(pp, __builtin_bit_cast(bf16x2, hi), a1, false);
-        }
-      }
-    }
-  }
-
-  __device__ __forceinline__ void consume2(Row& ra, Row& rb, float scale_log2) {
-    if constexpr (kBf16) {
-      consume_pair(ra, rb, scale_log2);
-    } else {
-      consume(ra, scale_log2);
-      consume(rb, scale_log2);
     }
   }
 
@@ -355,7 +235,8 @@ struct SplitWorker {
     for (int it = 0; it < n_it; it += R) {
 #pragma unroll
       for (int p = 0; p < kPairs; ++p) {
-        consume2(rows[2 * p], rows[2 * p + 1], scale_log2);
+        consume(rows[2 * p], scale_log2);
+        consume(rows[2 * p + 1], scale_log2);
         __builtin_amdgcn_sched_barrier(0);
         fetch(j + (R + 2 * p) * NT, rows[2 * p]);
         fetch(j + (R + 2 * p + 1) * NT, rows[2 * p + 1]);
@@ -464,7 +345,7 @@ __device__ __forceinline__ float combine_splits(const float* ml, const float* ac
 // writes its split partial, combined by attn_merge_kernel.
 template <int D, int G>
 __global__ __launch_bounds__(kThreads) void attn_partial_kernel(const AttnArgs a) {
-  using W = SplitWorker<float, D, G>;
+  using W = SplitWorker<D, G>;
   int64_t w = blockIdx.x;
   const int s = (int)(w % a.n_split_max);  w /= a.n_split_max;
   const int g = (int)(w % a.Hkv);          w /= a.Hkv;
@@ -490,7 +371,7 @@ __global__ __launch_bounds__(kThreads) void attn_partial_kernel(const AttnArgs a
 #pragma unroll
     for (int j = 0; j < W::CPL; ++j) {
       const uint4 v = ld16(qp + wk.q_chunk(j) * 4);
-      wk.set_q(h, j, v, v);
+      wk.set_q(h, j, v);
     }
   }
 
@@ -559,104 +440,14 @@ __global__ __launch_bounds__(kThreads) void attn_merge_kernel(const AttnArgs a) 
 // is finished in place; longer ones are combined by decode_merge_kernel in ascending split
 // order.  (Combining in the last-arriving workgroup would need a device-scope release per
 // workgroup, an L2 write-back on this chip that cost more than the second launch.)
-template <typename T>
-__device__ __forceinline__ void rotate_chunk(const uint4& va, const uint4& vb, bool first_half, int pair0,
-                                             int pairing, const float* cs, float* out) {
-  constexpr int E = Elem<T>::kPerVec;
-  if (pairing == 0) {
-    // va: this chunk, vb: its partner D/2 away; pair index pair0 + e
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      float x = first_half ? Elem<T>::get(va, e) : Elem<T>::get(vb, e);   // first-half element
-      float y = first_half ? Elem<T>::get(vb, e) : Elem<T>::get(va, e);   // second-half element
-      rotate_pair(x, y, cs[2 * (pair0 + e)], cs[2 * (pair0 + e) + 1]);
-      out[e] = first_half ? x : y;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < E; e += 2) {
-      float x = Elem<T>::get(va, e), y = Elem<T>::get(va, e + 1);
-      const int p = pair0 + (e >> 1);
-      rotate_pair(x, y, cs[2 * p], cs[2 * p + 1]);
-      out[e] = x;
-      out[e + 1] = y;
-    }
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ uint4 pack_chunk(const float* x) {
-  constexpr int E = Elem<T>::kPerVec;
-  uint4 v = make_uint4(0, 0, 0, 0);
-#pragma unroll
-  for (int e = 0; e < E; ++e) Elem<T>::put(v, e, x[e]);
-  return v;
-}
-
-// Rotated values of 16-byte chunk c of a raw row (pairing-aware), in fp32.
-template <typename T, int D>
-__device__ __forceinline__ void rotated_values(const T* raw_row, int c, int pairing, const float* cs, float* x) {
-  constexpr int E = Elem<T>::kPerVec;
-  constexpr int NCH = D / E;
-  const uint4 va = ld16(raw_row + c * E);
-  if (pairing == 0) {
-    const bool first = c < NCH / 2;
-    const int cp = first ? c + NCH / 2 : c - NCH / 2;
-    const uint4 vb = ld16(raw_row + cp * E);
-    rotate_chunk<T>(va, vb, first, (first ? c : cp) * E, 0, cs, x);
-  } else {
-    rotate_chunk<T>(va, va, true, c * E / 2, 1, cs, x);
-  }
-}
-
-// Rotated 16-byte query chunk c of a raw row: for bf16 rows as the hi and lo parts of
-// split_bf16, for fp32 rows the values themselves (lo unused).
-template <typename T, int D>
-__device__ __forceinline__ void rotated_query_chunk(const T* raw_row, int c, int pairing, const float* cs, uint4& hi,
-                                                    uint4& lo) {
-  constexpr int E = Elem<T>::kPerVec;
-  float x[E];
-  rotated_values<T, D>(raw_row, c, pairing, cs, x);
-  if constexpr (sizeof(T) == 2) {
-    uint32_t h[E], l[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) split_bf16(x[e], h[e], l[e]);
-    hi = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-    lo = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
-  } else {
-    hi = pack_chunk<T>(x);
-    lo = hi;
-  }
-}
-
-// Chunk c of a storage row of type T (rotated or not) from a raw row of type R: the raw
-// chunks it covers (two bf16 chunks per fp8 chunk), rounded once to T.
-template <typename T, typename R, int D>
-__device__ __forceinline__ uint4 storage_chunk(const R* raw_row, int c, bool rotate, int pairing, const float* cs) {
-  constexpr int ET = Elem<T>::kPerVec, ER = Elem<R>::kPerVec, P = ET / ER;
-  float x[ET];
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    if (rotate) {
-      rotated_values<R, D>(raw_row, c * P + p, pairing, cs, x + p * ER);
-    } else {
-      const uint4 v = ld16(raw_row + (c * P + p) * ER);
-#pragma unroll
-      for (int e = 0; e < ER; ++e) x[p * ER + e] = Elem<R>::get(v, e);
-    }
-  }
-  uint32_t w[4];
-  pack_words<T, ET>(x, w);
-  return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-template <typename T, int D, int G>
+template <int D, int G>
 __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
-  using W = SplitWorker<T, D, G>;
-  using R = typename W::QD;                         // raw input type (bf16 for fp8 caches)
-  constexpr int NCH = W::NCH;                       // 16-byte chunks of a cache row
+  using W = SplitWorker<D, G>;
+  using R = float;                                  // raw rows and cache rows
+  using T = float;
+  constexpr int NCH = W::NCH;                       // 16-byte chunks of a row
   constexpr int ER = Elem<R>::kPerVec;
-  constexpr int NCHR = D / ER;                      // 16-byte chunks of a raw row
+  constexpr int NCHR = NCH;
   // Sequence index fastest.  When the sequences share leading pages (a shared window,
   // shared_order), runs of 64 consecutive work items go to one XCD (workgroups are dealt
   // to the 8 XCDs in turn), so the sequences reading the same keys do so at about the same
@@ -672,10 +463,8 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
       w = ((g8 / CH) * 8 + w % 8) * CH + g8 % CH;
     }
   }
-  const int b = (int)(w % a.batch);        w /= a.batch;
-  const int si = (int)(w % a.n_split_grid); w /= a.n_split_grid;
-  const int g = (int)(w % a.Hkv);          w /= a.Hkv;
-  const int l = (int)w;
+  const DecodeItem item = decode_item(a, w);
+  const int b = item.b, si = item.si, g = item.g, l = item.l;
 
   const int tid = threadIdx.x;
   constexpr int QCH = G * NCHR;                     // 16-byte chunks of the group's raw q
@@ -707,13 +496,13 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
   if (ctx < 0 || ctx > a.max_ctx_len) return;
   const int n_keys = ctx + 1;                     // the new token is key ctx
   const int lo = window_start(win, n_keys);
-  const int n_split = split_count(n_keys, lo);
+  const int base = split_base(lo);
+  const int n_split = split_count(n_keys, base);
   if (s >= n_split) return;
-  const int k0 = lo + s * kSplit;                 // the split's keys [k0, k1)
+  const int k0 = base + s * kSplit;               // the split's keys [k0, k1), those below lo masked
   const int k1 = min(k0 + kSplit, n_keys);
-  const int kb = k0 & ~(kPage - 1);               // teams start at the page holding k0
   const bool last_split = s == n_split - 1;
-  if (win != 0) sp.init(bt, kb / kPage, a.max_pages, tid & 63);
+  if (win != 0) sp.init(bt, k0 / kPage, a.max_pages, tid & 63);
 
   __shared__ float cs[2 * kMaxHalfDim];
   __shared__ uint4 new_k[NCH], new_v[NCH];
@@ -738,7 +527,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
     const int32_t page = sp.page_of(j);
     const bool valid = page >= 0 && page < a.n_pages;
     rw.lds = j == ctx;
-    rw.ok = rw.lds || (valid && j >= k0);
+    rw.ok = rw.lds || (valid && j >= lo);
     const int64_t roff = (((int64_t)(valid ? page : 0) * a.Hkv + g) * kPage + (j % kPage)) * D;
 #pragma unroll
     for (int i = 0; i < W::CPL; ++i) rw.k[i] = ld16_stream(kpool + roff + (wk.tl + W::TL * i) * W::CH);
@@ -765,13 +554,13 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
     // the new token's V in the cache dtype (every split: a row equal to key ctx is taken
     // from LDS when it is consumed, which only the last split does)
     for (int c = tid; c < NCH; c += kThreads)
-      new_v[c] = storage_chunk<T, R, D>(reinterpret_cast<const R*>(raw_v), c, false, a.pairing, cs);
+      new_v[c] = storage_chunk<D>(reinterpret_cast<const float*>(raw_v), c, false, a.pairing, cs);
     if (last_split) {
       const int32_t page = sp.page_of(ctx);
       const bool ok = page >= 0 && page < a.n_pages;
       const int64_t roff = (((int64_t)(ok ? page : 0) * a.Hkv + g) * kPage + (ctx % kPage)) * D;
       for (int c = tid; c < NCH; c += kThreads) {
-        const uint4 kc = storage_chunk<T, R, D>(reinterpret_cast<const R*>(raw_k), c, true, a.pairing, cs);
+        const uint4 kc = storage_chunk<D>(reinterpret_cast<const float*>(raw_k), c, true, a.pairing, cs);
         new_k[c] = kc;
         if (ok) {
           st16(kpool + roff + c * W::CH, kc);
@@ -783,13 +572,10 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
 #pragma unroll
     for (int h = 0; h < G; ++h)
 #pragma unroll
-      for (int j = 0; j < W::CPL * W::QC; ++j) {
-        uint4 hi, lo;
-        rotated_query_chunk<R, D>(reinterpret_cast<const R*>(raw_q) + h * D, wk.q_chunk(j), a.pairing, cs, hi, lo);
-        wk.set_q(h, j, hi, lo);
-      }
+      for (int j = 0; j < W::CPL; ++j)
+        wk.set_q(h, j, storage_chunk<D>(reinterpret_cast<const float*>(raw_q) + h * D, wk.q_chunk(j), true, a.pairing, cs));
   };
-  wk.run(kb, k1, a.scale_log2, load, prologue);
+  wk.run(k0, k1, a.scale_log2, load, prologue);
 
   wk.to_lds(s_acc, s_ml);
   __syncthreads();
@@ -845,7 +631,7 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
     const int ctx = a.ctx_lens[b];
     if (ctx < 0 || ctx > a.max_ctx_len) return;
     const int win = layer_window(a, l);
-    const int n_split = split_count(ctx + 1, window_start(win, ctx + 1));
+    const int n_split = split_count(ctx + 1, split_base(window_start(win, ctx + 1)));
     if (n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;   // written by the split kernel
     float m = -INFINITY;
 #pragma unroll
@@ -864,40 +650,10 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
   const int ctx = a.ctx_lens[b];
   if (ctx < 0 || ctx > a.max_ctx_len) return;
   const int win = layer_window(a, l);
-  const int n_split = split_count(ctx + 1, window_start(win, ctx + 1));
+  const int n_split = split_count(ctx + 1, split_base(window_start(win, ctx + 1)));
   if (n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;     // written by the split kernel
   const float* ml = a.part_ml + row_head * a.n_split_max * 2;
   const float* acc = a.part_acc + row_head * a.n_split_max * a.D;
-  constexpr int kLdsSplits = 2048;
-  if (n_split <= kLdsSplits) {
-    // Many splits (long contexts, shared windows): the (reference, sum) pairs are staged in
-    // LDS by the whole workgroup in one round trip, and each lane requests 16 splits' values
-    // at a time; the arithmetic and its order are combine_splits' own.
-    __shared__ float s_ml[2 * kLdsSplits];
-    for (int t = threadIdx.x; t < 2 * n_split; t += kThreads) s_ml[t] = ml[t];
-    __syncthreads();
-    float m = -INFINITY;
-    for (int s = 0; s < n_split; ++s) m = fmaxf(m, s_ml[2 * s]);
-    constexpr int U = 16;
-    for (int d = threadIdx.x; d < a.D; d += kThreads) {
-      float lsum = 0.0f, o = 0.0f;
-      for (int s0 = 0; s0 < n_split; s0 += U) {
-        float av[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) av[u] = acc[min(s0 + u, n_split - 1) * a.D + d];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int s = min(s0 + u, n_split - 1);
-          const float f = merge_factor(s_ml[2 * s], m);
-          const bool in = s0 + u < n_split;
-          lsum = in ? fmaf(s_ml[2 * s + 1], f, lsum) : lsum;
-          o = in ? fmaf(av[u], f, o) : o;
-        }
-      }
-      a.out[row_head * a.D + d] = o / lsum;
-    }
-    return;
-  }
   for (int d = threadIdx.x; d < a.D; d += kThreads)
     a.out[row_head * a.D + d] = combine_splits(ml, acc + d, a.D, n_split);
 }
@@ -915,25 +671,135 @@ hipError_t launch_partial_g(const AttnArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <typename T, int D>
+// Combine of rows with many splits, or (kSolo, DecodeArgs.solo) with four partials per split: the
+// units of a split merged in order, then the splits in ascending order, combine_splits' own
+// arithmetic.  A workgroup per (layer, sequence, query head): the splits' (reference, sum) pairs
+// and weights are worked out once, in LDS; the lane groups then bring kMergeChunk splits' values
+// at a time (every partial requested at once), and one lane per element sums them in order.  256
+// rows of 66 splits took 15 us on one group of lanes, 11 us here.
+constexpr int kMergeThreads = 1024;
+constexpr int kMergeChunk = 32;
+template <bool kSolo>
+__global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const DecodeArgs a) {
+  constexpr int U = kSolo ? 4 : 1;                         // partials per split
+  const int64_t row_head = blockIdx.x;
+  const int b = (int)((row_head / a.Hq) % a.batch);
+  const int l = (int)(row_head / ((int64_t)a.Hq * a.batch));
+  const int D = a.D;
+  const int groups = kMergeThreads / D;
+  const int tid = threadIdx.x, d = tid % D, gi = tid / D;
+  const float* ml = a.part_ml + row_head * a.n_split_max * U * 2;
+  const float* acc = a.part_acc + row_head * a.n_split_max * U * D + d;
+  const int ctx = a.ctx_lens[b];
+  if (ctx < 0 || ctx > a.max_ctx_len) return;
+  const int win = layer_window(a, l);
+  const int base = split_base(window_start(win, ctx + 1));
+  const int n_split = split_count(ctx + 1, base);
+  if (!kSolo && n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;   // written by the split kernel
+  const int n_unit = (ctx - base) / kUnit + 1;             // units that hold keys (kSolo)
+  if (kSolo && n_unit == 1) return;                        // written by the split kernel
+  extern __shared__ float s_mem[];
+  float* s_m = s_mem;                                      // [split] reference, then weight
+  float* s_l = s_m + a.n_split_max;                        // [split] sum
+  float* s_u = s_l + a.n_split_max;                        // kSolo: [split][6] factors of units 1..3
+  float* s_o = s_u + (kSolo ? 6 : 0) * a.n_split_max;      // [kMergeChunk][D]
+  __shared__ float s_max[kMergeThreads / 64];
+
+  float mx = -INFINITY;
+  for (int s = tid; s < n_split; s += kMergeThreads) {
+    float2 p = *reinterpret_cast<const float2*>(ml + s * U * 2);
+    if constexpr (kSolo) {
+      float2 pu[3];
+#pragma unroll
+      for (int u = 1; u < 4; ++u) pu[u - 1] = *reinterpret_cast<const float2*>(ml + min(s * 4 + u, n_unit - 1) * 2);
+#pragma unroll
+      for (int u = 1; u < 4; ++u) {
+        const bool in = s * 4 + u < n_unit;
+        const float m_new = fmaxf(p.x, in ? pu[u - 1].x : p.x);
+        const float f_me = merge_factor(p.x, m_new);
+        const float f_o = in ? merge_factor(pu[u - 1].x, m_new) : 0.0f;
+        p.y = in ? fmaf(p.y, f_me, pu[u - 1].y * f_o) : p.y;
+        p.x = m_new;
+        s_u[s * 6 + 2 * (u - 1)] = f_me;
+        s_u[s * 6 + 2 * (u - 1) + 1] = f_o;
+      }
+    }
+    s_m[s] = p.x;
+    s_l[s] = p.y;
+    mx = fmaxf(mx, p.x);
+  }
+#pragma unroll
+  for (int x = 32; x >= 1; x >>= 1) mx = fmaxf(mx, __shfl_xor(mx, x));
+  if (tid % 64 == 0) s_max[tid / 64] = mx;
+  __syncthreads();
+  float m = s_max[0];
+#pragma unroll
+  for (int w = 1; w < kMergeThreads / 64; ++w) m = fmaxf(m, s_max[w]);
+  for (int s = tid; s < n_split; s += kMergeThreads) s_m[s] = merge_factor(s_m[s], m);
+  __syncthreads();
+
+  float lsum = 0.0f, o = 0.0f;
+  for (int c0 = 0; c0 < n_split; c0 += kMergeChunk) {
+    // splits c0 + gi, + groups, ... of this chunk, two at a time
+    for (int s0 = c0 + gi; s0 < min(c0 + kMergeChunk, n_split); s0 += 2 * groups) {
+      float av[2][U];
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int s = min(s0 + k * groups, n_split - 1);
+          av[k][u] = acc[(int64_t)(kSolo ? min(s * 4 + u, n_unit - 1) : s) * D];
+        }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int s = s0 + k * groups;
+        float v = av[k][0];
+        if constexpr (kSolo) {
+          const float* f = s_u + min(s, n_split - 1) * 6;
+#pragma unroll
+          for (int u = 1; u < 4; ++u) v = s * 4 + u < n_unit ? fmaf(v, f[2 * (u - 1)], av[k][u] * f[2 * (u - 1) + 1]) : v;
+        }
+        if (s < min(c0 + kMergeChunk, n_split)) s_o[(s - c0) * D + d] = v;
+      }
+    }
+    __syncthreads();
+    if (gi == 0) {
+      const int n = min(kMergeChunk, n_split - c0);
+#pragma unroll 8
+      for (int i = 0; i < n; ++i) {
+        const float f = s_m[c0 + i];
+        lsum = fmaf(s_l[c0 + i], f, lsum);
+        o = fmaf(s_o[i * D + d], f, o);
+      }
+    }
+    __syncthreads();
+  }
+  if (gi == 0) a.out[row_head * D + d] = o / lsum;
+}
+
+// Bytes of LDS merge_splits_kernel takes; a decode with more splits than fit combines without it.
+size_t merge_lds(const DecodeArgs& a) {
+  return ((size_t)a.n_split_max * (a.solo ? 8 : 2) + (size_t)kMergeChunk * a.D) * sizeof(float);
+}
+
+template <int D>
 hipError_t launch_decode_g(const DecodeArgs& a, hipStream_t stream) {
-  const int64_t n_blocks = (int64_t)a.n_layers * a.batch * a.Hkv * a.n_split_grid;
+  const int64_t n_blocks = decode_items(a);
   switch (a.group) {
-    case 1: decode_kernel<T, D, 1><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 2: decode_kernel<T, D, 2><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 4: decode_kernel<T, D, 4><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 8: decode_kernel<T, D, 8><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 1: decode_kernel<D, 1><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 2: decode_kernel<D, 2><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 4: decode_kernel<D, 4><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
+    case 8: decode_kernel<D, 8><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_decode_d(const DecodeArgs& a, hipStream_t stream) {
+hipError_t launch_decode_f32(const DecodeArgs& a, hipStream_t stream) {
   switch (a.D) {
-    case 64: return launch_decode_g<T, 64>(a, stream);
-    case 128: return launch_decode_g<T, 128>(a, stream);
-    case 256: return launch_decode_g<T, 256>(a, stream);
+    case 64: return launch_decode_g<64>(a, stream);
+    case 128: return launch_decode_g<128>(a, stream);
+    case 256: return launch_decode_g<256>(a, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1005,12 +871,18 @@ hipError_t launch_prefill_combine(const PrefillArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream) {
-  hipError_t e = dtype == kDtypeBf16  ? launch_decode_d<uint16_t>(a, stream)
-                 : dtype == kDtypeFp8 ? launch_decode_d<uint8_t>(a, stream)
-                                      : launch_decode_d<float>(a, stream);
+  const hipError_t e = decode_items(a) == 0   ? hipSuccess
+                       : dtype == kDtypeF32 ? launch_decode_f32(a, stream)
+                                            : launch_decode_mfma(a, dtype, stream);
   if (e != hipSuccess) return e;
   const int64_t n_rows = (int64_t)a.n_layers * a.batch * a.Hq;
-  decode_merge_kernel<<<dim3((unsigned)n_rows), kThreads, 0, stream>>>(a);
+  const dim3 grid((unsigned)n_rows);
+  if (a.solo)
+    merge_splits_kernel<true><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
+  else if (a.n_split_max > 16 && merge_lds(a) <= 65536)
+    merge_splits_kernel<false><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
+  else
+    decode_merge_kernel<<<grid, kThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 

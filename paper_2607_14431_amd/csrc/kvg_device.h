@@ -9,6 +9,7 @@ namespace kvg {
 constexpr int kPage = 16;           // tokens per page (the only supported page size)
 constexpr int kMaxWindowLayers = 128;  // per-layer sliding windows a launch carries
 constexpr int kSplit = 512;         // decode split-K range: 32 pages of logical index
+constexpr int kUnit = 128;          // decode: keys of one softmax state (bf16 and fp8 caches)
 constexpr int kMaxHalfDim = 128;    // head_dim <= 256
 
 // ---- storage element traits -------------------------------------------------------
@@ -195,12 +196,37 @@ struct DecodeArgs {
   int32_t layer0, n_layers, batch, max_pages, max_ctx_len, n_split_max, pairing;
   int32_t shared_order;       // sequences share leading pages: run equal work items together
   int32_t n_shared_split;     // splits [0, n) of full-attention layers come from the shared-split kernel
-  // splits per (layer, sequence, KV head) in the grid: a full-attention layer's item i is
-  // split n_shared_split + i, a windowed layer's split i
-  int32_t n_split_grid;
+  // The grid: n_full full-attention layers with n_split_full splits per (sequence, KV head) (item i is
+  // split n_shared_split + i), then the windowed layers with n_split_win, as many as any of their
+  // windows can touch.  layer_order: the launch's layers in that order (only read when some
+  // are windowed).
+  int32_t n_full, n_split_full, n_split_win;
+  uint8_t layer_order[kMaxWindowLayers];
+  int32_t solo;               // a wave per 128-key unit: four partials per split in part_acc / part_ml
   double theta[kMaxHalfDim];
   int32_t window[kMaxWindowLayers];
 };
+
+// Work item w of a decode grid, the sequence fastest: layer of the launch, KV head, split of the
+// grid, sequence.
+struct DecodeItem {
+  int l, g, si, b;
+};
+__device__ __forceinline__ DecodeItem decode_item(const DecodeArgs& a, int64_t w) {
+  DecodeItem it;
+  it.b = (int)(w % a.batch);
+  w /= a.batch;
+  const int64_t full = (int64_t)a.n_full * a.Hkv * a.n_split_full;
+  const bool win = w >= full;
+  const int ns = win ? a.n_split_win : a.n_split_full;
+  w -= win ? full : 0;
+  it.si = (int)(w % ns);
+  w /= ns;
+  it.g = (int)(w % a.Hkv);
+  it.l = (int)(w / a.Hkv) + (win ? a.n_full : 0);
+  if (a.n_full != a.n_layers) it.l = a.layer_order[it.l];
+  return it;
+}
 
 struct PrefillArgs {
   const void* k_pool;
@@ -242,6 +268,8 @@ __device__ __forceinline__ int window_start(int W, int n_keys) {
 // Split-K plan of a row that sees keys [lo, n_keys): splits of kSplit keys from lo on
 // (split s = keys [lo + kSplit s, lo + kSplit (s + 1))), a function of the row's own
 // length and window only.  Full attention (lo = 0) splits at multiples of kSplit.
+// The decode's splits start at the page of the first visible key, so that whole pages are read.
+__device__ __forceinline__ int split_base(int lo) { return lo & ~(kPage - 1); }
 __device__ __forceinline__ int split_count(int n_keys, int lo) { return (n_keys - lo + kSplit - 1) / kSplit; }
 
 }  // namespace kvg

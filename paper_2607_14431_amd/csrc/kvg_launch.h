@@ -32,6 +32,12 @@ hipError_t launch_prefill_combine(const PrefillArgs& a, hipStream_t stream);
 // 8 query heads per KV head: out = each row's partials of the kSplit-key segments it sees
 hipError_t launch_prefill_segments(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream);
+// work items (a split of a KV head of a layer of a sequence) of a decode's grid
+inline int64_t decode_items(const DecodeArgs& a) {
+  return (int64_t)a.batch * a.Hkv * ((int64_t)a.n_full * a.n_split_full + (int64_t)(a.n_layers - a.n_full) * a.n_split_win);
+}
+// its split kernel for bf16 and fp8 caches (kvg_decode_mfma.hip)
+hipError_t launch_decode_mfma(const DecodeArgs& a, int dtype, hipStream_t stream);
 
 
 // The decode call split at its workspace (kvg_api.cpp): argument validation, the workspace

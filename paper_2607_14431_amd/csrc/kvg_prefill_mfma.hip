@@ -46,8 +46,8 @@
 // Every MFMA step is a scheduling region of its own (scheduling barriers), holding the step's
 // LDS reads, its share of the tile loads and, in the overlapped phases, one piece of the other
 // block's softmax.
-#include "kvg_device.h"
 #include "kvg_launch.h"
+#include "kvg_mfma.h"
 
 #include <limits.h>
 #include <math.h>
@@ -59,45 +59,11 @@ namespace kvg {
 
 namespace {
 
-// A lane's value and that of lane ^ 32, as (the value in lanes 0-31, the value in lanes
-// 32-63): both halves of the wave get the same pair, so a reduction of the two is the same
-// bits in both.  A VALU half swap, where a cross-lane shuffle would be an LDS round trip whose
-// wait also drains every LDS read issued before it.
-__device__ inline float2 halves32(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-typedef __attribute__((address_space(3))) char lds_char;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) u32x2 lds_u32x2;
-typedef int i32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
-
 constexpr int kTileKeys = 64;
-// Fourth word of a raw buffer resource on gfx9-family targets (32-bit data format, no
-// swizzle): accesses past num_records return zeros instead of touching memory.
-constexpr int kBufferWord3 = 0x00020000;
 // LDS fragments read ahead of the MFMAs that use them at head_dim 256 (K and Vᵀ streams)
 constexpr int kLookK256 = 6;
 constexpr int kLookV256 = 6;
 constexpr float kRescale = 8.0f;  // lazy-rescale threshold of a row's reference (log2 units)
-
-__device__ __forceinline__ bf16x8 as_bf16x8(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
-
-// two fp32 -> packed bf16, round to nearest even (v_cvt_pk_bf16_f32)
-__device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
-}
 
 // LDS tile layout: row r (0..63) of a tile holds its NCH 16-byte chunks at positions
 // chunk ^ swizzle(r).  Only r mod 16 matters, and every swizzle is XOR-linear in the row
@@ -131,14 +97,6 @@ struct SwzFp8 {
     return D == 256 ? (r & 15) : D == 128 ? (((r >> 1) & 1) | (((r >> 3) & 1) << 1)) : ((r >> 3) & 1);
   }
 };
-
-// eight fp8 values (two words) -> eight bf16 values, exactly
-__device__ __forceinline__ uint4 widen_fp8x8(uint32_t lo, uint32_t hi) {
-  return make_uint4(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, 1.0f, false)),
-                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)lo, 1.0f, true)),
-                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, 1.0f, false)),
-                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)hi, 1.0f, true)));
-}
 
 // T: cache storage (uint16_t bf16, uint8_t fp8 E4M3).  fp8 tiles are staged as bytes (half the
 // HBM, DMA and LDS traffic) and widened to bf16 fragments exactly before the MFMAs.

@@ -67,3 +67,53 @@ def test_logit_compare_special_values():
     kl, ia, ib = h.compare_logits(torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda())
     assert np.isnan(kl[[0, 1, 3, 4]]).all() and kl[2] == 0.0 and kl[5] == inf
     assert list(ia) == [0, 1, 6, 8, 1, 0] and list(ib) == [0, 1, 6, 0, 1, 0]
+
+
+# Decode of bf16 and fp8 caches: units of 128 keys, splits of 512, windows that start inside a page
+# and a unit; groups of 1 to 8 heads.  Small calls take a wave per unit.
+DECODE_CASES = [
+    # dtype, D, Hq, Hkv, ctx_lens, steps, windows
+    ("bf16", 256, 2, 1, [126, 127, 128], 3, (0, 0)),
+    ("bf16", 64, 4, 2, [0, 15, 640], 2, (0, 127)),
+    ("bf16", 128, 2, 2, [511, 1151], 3, (0, 513)),
+    ("fp8", 256, 8, 1, [129, 1030], 2, (0, 128)),
+    ("fp8", 128, 4, 1, [255, 31], 2, (0, 17)),
+    ("fp8", 64, 16, 2, [639, 383], 2, (0, 600)),
+]
+
+
+@pytest.mark.parametrize("dtype,D,Hq,Hkv,ctxs,steps,windows", DECODE_CASES)
+def test_decode_units(dtype, D, Hq, Hkv, ctxs, steps, windows):
+    from test_gpu_prefill import _decode_case
+    _decode_case(dtype, D, Hq, Hkv, ctxs, steps, windows)
+
+
+@pytest.mark.parametrize("dtype,D,window", [("bf16", 256, 0), ("bf16", 128, 700), ("fp8", 256, 100), ("fp8", 64, 0)])
+def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window):
+    """A workspace that only holds a partial per split makes the call run a wave per split; the
+    full one lets it run a wave per unit.  Same bytes, for contexts of one unit to many splits."""
+    import torch
+
+    from gpu_helpers import TORCH_DTYPE
+    from paper_2607_14431_amd import kvg
+    L, Hq, Hkv, ctxs = 2, 4, 2, [0, 100, 130, 511, 512, 9000]
+    B, per_seq = len(ctxs), (max(ctxs) + 16) // 16
+    g = torch.Generator(device="cuda").manual_seed(D + window)
+    cache = kvg.Cache.allocate(L, B * per_seq, Hq, Hkv, D, TORCH_DTYPE[dtype], windows=(window, 0))
+    for pool in (cache.k_pool, cache.v_pool):
+        pool.copy_((torch.randn(pool.shape, generator=g, device="cuda") * 0.5).to(pool.dtype))
+    tables = torch.randperm(B * per_seq, generator=g, device="cuda").to(torch.int32).view(B, per_seq)
+    seqs = kvg.Seqs(tables, torch.tensor(ctxs, dtype=torch.int32, device="cuda"),
+                    torch.full((B,), 777, dtype=torch.int64, device="cuda"), max(ctxs))
+    q, k, v = (torch.randn((L, B, 1, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    n_split = max(ctxs) // 512 + 1
+    one = sum(-(-L * B * Hq * n_split * n * 4 // 256) * 256 for n in (2, D))
+    assert kvg.kvg_decode_workspace_bytes(cache, seqs, L) > one
+    outs = []
+    for nbytes in (one, kvg.kvg_decode_workspace_bytes(cache, seqs, L)):
+        out = torch.full((L, B, 1, Hq, D), float("nan"), device="cuda")
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, L, q, k, v, D ** -0.5, out, ws)
+        outs.append(out)
+    assert torch.isfinite(outs[0]).all()
+    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
