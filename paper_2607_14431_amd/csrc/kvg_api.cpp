@@ -257,6 +257,18 @@ DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, size
   return w;
 }
 
+// What the size query returns: enough for a call of this size, and for a wave per unit wherever a
+// call no larger than this one takes it: four partials per split of every row, which only
+// windowed layers (whose rows hold more splits than their windows touch) let exceed the resident
+// waves.
+size_t decode_ws_bytes(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
+  const size_t unit_bytes = (size_t)(c->n_q_heads / c->n_kv_heads) * (c->head_dim + 2) * sizeof(float);
+  const size_t layout = (size_t)n_layers * s->batch * c->n_kv_heads * n_split_max(s, 1) * 4;
+  const size_t most = c->layer_window != nullptr ? 4 * kSoloWaves : kSoloWaves;
+  const size_t units = c->dtype == KVG_F32 ? 0 : std::min(most, layout);
+  return std::max(decode_ws(c, s, n_layers).total, units * unit_bytes + 2 * kAlign);
+}
+
 // One plane of rotated bf16 queries (the workspace holds a hi and a lo plane); with shared
 // pages also two partials per (row, head).
 size_t mfma_q_plane(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t chunk) {
@@ -558,14 +570,7 @@ int kvg_prefill_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rop
 
 size_t kvg_decode_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs, int32_t n_layers) {
   if (check_cache(cache) != KVG_OK || seqs == nullptr || n_layers <= 0 || seqs->batch <= 0) return 0;
-  // Also enough for a wave per unit wherever a call no larger than this one takes it: four partials
-  // per split of every row, which only windowed layers (whose rows hold more splits than
-  // their windows touch) let exceed the resident waves.
-  const size_t unit_bytes = (size_t)(cache->n_q_heads / cache->n_kv_heads) * (cache->head_dim + 2) * sizeof(float);
-  const size_t layout = (size_t)n_layers * seqs->batch * cache->n_kv_heads * n_split_max(seqs, 1) * 4;
-  const size_t most = cache->layer_window != nullptr ? 4 * kSoloWaves : kSoloWaves;
-  const size_t units = cache->dtype == KVG_F32 ? 0 : std::min(most, layout);
-  return std::max(decode_ws(cache, seqs, n_layers).total, units * unit_bytes + 2 * kAlign);
+  return decode_ws_bytes(cache, seqs, n_layers);
 }
 
 int kvg_decode_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope, int32_t layer0,
@@ -588,14 +593,14 @@ int decode_attn_check(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_ro
 }
 
 size_t decode_attn_ws_bytes(const kvg_cache* cache, const kvg_seqs* seqs, int32_t n_layers) {
-  return decode_ws(cache, seqs, n_layers).total;
+  return decode_ws_bytes(cache, seqs, n_layers);
 }
 
 int decode_attn_launch(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope, int32_t layer0,
                        int32_t n_layers, const void* q_raw, const void* k_raw, const void* v_raw, float scale,
                        float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
   const DecodeWs w = decode_ws(cache, seqs, n_layers);
-  if (ws == nullptr || ws_bytes < w.total) return KVG_E_WORKSPACE;
+  if (ws == nullptr || ws_bytes < decode_ws_bytes(cache, seqs, n_layers)) return KVG_E_WORKSPACE;
   const int n_split = n_split_max(seqs, 1);
   const DecodeGrid grid = decode_grid(cache, seqs, layer0, n_layers);
   const int64_t n_blocks = grid.items;
@@ -640,7 +645,8 @@ int decode_attn_launch(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_r
   a.n_split_full = grid.n_split_full;
   a.n_split_win = grid.n_split_win;
   std::memcpy(a.layer_order, grid.order, sizeof(a.layer_order));
-  // the bytes are the same either way, so a workspace that only holds a partial per split is enough
+  // the bytes are the same either way: a workspace whose rows hold too many splits for four
+  // partials each (windowed layers) takes a wave per split
   const DecodeWs wu = decode_ws(cache, seqs, n_layers, 4);
   a.solo = decode_solo(cache, seqs, grid) && ws_bytes >= wu.total;
   if (a.solo) a.part_acc = reinterpret_cast<float*>(base + wu.ml);

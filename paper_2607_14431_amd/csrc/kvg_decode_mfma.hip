@@ -13,13 +13,14 @@
 // small beside that: a 16-key tile's scores for up to 8 query heads are D / 32
 // v_mfma_f32_16x16x32_bf16 (A = 16 keys, B = the heads' queries: bf16 high parts in columns 0-7, low
 // parts in columns 8-15, the two halves added by one row rotation), the weights leave the
-// accumulator in the order the next operand needs, and O^T += V^T P^T takes one MFMA per 16
-// dimensions with V read transposed from LDS (ds_read_b64_tr).  On the vector ALUs (16-lane teams,
+// accumulator in the order the next operand needs (high parts in columns 0-7, remainders in columns
+// 8-15, so a weight keeps 16 significant bits at no cost), and O^T += V^T P^T takes one MFMA per
+// 16 dimensions with V read transposed from LDS (ds_read_b64_tr).  On the vector ALUs (16-lane teams,
 // one dot product per key and head) a pair of keys took ~200 instructions in a row, which bound
 // every launch that left CUs idle.
 //
 // kSolo: a wave per unit instead of per split, with more stages in flight, for launches that
-// leave CUs idle; the four units of a split leave four partials, which solo_merge_kernel merges with
+// leave CUs idle; the four units of a split leave four partials, which merge_splits_kernel merges with
 // the same operations in the same order, so the bytes are the same.
 #include "kvg_launch.h"
 #include "kvg_mfma.h"
@@ -325,6 +326,11 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   const uint32_t v_lane = kFp8 ? SK * RB + kk * RB + 16 * SW::v(kk) + 8 * (col & 1)
                                : SK * RB + kk * RB + 16 * (((col & 3) >> 1) ^ SW::v(kk)) + 8 * (col & 1);
 
+  const bool is_lo = col >= 8;
+  // O of the unit: the sums over the weights' high parts and over their remainders
+  auto unit_o = [&](int d) -> f32x4 {
+    return (f32x4){add_ror8(o[d][0]), add_ror8(o[d][1]), add_ror8(o[d][2]), add_ror8(o[d][3])};
+  };
   auto stage = [&](auto st, int i) {
     // stage i has landed: the loads of the kStages - 1 later ones may be in flight
     __builtin_amdgcn_s_waitcnt(vm_wait((kStages - 1) * kLoads));
@@ -381,7 +387,6 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
       for (int t = 0; t < NTL; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[t][e]);
-      // the reference is raised to every new maximum: the heaviest weight is then 1 exactly
       const float mx2 = max_over_groups(mx) * a.scale_log2;
       const bool raised = mx2 > m;
       if (__builtin_amdgcn_ballot_w64(raised) != 0) {
@@ -392,17 +397,19 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
         for (int d = 0; d < ND; ++d) o[d] *= alpha;
       }
       const float m_ref = m == -INFINITY ? 0.0f : m;          // no key seen yet: every p is 0
-      uint32_t pw[2 * NTL];                                   // weights as bf16 pairs
-      const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+      // weights as bf16 pairs: their high parts in columns 0-7, the remainders in columns 8-15
+      uint32_t pw[2 * NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t)
 #pragma unroll
         for (int e = 0; e < 4; e += 2) {
           const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[t][e], a.scale_log2, -m_ref));
           const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[t][e + 1], a.scale_log2, -m_ref));
-          const bf16x2 pp = __builtin_convertvector((f32x2){p0, p1}, bf16x2);
-          lsum = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, lsum, false);   // the rounded weights
-          pw[2 * t + e / 2] = __builtin_bit_cast(uint32_t, pp);
+          lsum += p0;
+          lsum += p1;
+          const bf16x2 h = __builtin_convertvector((f32x2){p0, p1}, bf16x2);
+          const uint32_t lw = pack_bf16_rne(p0 - (float)h.x, p1 - (float)h.y);
+          pw[2 * t + e / 2] = is_lo ? lw : __builtin_bit_cast(uint32_t, h);
         }
 #pragma unroll
       for (int d = 0; d < ND; ++d) {
@@ -437,7 +444,7 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
           m_run = m;
           l_run = lu;
 #pragma unroll
-          for (int d = 0; d < ND; ++d) o_run[d] = o[d];
+          for (int d = 0; d < ND; ++d) o_run[d] = unit_o(d);
         } else {
           const float m_new = fmaxf(m_run, m);
           const float f_me = merge_factor(m_run, m_new);
@@ -445,9 +452,11 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
           l_run = fmaf(l_run, f_me, lu * f_o);
           m_run = m_new;
 #pragma unroll
-          for (int d = 0; d < ND; ++d)
+          for (int d = 0; d < ND; ++d) {
+            const f32x4 ou = unit_o(d);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o_run[d][e] = fmaf(o_run[d][e], f_me, o[d][e] * f_o);
+            for (int e = 0; e < 4; ++e) o_run[d][e] = fmaf(o_run[d][e], f_me, ou[e] * f_o);
+          }
         }
         m = -INFINITY;
         lsum = 0.0f;
@@ -469,6 +478,8 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   // ---- the wave's partial, or the output itself when the row has one split
   if constexpr (kSolo) {
     const float lu = sum_over_groups(lsum);
+#pragma unroll
+    for (int d = 0; d < ND; ++d) o[d] = unit_o(d);
     if (col < G && n_keys - base <= kUnit) {         // the row's only unit
       float* op = a.out + (head0 + col) * D + 4 * grp;
 #pragma unroll

@@ -353,8 +353,12 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
   int32_t pg_next = page_of_tile(kt_begin);
   issue(tile_rsrc(kpool, kt_begin, pg_next), tile_rsrc(vpool, kt_begin, pg_next), Stage0{}, 0, kTileLoads);
   pg_next = page_of_tile(kt_begin + 1);
-  auto tile = [&](auto stage, int kt) {
+  // exact (kTight, the tile of keys 0-63): the weights keep a bf16 remainder too.  A row of a few
+  // keys has no other rounding, and on the vector path, one team per key, its weights were exact:
+  // 3 rows over nothing were 1.4e-6 off the 64-bit result, 3.8e-4 with weights rounded once.
+  auto tile = [&](auto stage, int kt, auto exact) {
     constexpr int ST = decltype(stage)::value;
+    constexpr bool kExact = decltype(exact)::value;
     using Next = std::integral_constant<int, 1 - ST>;
     // vmcnt(0): this wave's share of tile kt (and the next page id) has arrived
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -453,7 +457,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     // weights there measured 0.5% slower on the 31B-class suffix).
     // Branch-free: exp2(-inf - finite) = 0 for a first raise, and the value of an unraised
     // lane (possibly NaN) is discarded by the select.
-    uint4 pf[4];
+    uint4 pf[4], pl[kExact ? 4 : 1];
     struct SoftState {
       float mx, alpha, m_ref, psum;
       bool raised;
@@ -478,7 +482,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
         for (int r = 2 * (j - 5); r < 2 * (j - 5) + 2; ++r) {
           const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], a.scale_log2, -st.m_ref));
           s[kb][r] = p;
-          if constexpr (!kTight) st.psum += p;
+          if constexpr (!kTight || kExact) st.psum += p;
         }
       } else if (j == 13) {
         if constexpr (!kTight) {
@@ -492,11 +496,20 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
         f.y = pack_bf16_rne(s[kb][8 * hs + 2], s[kb][8 * hs + 3]);
         f.z = pack_bf16_rne(s[kb][8 * hs + 4], s[kb][8 * hs + 5]);
         f.w = pack_bf16_rne(s[kb][8 * hs + 6], s[kb][8 * hs + 7]);
+        if constexpr (kExact) {
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const bf16x2 h = __builtin_bit_cast(bf16x2, (&f.x)[w]);
+            (&pl[2 * kb + hs].x)[w] = pack_bf16_rne(s[kb][8 * hs + 2 * w] - (float)h.x, s[kb][8 * hs + 2 * w + 1] - (float)h.y);
+          }
+        }
         if constexpr (kTight) {
           const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+          if constexpr (!kExact) {
 #pragma unroll
-          for (int w = 0; w < 4; ++w)
-            st.psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (&f.x)[w]), ones, st.psum, false);
+            for (int w = 0; w < 4; ++w)
+              st.psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (&f.x)[w]), ones, st.psum, false);
+          }
           if (hs == 1) {
             const float2 ph = halves32(st.psum);
             l_run = l_run * st.alpha + (ph.x + ph.y);
@@ -572,6 +585,8 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
       vfetch(t + LV);
       const int d = t % ND;
       o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pf[t / ND]), o[d], 0, 0, 0);
+      if constexpr (kExact)
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pl[t / ND]), o[d], 0, 0, 0);
 #pragma unroll
       for (int j = t * kSoftPieces / (2 * ND); j < (t + 1) * kSoftPieces / (2 * ND); ++j) soft_piece(1, j, st1);
       __builtin_amdgcn_sched_barrier(0);
@@ -583,12 +598,23 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
       __builtin_amdgcn_sched_barrier(0);
       const int d = t % ND;
       o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pf[t / ND]), o[d], 0, 0, 0);
+      if constexpr (kExact)
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pl[t / ND]), o[d], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  if constexpr (kTight) {
+    if (kt_begin == 0) {
+      tile(Stage0{}, 0, std::true_type{});
+    } else {
+      tile(Stage0{}, kt_begin, std::false_type{});
+    }
+    if (kt_begin + 1 < n_tiles) tile(Stage1{}, kt_begin + 1, std::false_type{});
+    kt_begin += 2;
+  }
   for (int kt = kt_begin; kt < n_tiles; kt += 2) {
-    tile(Stage0{}, kt);
-    if (kt + 1 < n_tiles) tile(Stage1{}, kt + 1);
+    tile(Stage0{}, kt, std::false_type{});
+    if (kt + 1 < n_tiles) tile(Stage1{}, kt + 1, std::false_type{});
   }
 
   // ---- shared split: the partial (reference, sum, unnormalised O) of this lane's row in the

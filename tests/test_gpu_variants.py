@@ -90,8 +90,8 @@ def test_decode_units(dtype, D, Hq, Hkv, ctxs, steps, windows):
 
 @pytest.mark.parametrize("dtype,D,window", [("bf16", 256, 0), ("bf16", 128, 700), ("fp8", 256, 100), ("fp8", 64, 0)])
 def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window):
-    """A workspace that only holds a partial per split makes the call run a wave per split; the
-    full one lets it run a wave per unit.  Same bytes, for contexts of one unit to many splits."""
+    """Six sequences together take a wave per split, each alone a wave per 128-key unit.  Same
+    bytes, for contexts of one unit to many splits."""
     import torch
 
     from gpu_helpers import TORCH_DTYPE
@@ -103,17 +103,18 @@ def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window):
     for pool in (cache.k_pool, cache.v_pool):
         pool.copy_((torch.randn(pool.shape, generator=g, device="cuda") * 0.5).to(pool.dtype))
     tables = torch.randperm(B * per_seq, generator=g, device="cuda").to(torch.int32).view(B, per_seq)
-    seqs = kvg.Seqs(tables, torch.tensor(ctxs, dtype=torch.int32, device="cuda"),
-                    torch.full((B,), 777, dtype=torch.int64, device="cuda"), max(ctxs))
-    q, k, v = (torch.randn((L, B, 1, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
-    n_split = max(ctxs) // 512 + 1
-    one = sum(-(-L * B * Hq * n_split * n * 4 // 256) * 256 for n in (2, D))
-    assert kvg.kvg_decode_workspace_bytes(cache, seqs, L) > one
-    outs = []
-    for nbytes in (one, kvg.kvg_decode_workspace_bytes(cache, seqs, L)):
-        out = torch.full((L, B, 1, Hq, D), float("nan"), device="cuda")
-        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-        kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, L, q, k, v, D ** -0.5, out, ws)
-        outs.append(out)
-    assert torch.isfinite(outs[0]).all()
-    assert torch.equal(outs[0].view(torch.int32), outs[1].view(torch.int32))
+    lens = torch.tensor(ctxs, dtype=torch.int32, device="cuda")
+    start = torch.full((B,), 777, dtype=torch.int64, device="cuda")
+    raw = [torch.randn((L, B, 1, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv)]
+
+    def decode(rows):
+        seqs = kvg.Seqs(tables[rows].contiguous(), lens[rows].contiguous(), start[rows].contiguous(), max(ctxs))
+        out = torch.full((L, len(rows), 1, Hq, D), float("nan"), device="cuda")
+        ws = kvg.decode_workspace(cache, seqs, L)
+        kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, L, *(t[:, rows].contiguous() for t in raw), D ** -0.5, out, ws)
+        return out
+
+    together = decode(list(range(B)))
+    assert torch.isfinite(together).all()
+    for b in range(B):
+        assert torch.equal(together[:, b:b + 1].view(torch.int32), decode([b]).view(torch.int32)), f"context {ctxs[b]}"
