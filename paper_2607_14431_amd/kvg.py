@@ -119,18 +119,24 @@ def _check(status: int, where: str):
         raise KvgError(status, where)
 
 
+# Addresses go to the library as plain ints (its argument types convert them): a decode step's
+# marshalling is a large part of a small call's time.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        # the current stream's handle, without the Stream object that torch.cuda.current_stream() makes
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def rope(base: float = 10000.0, pairing: int = KVG_ROPE_HALF) -> kvg_rope:
     return kvg_rope(base, pairing, 0)
+
+
+_DTYPE_CODE = {torch.float32: KVG_F32, torch.bfloat16: KVG_BF16, torch.float8_e4m3fn: KVG_FP8_E4M3}
 
 
 @dataclasses.dataclass
@@ -173,19 +179,22 @@ class Cache:
 
     @property
     def kvg_dtype(self):
-        return {torch.float32: KVG_F32, torch.bfloat16: KVG_BF16,
-                torch.float8_e4m3fn: KVG_FP8_E4M3}[self.k_pool.dtype]
+        return _DTYPE_CODE[self.k_pool.dtype]
 
     @property
     def raw_dtype(self) -> torch.dtype:
         """dtype of the raw q/k/v this cache takes (bf16 for an fp8 cache)."""
-        return torch.bfloat16 if self.k_pool.dtype == torch.float8_e4m3fn else self.k_pool.dtype
+        dtype = self.k_pool.dtype
+        return torch.bfloat16 if dtype is torch.float8_e4m3fn else dtype
 
     def struct(self) -> kvg_cache:
-        assert self.k_pool.is_contiguous() and self.v_pool.is_contiguous()
-        assert self.k_pool.shape == self.v_pool.shape and self.k_pool.dtype == self.v_pool.dtype
-        c = kvg_cache(self.n_layers, self.n_q_heads, self.n_kv_heads, self.head_dim, self.page_size,
-                      self.kvg_dtype, self.n_pages, self.k_pool.data_ptr(), self.v_pool.data_ptr(), None)
+        k, v = self.k_pool, self.v_pool
+        shape, dtype = k.shape, k.dtype
+        assert k.is_contiguous() and v.is_contiguous()
+        assert shape == v.shape and dtype == v.dtype
+        n_layers, n_pages, n_kv_heads, page_size, head_dim = shape
+        c = kvg_cache(n_layers, self.n_q_heads, n_kv_heads, head_dim, page_size, _DTYPE_CODE[dtype], n_pages,
+                      k.data_ptr(), v.data_ptr(), None)
         if self.windows is not None and any(self.windows):
             arr = (ctypes.c_int32 * len(self.windows))(*self.windows)
             c.layer_window = ctypes.cast(arr, ctypes.POINTER(ctypes.c_int32))
@@ -204,11 +213,12 @@ class Seqs:
     shared_tokens: int = 0      # leading tokens every sequence's table shares (see kvg_seqs in kvg.h)
 
     def struct(self) -> kvg_seqs:
-        bt = self.block_tables
-        assert bt.dtype == torch.int32 and bt.is_contiguous() and bt.dim() == 2
-        assert self.ctx_lens.dtype == torch.int32 and self.start_pos.dtype == torch.int64
-        return kvg_seqs(bt.shape[0], bt.shape[1], self.max_ctx_len, self.shared_tokens, bt.data_ptr(),
-                        self.ctx_lens.data_ptr(), self.start_pos.data_ptr())
+        bt, ctx, pos = self.block_tables, self.ctx_lens, self.start_pos
+        shape = bt.shape
+        assert bt.dtype is torch.int32 and bt.is_contiguous() and len(shape) == 2
+        assert ctx.dtype is torch.int32 and pos.dtype is torch.int64
+        return kvg_seqs(shape[0], shape[1], self.max_ctx_len, self.shared_tokens, bt.data_ptr(), ctx.data_ptr(),
+                        pos.data_ptr())
 
 
 def kvg_payload_bytes(cache: Cache, n_tokens: int) -> int:
@@ -229,7 +239,7 @@ def kvg_artifact_digest_workspace_bytes(hdr: kvg_artifact_hdr) -> int:
 def _payload_ptr(payload):
     """Device address of a payload: a torch tensor, or an object with data_ptr() (pinned host
     memory exposed through its device address)."""
-    return ctypes.c_void_p(payload.data_ptr())
+    return payload.data_ptr()
 
 
 def kvg_artifact_seal(hdr: kvg_artifact_hdr, payload, ws: torch.Tensor, stream=None):
@@ -246,8 +256,9 @@ def kvg_artifact_verify(hdr: kvg_artifact_hdr, payload, ws: torch.Tensor, stream
 
 
 def _raw_ok(cache: Cache, *raws):
+    dtype = cache.raw_dtype
     for t in raws:
-        assert t.dtype == cache.raw_dtype and t.is_contiguous(), "raw inputs: the cache's raw dtype, contiguous"
+        assert t.dtype is dtype and t.is_contiguous(), "raw inputs: the cache's raw dtype, contiguous"
 
 
 def kvg_append(cache: Cache, seqs: Seqs, rp: kvg_rope, layer0: int, n_layers: int, chunk_len: int,
