@@ -263,7 +263,7 @@ size_t kvg_prefill_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs,
  * bf16 and fp8 caches use bf16 MFMA for Q K^T and P V (each rotated query carried as a bf16
  * high part and a bf16 low part, both multiplied with every key, so a score is as accurate as
  * with the fp32 query; P rounded to bf16; fp8 rows widened to bf16 exactly); fp32 caches use
- * fp32 vector arithmetic.
+ * fp32 matrix arithmetic.
  * q_raw_dev: [n_layers][batch][chunk_len][n_q_heads][head_dim] of the raw dtype (the cache
  * dtype, bf16 for an fp8 cache), pre-rotation;
  * k_raw_dev, v_raw_dev as kvg_append; out_dev: [n_layers][batch][chunk_len][n_q_heads]

@@ -21,7 +21,7 @@ BUILD = os.path.join(ROOT, "_build")
 
 KVG_SOURCES = ["kvg_api.cpp", "kvg_api_digest.cpp", "kvg_api_logits.cpp", "kvg_api_noalloc.cpp", "kvg_append.hip",
                "kvg_copy.hip",
-               "kvg_attn_valu.hip", "kvg_decode_mfma.hip", "kvg_prefill_mfma.hip", "kvg_digest.hip", "kvg_logits.hip"]
+               "kvg_attn_valu.hip", "kvg_decode_mfma.hip", "kvg_prefill_mfma.hip", "kvg_prefill_f32.hip", "kvg_digest.hip", "kvg_logits.hip"]
 ARCH = "gfx950"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed fp32 VALU instructions are disabled for all device code.
@@ -29,7 +29,7 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-unused-function"]
 # Per-source extras.  The MFMA prefill keeps its accumulators in VGPRs: left to choose, the
 # register allocator splits them between AGPRs and VGPRs and copies them every key tile.
-EXTRA = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("kvg_prefill_mfma.hip", "kvg_decode_mfma.hip")}
+EXTRA = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("kvg_prefill_mfma.hip", "kvg_prefill_f32.hip", "kvg_decode_mfma.hip")}
 
 
 def _run(cmd):

@@ -79,15 +79,26 @@ int n_split_max(const kvg_seqs* s, int32_t chunk) {
   return (int)(((int64_t)s->max_ctx_len + chunk + kSplit - 1) / kSplit);
 }
 
-// Workspace of the vector-ALU attention path (fp32 caches): rotated queries, split partials.
-struct ValuWs {
+// An fp32 prefill of so few workgroups takes one per 128 keys of a split instead (the same bytes), when it
+// has more than 128: a workgroup then runs a block of 32 keys per wave instead of four in a row.
+// One row over 512 keys: 24.4 -> 17.5 us at head_dim 64, 2 KV heads; 58 -> 29 at 256, 8 KV heads.  At 136
+// workgroups the four rounds cost more than that (4 x 4 rows over 8k keys, head_dim 64: 29 -> 37).
+constexpr int64_t kF32SoloWorkgroups = 128;
+
+// Workspace of an fp32 cache's prefill: rotated queries, split partials.
+struct F32Ws {
   size_t q, acc, ml, total;
+  bool solo, parts;
 };
 
-ValuWs valu_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows) {
-  ValuWs w;
+F32Ws f32_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows) {
+  F32Ws w;
   const size_t nrow_heads = (size_t)n_layers * s->batch * rows * c->n_q_heads;
-  const size_t ns = (size_t)n_split_max(s, rows);
+  const int64_t n_wg = (int64_t)n_layers * s->batch * c->n_kv_heads * n_split_max(s, rows) *
+                       (((int64_t)rows * (c->n_q_heads / c->n_kv_heads) + 31) / 32);
+  w.solo = n_wg <= kF32SoloWorkgroups && (int64_t)s->max_ctx_len + rows > kSplit / kvg::kF32Units;
+  w.parts = w.solo || n_split_max(s, rows) > 1;
+  const size_t ns = w.parts ? (size_t)n_split_max(s, rows) * (w.solo ? kvg::kF32Units : 1) : 0;
   w.q = align_up(nrow_heads * c->head_dim * sizeof(float));
   w.acc = align_up(nrow_heads * ns * c->head_dim * sizeof(float));
   w.ml = align_up(nrow_heads * ns * 2 * sizeof(float));
@@ -154,27 +165,13 @@ int check_raw(const void* k_raw, const void* v_raw) {
   return (k_raw == nullptr || v_raw == nullptr) ? KVG_E_INVAL : KVG_OK;
 }
 
-// Prefill of an fp32 cache: append, rotate queries, partials, merge.
-int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t layer0, int32_t n_layers,
-              int32_t rows, const void* q_raw, const void* k_raw, const void* v_raw, float scale,
-              float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
-  const ValuWs w = valu_ws(c, s, n_layers, rows);
+// Prefill of an fp32 cache: append (queries rotated into the workspace), attention, combine of the splits.
+int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t layer0, int32_t n_layers,
+             int32_t rows, const void* q_raw, const void* k_raw, const void* v_raw, float scale,
+             float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
+  const F32Ws w = f32_ws(c, s, n_layers, rows);
   if (ws == nullptr || ws_bytes < w.total) return KVG_E_WORKSPACE;
-  const int64_t n_blocks = (int64_t)n_layers * s->batch * rows * c->n_kv_heads * n_split_max(s, rows);
-  const int64_t n_rows = (int64_t)n_layers * s->batch * rows * c->n_q_heads;
-  if (!fits_grid(n_blocks, 256) || !fits_grid(n_rows, 256) || !append_fits(s, rows)) return KVG_E_SHAPE;
-  char* base = static_cast<char*>(ws);
-  float* q = reinterpret_cast<float*>(base);
-  float* acc = reinterpret_cast<float*>(base + w.q);
-  float* ml = reinterpret_cast<float*>(base + w.q + w.acc);
-
-  kvg::AppendArgs ap = append_args(c, s, r, layer0, n_layers, rows, k_raw, v_raw);
-  ap.q_raw = q_raw;
-  ap.q_out = q;
-  int st = hip_status(kvg::launch_append(ap, c->dtype, stream));
-  if (st != KVG_OK) return st;
-
-  kvg::AttnArgs a;
+  kvg::PrefillArgs a;
   std::memset(&a, 0, sizeof(a));
   a.k_pool = c->k_pool;
   a.v_pool = c->v_pool;
@@ -182,9 +179,7 @@ int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   a.n_pages = c->n_pages;
   a.block_tables = s->block_tables;
   a.ctx_lens = s->ctx_lens;
-  a.q = q;
-  a.part_acc = acc;
-  a.part_ml = ml;
+  a.q = ws;
   a.out = out;
   a.scale_log2 = scale * 1.4426950408889634f;
   a.Hq = c->n_q_heads;
@@ -194,18 +189,28 @@ int attn_valu(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t 
   a.layer0 = layer0;
   a.n_layers = n_layers;
   a.batch = s->batch;
-  a.rows = rows;
+  a.chunk = rows;
   a.max_pages = s->max_pages;
   a.max_ctx_len = s->max_ctx_len;
+  a.n_qt = (int)(((int64_t)rows * a.group + 31) / 32);
   a.n_split_max = n_split_max(s, rows);
   fill_windows(c, layer0, n_layers, a.window);
-  return hip_status(kvg::launch_attn_valu(a, stream));
+  if (w.parts) {
+    a.part_acc = reinterpret_cast<float*>(static_cast<char*>(ws) + w.q);
+    a.part_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + w.q + w.acc);
+  }
+  if (!fits_grid(kvg::prefill_f32_workgroups(a), 256) || !append_fits(s, rows)) return KVG_E_SHAPE;
+  kvg::AppendArgs ap = append_args(c, s, r, layer0, n_layers, rows, k_raw, v_raw);
+  ap.q_raw = q_raw;
+  ap.q_out = ws;
+  const int st = hip_status(kvg::launch_append(ap, c->dtype, stream));
+  return st == KVG_OK ? hip_status(kvg::launch_prefill_f32(a, w.solo, stream)) : st;
 }
 
 // Workspace of the decode kernels: the split partials.
-// bf16 and fp8 caches prefill on MFMA, fp32 caches on the VALU path.  8 query heads per KV
-// head (31B-like heads, 2 layers x 3 x 300 rows over 1.6k keys): 1,153 us on the VALU path,
-// which reads every key again for every row, 115 us on MFMA.
+// bf16 and fp8 caches take the bf16 matrix cores.  8 query heads per KV head (2 layers x 3 x 300 rows
+// over 1.6k keys) took 1,153 us on the vector ALUs, which read every key again for every row,
+// 114 us on MFMA.
 bool use_mfma(const kvg_cache* c) { return c->dtype == KVG_BF16 || c->dtype == KVG_FP8_E4M3; }
 
 // Decode splits served by the shared-split kernel: the whole 512-key splits inside the
@@ -566,7 +571,7 @@ size_t kvg_prefill_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs,
   if (check_cache(cache) != KVG_OK || seqs == nullptr || n_layers <= 0 || chunk_len <= 0 || seqs->batch <= 0)
     return 0;
   if (use_mfma(cache)) return mfma_ws(cache, seqs, n_layers, chunk_len);
-  return valu_ws(cache, seqs, n_layers, chunk_len).total;
+  return f32_ws(cache, seqs, n_layers, chunk_len).total;
 }
 
 int kvg_prefill_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope, int32_t layer0,
@@ -577,7 +582,7 @@ int kvg_prefill_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rop
   if (use_mfma(cache))
     return attn_mfma(cache, seqs, rope, layer0, n_layers, chunk_len, q_raw, k_raw, v_raw, scale, out, ws,
                      ws_bytes, static_cast<hipStream_t>(stream));
-  return attn_valu(cache, seqs, rope, layer0, n_layers, chunk_len, q_raw, k_raw, v_raw, scale, out, ws,
+  return attn_f32(cache, seqs, rope, layer0, n_layers, chunk_len, q_raw, k_raw, v_raw, scale, out, ws,
                    ws_bytes, static_cast<hipStream_t>(stream));
 }
 

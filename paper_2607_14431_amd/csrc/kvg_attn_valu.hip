@@ -1,6 +1,5 @@
-// Grouped-query attention of fp32 caches on the vector ALUs, split over keys ("split-K"): the fused
-// decode kernel (one new token per sequence) and the prefill rows; and the kernels that combine
-// the split partials of every cache type.
+// Grouped-query decode attention of fp32 caches on the vector ALUs (one new token per sequence), split
+// over keys ("split-K"); and the kernels that combine the split partials of every cache type.
 //
 // Work item = (layer, sequence, row, KV head g, split s).  A split is a fixed logical key range of
 // the row's visible keys; the split plan is a function of the row's own length and window only.
@@ -341,99 +340,6 @@ __device__ __forceinline__ float combine_splits(const float* ml, const float* ac
 }
 
 // ------------------------------------------------------------------------------------
-// Multi-row calls (fp32 prefill): queries pre-rotated by the append kernel; each work item
-// writes its split partial, combined by attn_merge_kernel.
-template <int D, int G>
-__global__ __launch_bounds__(kThreads) void attn_partial_kernel(const AttnArgs a) {
-  using W = SplitWorker<D, G>;
-  int64_t w = blockIdx.x;
-  const int s = (int)(w % a.n_split_max);  w /= a.n_split_max;
-  const int g = (int)(w % a.Hkv);          w /= a.Hkv;
-  const int r = (int)(w % a.rows);         w /= a.rows;
-  const int b = (int)(w % a.batch);        w /= a.batch;
-  const int l = (int)w;
-
-  const int ctx = a.ctx_lens[b];
-  if (ctx < 0 || ctx > a.max_ctx_len) return;
-  const int n_keys = ctx + r + 1;                 // keys [0, ctx + r] are visible
-  const int lo = window_start(layer_window(a, l), n_keys);
-  if (s >= split_count(n_keys, lo)) return;
-  const int k0 = lo + s * kSplit;                 // the split's keys [k0, k1)
-  const int k1 = min(k0 + kSplit, n_keys);
-  const int kb = k0 & ~(kPage - 1);               // teams start at the page holding k0
-
-  W wk;
-  wk.init();
-  const int64_t row_id = ((int64_t)l * a.batch + b) * a.rows + r;
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const float* qp = a.q + (row_id * a.Hq + (int64_t)g * G + h) * D;
-#pragma unroll
-    for (int j = 0; j < W::CPL; ++j) {
-      const uint4 v = ld16(qp + wk.q_chunk(j) * 4);
-      wk.set_q(h, j, v);
-    }
-  }
-
-  const int64_t lbase = (int64_t)(a.layer0 + l) * a.layer_elems;
-  const float* kpool = reinterpret_cast<const float*>(a.k_pool) + lbase;
-  const float* vpool = reinterpret_cast<const float*>(a.v_pool) + lbase;
-  const int32_t* bt = a.block_tables + (int64_t)b * a.max_pages;
-  SplitPages sp;
-  sp.init(bt, kb / kPage, a.max_pages, wk.lane);
-  wk.run(kb, k1, a.scale_log2, [&](int j, typename W::Row& rw) {
-    const int32_t page = sp.page_of(j);
-    const bool valid = page >= 0 && page < a.n_pages;
-    rw.ok = valid && j >= k0;
-    rw.lds = false;
-    const int64_t roff = (((int64_t)(valid ? page : 0) * a.Hkv + g) * kPage + (j % kPage)) * D;
-#pragma unroll
-    for (int i = 0; i < W::CPL; ++i) rw.k[i] = ld16_stream(kpool + roff + (wk.tl + W::TL * i) * W::CH);
-#pragma unroll
-    for (int i = 0; i < W::CPL; ++i) rw.v[i] = ld16_stream(vpool + roff + (wk.tl + W::TL * i) * W::CH);
-  }, [] {});
-
-  __shared__ float s_acc[4][G][D];
-  __shared__ float s_ml[4][G][2];
-  wk.to_lds(s_acc, s_ml);
-  __syncthreads();
-
-  const int64_t part_base = (row_id * a.Hq + (int64_t)g * G) * a.n_split_max + s;  // head 0 of group
-  for (int t = threadIdx.x; t < G * D; t += kThreads) {
-    const int h = t / D;
-    const int d = t - h * D;
-    float m, lsum, o;
-    wave_merge<G, D>(s_acc, s_ml, h, d, m, lsum, o);
-    const int64_t pidx = part_base + (int64_t)h * a.n_split_max;
-    a.part_acc[pidx * D + d] = o;
-    if (d == 0) {
-      a.part_ml[pidx * 2] = m;
-      a.part_ml[pidx * 2 + 1] = lsum;
-    }
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void attn_merge_kernel(const AttnArgs a) {
-  int64_t w = blockIdx.x;                       // (layer, batch, row, q head)
-  w /= a.Hq;
-  const int r = (int)(w % a.rows); w /= a.rows;
-  const int b = (int)(w % a.batch); w /= a.batch;
-  const int l = (int)w;
-  const int64_t row_head = blockIdx.x;
-  float* out = a.out + row_head * a.D;
-  const int ctx = a.ctx_lens[b];
-  if (ctx < 0 || ctx > a.max_ctx_len) {
-    for (int d = threadIdx.x; d < a.D; d += kThreads) out[d] = __int_as_float(0x7FC00000);
-    return;
-  }
-  const int n_keys = ctx + r + 1;
-  const int n_split = split_count(n_keys, window_start(layer_window(a, l), n_keys));
-  const float* ml = a.part_ml + row_head * a.n_split_max * 2;
-  const float* acc = a.part_acc + row_head * a.n_split_max * a.D;
-  for (int d = threadIdx.x; d < a.D; d += kThreads) out[d] = combine_splits(ml, acc + d, a.D, n_split);
-}
-
-// ------------------------------------------------------------------------------------
 // Decode: the split kernel rotates its queries from the raw input (angles in fp64 once per
 // workgroup) and the last split's workgroup appends the new token's K/V for its KV head
 // (written to the cache and kept in LDS for its own use).  A context that fits one split
@@ -658,19 +564,6 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
     a.out[row_head * a.D + d] = combine_splits(ml, acc + d, a.D, n_split);
 }
 
-template <int D>
-hipError_t launch_partial_g(const AttnArgs& a, hipStream_t stream) {
-  const int64_t n_blocks = (int64_t)a.n_layers * a.batch * a.rows * a.Hkv * a.n_split_max;
-  switch (a.group) {
-    case 1: attn_partial_kernel<D, 1><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 2: attn_partial_kernel<D, 2><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 4: attn_partial_kernel<D, 4><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    case 8: attn_partial_kernel<D, 8><<<dim3((unsigned)n_blocks), kThreads, 0, stream>>>(a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 // Combine of rows with many splits, or (kSolo, DecodeArgs.solo) with four partials per split: the
 // units of a split merged in order, then the splits in ascending order, combine_splits' own
 // arithmetic.  A workgroup per (layer, sequence, query head): the splits' (reference, sum) pairs
@@ -822,7 +715,7 @@ __global__ __launch_bounds__(kThreads) void prefill_combine_kernel(const Prefill
   }
 }
 
-// Prefill with 8 query heads per KV head: each row's partials over the kSplit-key segments (absolute
+// Prefill of fp32 caches, and with 8 query heads per KV head: each row's partials over the kSplit-key segments (absolute
 // multiples) that hold its visible keys, combined in ascending order.  One element per lane.
 __global__ __launch_bounds__(kThreads) void prefill_segments_kernel(const PrefillArgs a, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
@@ -845,20 +738,6 @@ hipError_t launch_prefill_segments(const PrefillArgs& a, hipStream_t stream) {
   const int64_t n = (int64_t)a.n_layers * a.batch * a.chunk * a.Hq * a.D;
   const unsigned n_wg = (unsigned)std::min<int64_t>((n + kThreads - 1) / kThreads, int64_t(1) << 22);
   prefill_segments_kernel<<<dim3(n_wg), kThreads, 0, stream>>>(a, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_attn_valu(const AttnArgs& a, hipStream_t stream) {
-  hipError_t e;
-  switch (a.D) {
-    case 64: e = launch_partial_g<64>(a, stream); break;
-    case 128: e = launch_partial_g<128>(a, stream); break;
-    case 256: e = launch_partial_g<256>(a, stream); break;
-    default: return hipErrorInvalidValue;
-  }
-  if (e != hipSuccess) return e;
-  const int64_t n_rows = (int64_t)a.n_layers * a.batch * a.rows * a.Hq;
-  attn_merge_kernel<<<dim3((unsigned)n_rows), kThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 

@@ -160,23 +160,6 @@ struct CopyArgs {
   float cs[2 * kMaxHalfDim];  // (cos, sin) of d * theta_i, fp64 on the host, rounded to fp32
 };
 
-struct AttnArgs {
-  const void* k_pool;
-  const void* v_pool;
-  int64_t layer_elems;
-  int64_t n_pages;
-  const int32_t* block_tables;
-  const int32_t* ctx_lens;
-  const float* q;             // rotated queries [n_layers][batch][rows][Hq][D]
-  float* part_acc;            // [n_layers][batch][rows][Hq][n_split_max][D]
-  float* part_ml;             // [n_layers][batch][rows][Hq][n_split_max][2]
-  float* out;                 // [n_layers][batch][rows][Hq][D]
-  float scale_log2;           // scale * log2(e)
-  int32_t Hq, Hkv, D, group;
-  int32_t layer0, n_layers, batch, rows, max_pages, max_ctx_len, n_split_max;
-  int32_t window[kMaxWindowLayers];   // per layer of the launch: 0 = full causal, W = last W keys
-};
-
 struct DecodeArgs {
   void* k_pool;
   void* v_pool;
@@ -235,7 +218,7 @@ struct PrefillArgs {
   int64_t n_pages;
   const int32_t* block_tables;
   const int32_t* ctx_lens;
-  const uint16_t* q;          // rotated queries, bf16 hi parts [n_layers][batch][chunk][Hq][D]
+  const void* q;              // rotated queries, bf16 hi parts [n_layers][batch][chunk][Hq][D] (fp32 caches: fp32)
   const uint16_t* q_lo;       // their bf16 lo parts, same layout
   float* out;                 // [n_layers][batch][chunk][Hq][D]
   // attention over pages every sequence shares: partials (reference, sum, unnormalised O)

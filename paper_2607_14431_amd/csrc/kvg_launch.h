@@ -15,8 +15,14 @@ hipError_t launch_graft(const CopyArgs& a, int dtype, hipStream_t stream);
 // workgroups (256 threads each) of the deposit's and of the graft's launch (own position or
 // relocated), for the host's launch-size checks
 int64_t copy_workgroups(const CopyArgs& a, int dtype);
-// the prefill of an fp32 cache on the vector ALUs
-hipError_t launch_attn_valu(const AttnArgs& a, hipStream_t stream);
+// the prefill of an fp32 cache (kvg_prefill_f32.hip): a.q holds fp32 queries, a.n_qt 32-pair tiles,
+// a.n_split_max kSplit-key splits; partials (a.part_acc) where there are several, or units of splits
+// (solo: a workgroup per unit, kF32Units partials a split)
+constexpr int kF32Units = 4;
+hipError_t launch_prefill_f32(const PrefillArgs& a, bool solo, hipStream_t stream);
+inline int64_t prefill_f32_workgroups(const PrefillArgs& a) {
+  return (int64_t)a.n_layers * a.batch * a.Hkv * a.n_split_max * a.n_qt;
+}
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int dtype, hipStream_t stream);
 // waves (32 query rows each) per workgroup of the MFMA prefill at head_dim D; a workgroup
 // covers 32 * waves / group rows of each of the group's query heads
@@ -29,7 +35,8 @@ int prefill_head_sets(int D, int group);
 hipError_t launch_shared_splits(const PrefillArgs& a, int dtype, hipStream_t stream);
 // a suffix prefill over shared pages: out = the rows' n_split_max partials combined in order
 hipError_t launch_prefill_combine(const PrefillArgs& a, hipStream_t stream);
-// 8 query heads per KV head: out = each row's partials of the kSplit-key segments it sees
+// fp32 caches, and 8 query heads per KV head: out = each row's partials of the kSplit-key segments it
+// sees
 hipError_t launch_prefill_segments(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream);
 // work items (a split of a KV head of a layer of a sequence) of a decode's grid

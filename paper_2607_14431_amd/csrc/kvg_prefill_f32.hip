@@ -1,0 +1,399 @@
+// Chunked-prefill attention of fp32 caches on v_mfma_f32_32x32x2_f32: fp32 operands, products and
+// sums, so the results are as exact as on the vector ALUs.
+//
+// Workgroup = (layer, sequence, KV head g, tile, split): a tile is 32 (row, query head) pairs of the
+// chunk, heads fastest; a split is kSplit keys at an absolute multiple of 512, so a row's bytes
+// do not depend on how its sequence was chunked.  Each of the four waves takes 128 of the split's
+// keys in blocks of 32; their states are folded in order in LDS, and the splits by
+// prefill_segments_kernel.  In a small call (solo) a workgroup takes a unit of 128 keys, a block a wave, and
+// prefill_f32_units_kernel folds a split's units as the waves' states are folded.
+//
+//   S^T = K Q^T    C = 32 keys x 32 pairs.  A lane's operand of a step is one float of key lane % 32
+//                  (of pair lane % 32): step (j, e) takes dims 8 j + e (lanes 0-31) and 8 j + 4 + e
+//                  (lanes 32-63), so one 16-byte load feeds four steps.  Four accumulation
+//                  chains (j mod 4), added pairwise: shorter chains round less, and independent
+//                  ones issue back to back.
+//   softmax        per block, against the block's largest score, all fp32; the block's state is folded into
+//                  the wave's, so a block's 32 keys are summed alike whichever wave takes them.
+//   O^T += V^T P^T step r takes the keys whose weights accumulator element r holds (8 (r / 4) + r % 4,
+//                  lanes 32-63 four further), so P is the operand as it stands; V^T block db is
+//                  dims ND i + db of lane i, so a lane's ND values are consecutive.
+//
+// What bounds it: the matrix cores (64 cycles a step); V comes from L2 straight into
+// registers, a few loads ahead, K through LDS up to head_dim 128 (V through LDS too would leave one workgroup
+// a CU).  4 layers x 2 x 256 rows x 4 heads over 1k keys, head_dim 64: 169 us a pass on the vector ALUs, where
+// every row read all its keys again; 70 here, 57 of them this kernel; 512 rows over 4k keys, 8 KV heads x
+// 256: 4,627 -> 698.  One row over 8k keys costs more than it did (24 -> 27 us at head_dim 64, 39 -> 74 at
+// 256): 31 of the tile's 32 pairs are padding.
+#include "kvg_launch.h"
+#include "kvg_mfma.h"
+#include "kvg_rows.h"
+
+#include <math.h>
+
+#include <type_traits>
+
+namespace kvg {
+
+namespace {
+
+constexpr int kWaves = kF32Units;
+constexpr int kUnitKeys = kSplit / kF32Units;
+
+template <int N>
+struct FloatVec {
+  float x[N];
+};
+
+// v f_v + x f_x, rounded alike wherever states are folded
+__device__ __forceinline__ float fold(float v, float f_v, float x, float f_x) { return fmaf(x, f_x, v * f_v); }
+
+// Folds the state (pm, pl, pv) of the keys that follow into (m, l, v); (-inf, 0, 0) is the empty one.
+__device__ __forceinline__ void fold_state(float& m, float& l, float& v, float pm, float pl, float pv) {
+  const float m_new = fmaxf(m, pm), f = merge_factor(m, m_new), pf = merge_factor(pm, m_new);
+  l = fold(l, f, pl, pf);
+  v = fold(v, f, pv, pf);
+  m = m_new;
+}
+
+template <int D, bool kSolo>
+__global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillArgs a) {
+  constexpr int NJ = D / 8;            // 16-byte K loads per block and lane
+  constexpr int ND = D / 32;           // O blocks
+  constexpr int NB = ND < 4 ? ND : 4;  // O blocks of a pass over the block's V
+  constexpr int LK = 8;                // K loads ahead
+  constexpr int LV = 8;                // V loads ahead
+  // up to head_dim 128 K blocks of the waves, above it the queries; after the last block the waves' O
+  constexpr bool kStaged = D <= 128;
+  constexpr int RB = D * 4, NCH = RB / 16;
+  constexpr int kOBytes = kWaves * 32 * (D + 1) * 4, kKBytes = kStaged ? kWaves * 32 * RB : 32 * RB;
+  __shared__ __attribute__((aligned(1024))) char s_mem[kOBytes > kKBytes ? kOBytes : kKBytes];
+  float (*s_o)[32][D + 1] = reinterpret_cast<float (*)[32][D + 1]>(s_mem);
+  __shared__ float s_ml[kWaves][32][2];
+
+  // (tile, split, KV head, sequence, layer), late tiles first
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lrow = lane & 31, half = lane >> 5;
+  const int G = a.group;
+  int64_t id = blockIdx.x;
+  const int tile = a.n_qt - 1 - (int)(id % a.n_qt);
+  id /= a.n_qt;
+  const int n_slots = a.n_split_max * (kSolo ? kF32Units : 1);
+  const int slot = (int)(id % n_slots);                        // split, or unit of one
+  id /= n_slots;
+  const int g = (int)(id % a.Hkv);
+  id /= a.Hkv;
+  const int b = (int)(id % a.batch);
+  const int l = (int)(id / a.batch);
+  const int ctx = a.ctx_lens[b];
+  if (ctx < 0 || ctx > a.max_ctx_len) return;
+
+  const int pair = tile * 32 + lrow;
+  const int row = pair / G, h = g * G + pair % G;
+  const bool row_ok = row < a.chunk;
+  const int first = tile * 32 / G, last = min((tile * 32 + 31) / G, a.chunk - 1);
+  const int W = layer_window(a, l);
+  const int row_n = ctx + row, row_lo = window_start(W, row_n + 1);
+  const int mask_lo = window_start(W, ctx + last + 1);        // keys below it are masked for some row
+  const int tile_lo = window_start(W, ctx + first + 1);       // the tile's rows see keys in [tile_lo, tile_hi)
+  const int tile_hi = ctx + last + 1;
+  constexpr int kSlotKeys = kSolo ? kUnitKeys : kSplit, kWaveKeys = kSlotKeys / kWaves;
+  if (slot * kSlotKeys >= tile_hi || (slot + 1) * kSlotKeys <= tile_lo) return;
+  // this wave's keys, in whole blocks of 32
+  const int key_end = min(slot * kSlotKeys + (wave + 1) * kWaveKeys, tile_hi);
+  const int key_begin = max(slot * kSlotKeys + wave * kWaveKeys, tile_lo & ~31);
+  const int n_blocks = key_end > key_begin ? (key_end - key_begin + 31) / 32 : 0;
+
+  const int64_t lbase = (int64_t)(a.layer0 + l) * a.layer_elems;
+  const float* kpool = reinterpret_cast<const float*>(a.k_pool) + lbase;
+  const float* vpool = reinterpret_cast<const float*>(a.v_pool) + lbase;
+  const int32_t* bt = a.block_tables + (int64_t)b * a.max_pages;
+  const int last_page = (tile_hi - 1) / kPage;
+  // page ids of the wave's keys (8 pages), one per lane
+  const int page0 = key_begin / kPage;
+  const int32_t pg = bt[min(page0 + (lane & 15), last_page)];
+  auto page_row = [&](int page_slot) -> int64_t {              // first row of the (page, head) slab
+    int32_t page = __builtin_amdgcn_readlane(pg, min(page_slot, 15));
+    page = (page >= 0 && page < a.n_pages) ? page : 0;
+    return ((int64_t)page * a.Hkv + g) * kPage;
+  };
+
+  // queries: dims 8 j + 4 half + e; in registers up to head_dim 128, above it in LDS (the K layout)
+  FloatVec<4> q[kStaged ? NJ : 1];
+  {
+    const float* qp = reinterpret_cast<const float*>(a.q) +
+                      ((((int64_t)l * a.batch + b) * a.chunk + (row_ok ? row : 0)) * a.Hq + h) * D + 4 * half;
+    if constexpr (kStaged) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) q[j] = __builtin_bit_cast(FloatVec<4>, row_ok ? ld16(qp + 8 * j) : make_uint4(0, 0, 0, 0));
+    } else {
+#pragma unroll
+      for (int j = 0; j < NJ / kWaves; ++j) {
+        const int jj = wave * (NJ / kWaves) + j;
+        st16(s_mem + lrow * RB + 16 * ((2 * jj + half) ^ (lrow & 15)), row_ok ? ld16(qp + 8 * jj) : make_uint4(0, 0, 0, 0));
+      }
+      __syncthreads();
+    }
+  }
+
+  f32x16 o[ND];
+#pragma unroll
+  for (int d = 0; d < ND; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
+  float m_run = -INFINITY, l_run = 0.0f;
+
+  // K rows of block i: lane % 32's row; V rows of block i: key 8 (r / 4) + 4 half + r % 4.  Rows past the
+  // range are rows of a page of the pool: K's are masked, V's are replaced by zeros.
+  auto k_ptr = [&](int i) -> const float* {
+    const int64_t ra = page_row(2 * i), rb = page_row(2 * i + 1);
+    return kpool + ((lrow < kPage ? ra : rb) + lrow % kPage) * D + 4 * half;
+  };
+  FloatVec<4> kf[LK];
+  const float* kp = k_ptr(0);
+  const float* kp_next = kp;
+  // Up to head_dim 128 a block's K goes through the wave's own LDS (buffer_load ... lds, 1 KiB of
+  // consecutive bytes per load; 16-byte chunks at position chunk ^ (row mod 16)): a lane's 16 bytes of
+  // a row straight from L2 took ~90 cycles a load, as long as the MFMAs.  The next block's is
+  // requested once this one's has been read, and lands during P V.
+  lds_char* const k_lds = (lds_char*)(lds_void*)(s_mem + (kStaged ? wave * 32 * RB : 0));
+  constexpr int RPL = 64 / NCH > 0 ? 64 / NCH : 1;
+  const int k_r = lane / NCH;
+  const uint32_t k_off = k_r * RB + 16 * ((lane % NCH) ^ (k_r & 15));
+  const uint32_t k_lane = lrow * RB + 16 * (half ^ (lrow & 15));
+  auto stage_k = [&](int i) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int rows = __builtin_amdgcn_readfirstlane(min(max(tile_hi - (key_begin + 32 * i + kPage * p), 0), kPage));
+      const int64_t off = __builtin_amdgcn_readfirstlane((int)(page_row(2 * i + p) / kPage)) * (int64_t)kPage * D;
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(kpool + off), 0, rows * RB, kBufferWord3);
+#pragma unroll
+      for (int j = 0; j < kPage / RPL; ++j) {
+        const uint32_t at = j * RPL * RB + (k_off ^ (uint32_t)(16 * ((j * RPL) & 15)));
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(k_lds + (p * kPage + j * RPL) * RB), 16, at, 0, 0, 0);
+      }
+    }
+  };
+  if (n_blocks > 0) {
+    if constexpr (kStaged) {
+      stage_k(0);
+    } else {
+#pragma unroll
+      for (int j = 0; j < LK; ++j) kf[j] = __builtin_bit_cast(FloatVec<4>, ld16(kp + 8 * j));
+    }
+  }
+  for (int i = 0; i < n_blocks; ++i) {
+    const int kb = key_begin + 32 * i;
+    kp_next = k_ptr(i + 1);                                    // past the last block: rows never used
+    const int64_t va = page_row(2 * i), vb = page_row(2 * i + 1);
+    const float* vp0 = vpool + (va + 4 * half) * D + ND * lrow;
+    const float* vp1 = vpool + (vb + 4 * half) * D + ND * lrow;
+    FloatVec<NB> vf[LV];
+    auto vfetch = [&](int x) {                                 // step x mod 16 of pass x / 16
+      const int r = x % 16;
+      const float* p = (r < 8 ? vp0 : vp1) + (8 * ((r / 4) & 1) + r % 4) * D + NB * (x / 16);
+      vf[x % LV] = *reinterpret_cast<const FloatVec<NB>*>(p);
+    };
+
+    f32x16 c[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) c[x][r] = 0.0f;
+    auto kread = [&](int j) -> FloatVec<4> {
+      return __builtin_bit_cast(FloatVec<4>, *reinterpret_cast<const lds_u32x4*>(k_lds + (k_lane ^ (uint32_t)(32 * j))));
+    };
+    if constexpr (kStaged) {
+      __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): the block's K
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int j = 0; j < 4; ++j) kf[j] = kread(j);
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const FloatVec<4> k = kf[j % LK];
+      if constexpr (kStaged) {
+        if (j + 4 < NJ) kf[(j + 4) % LK] = kread(j + 4);
+      } else {
+        kf[j % LK] = __builtin_bit_cast(FloatVec<4>, ld16((j + LK < NJ ? kp : kp_next) + 8 * ((j + LK) % NJ)));
+      }
+      if (j >= NJ - LV) vfetch(j - (NJ - LV));
+      const FloatVec<4> qj = kStaged ? q[kStaged ? j : 0] : kread(j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c[j % 4] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.x[e], qj.x[e], c[j % 4], 0, 0, 0);
+    }
+    kp = kp_next;
+    if constexpr (kStaged) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): the reads have returned
+      asm volatile("" ::: "memory");
+      if (i + 1 < n_blocks) stage_k(i + 1);
+    }
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = (c[0][r] + c[1][r]) + (c[2][r] + c[3][r]);
+    if (kb + 31 > ctx + first || kb < mask_lo) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = kb + half * 4 + (r >> 2) * 8 + (r & 3);
+        s[r] = (key <= row_n && key >= row_lo) ? s[r] : -INFINITY;
+      }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    const float2 mh = halves32(mx);
+    // the block's own state (reference: its largest score), folded into the wave's
+    const float m_blk = fmaxf(mh.x, mh.y) * a.scale_log2;
+    const float m_ref = m_blk == -INFINITY ? 0.0f : m_blk;     // no key seen: every p is 0
+    float psum = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(s[r] * a.scale_log2 - m_ref);
+      psum += s[r];
+    }
+    const float2 ph = halves32(psum);
+    const float m_new = fmaxf(m_run, m_blk);
+    const float f_run = merge_factor(m_run, m_new), f_blk = merge_factor(m_blk, m_new);
+    l_run = fold(l_run, f_run, ph.x + ph.y, f_blk);
+    m_run = m_new;
+    const bool edge = kb + 32 > tile_hi || kb < tile_lo;
+#pragma unroll
+    for (int pass = 0; pass < ND / NB; ++pass) {
+      f32x16 ob[NB];
+#pragma unroll
+      for (int d = 0; d < NB; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ob[d][r] = 0.0f;
+      auto pv = [&](auto masked) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int x = 16 * pass + r;
+          FloatVec<NB> v = vf[x % LV];
+          if (x + LV < 16 * (ND / NB)) vfetch(x + LV);
+          if constexpr (decltype(masked)::value) {
+            const int key = kb + half * 4 + (r >> 2) * 8 + (r & 3);
+            const bool in = key >= tile_lo && key < tile_hi;
+#pragma unroll
+            for (int d = 0; d < NB; ++d) v.x[d] = in ? v.x[d] : 0.0f;
+          }
+#pragma unroll
+          for (int d = 0; d < NB; ++d) ob[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.x[d], s[r], ob[d], 0, 0, 0);
+        }
+      };
+      if (edge)
+        pv(std::true_type{});
+      else
+        pv(std::false_type{});
+#pragma unroll
+      for (int d = 0; d < NB; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[NB * pass + d][r] = fold(o[NB * pass + d][r], f_run, ob[d][r], f_blk);
+    }
+  }
+
+  __syncthreads();                                             // every wave is past its K blocks
+  // ---- the four waves' states in order: O^T element r of block d is dim ND (8 (r / 4) + 4 half + r % 4) + d
+  // of pair lrow
+#pragma unroll
+  for (int d = 0; d < ND; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s_o[wave][lrow][ND * (8 * (r >> 2) + 4 * half + (r & 3)) + d] = o[d][r];
+  if (half == 0) {
+    s_ml[wave][lrow][0] = m_run;
+    s_ml[wave][lrow][1] = l_run;
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < 32 * D; t += 64 * kWaves) {
+    const int p = t / D, d = t % D;
+    const int prow = (tile * 32 + p) / G, ph = g * G + (tile * 32 + p) % G;
+    if (prow >= a.chunk) break;
+    float m = -INFINITY, lsum = 0.0f, v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) fold_state(m, lsum, v, s_ml[w][p][0], s_ml[w][p][1], s_o[w][p][d]);
+    const int64_t rh = (((int64_t)l * a.batch + b) * a.chunk + prow) * a.Hq + ph;
+    if (a.part_acc == nullptr) {
+      a.out[rh * D + d] = v / lsum;
+    } else {
+      const int64_t pidx = rh * n_slots + slot;
+      a.part_acc[pidx * D + d] = v;
+      if (d == 0) *reinterpret_cast<float2*>(a.part_ml + pidx * 2) = make_float2(m, lsum);
+    }
+  }
+}
+
+// The units' partials of a row in the order the one-workgroup split takes them, then the splits as
+// combine_splits does.  One element per lane.
+__global__ __launch_bounds__(256) void prefill_f32_units_kernel(const PrefillArgs a, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int64_t row_head = i / a.D;
+  const int row = (int)((row_head / a.Hq) % a.chunk);
+  const int b = (int)((row_head / ((int64_t)a.Hq * a.chunk)) % a.batch);
+  const int l = (int)(row_head / ((int64_t)a.Hq * a.chunk * a.batch));
+  const int ctx = a.ctx_lens[b];
+  if (ctx < 0 || ctx > a.max_ctx_len) return;
+  const int n_keys = ctx + row + 1;
+  const int u0 = window_start(layer_window(a, l), n_keys) / kUnitKeys, u1 = (n_keys - 1) / kUnitKeys;
+  const int64_t p0 = row_head * a.n_split_max * kF32Units;
+  const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + p0;
+  const float* acc = a.part_acc + p0 * a.D + i % a.D;
+  constexpr int NS = 2, U = NS * kF32Units;                    // splits and units whose loads are in flight
+  float m = -INFINITY;
+  for (int u = u0; u <= u1; u += U) {
+    float mv[U];
+#pragma unroll
+    for (int x = 0; x < U; ++x) mv[x] = ml[min(u + x, u1)].x;
+#pragma unroll
+    for (int x = 0; x < U; ++x) m = fmaxf(m, mv[x]);
+  }
+  float lsum = 0.0f, o = 0.0f;
+  for (int s = u0 / kF32Units; s <= u1 / kF32Units; s += NS) {
+    float2 pv[U];
+    float av[U];
+#pragma unroll
+    for (int x = 0; x < U; ++x) {
+      const int u = min(max(s * kF32Units + x, u0), u1);
+      pv[x] = ml[u];
+      av[x] = acc[(int64_t)u * a.D];
+    }
+#pragma unroll
+    for (int y = 0; y < NS; ++y) {
+      float sm = -INFINITY, sl = 0.0f, sv = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kF32Units; ++w) {
+        const int x = y * kF32Units + w, u = s * kF32Units + x;
+        if (u >= u0 && u <= u1) fold_state(sm, sl, sv, pv[x].x, pv[x].y, av[x]);
+      }
+      const float f = merge_factor(sm, m);
+      lsum = fmaf(sl, f, lsum);
+      o = fmaf(sv, f, o);
+    }
+  }
+  a.out[i] = o / lsum;
+}
+
+template <bool kSolo>
+hipError_t launch(const PrefillArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)(prefill_f32_workgroups(a) * (kSolo ? kF32Units : 1)));
+  switch (a.D) {
+    case 64: prefill_f32_kernel<64, kSolo><<<grid, 64 * kWaves, 0, stream>>>(a); break;
+    case 128: prefill_f32_kernel<128, kSolo><<<grid, 64 * kWaves, 0, stream>>>(a); break;
+    case 256: prefill_f32_kernel<256, kSolo><<<grid, 64 * kWaves, 0, stream>>>(a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefill_f32(const PrefillArgs& a, bool solo, hipStream_t stream) {
+  const hipError_t e = solo ? launch<true>(a, stream) : launch<false>(a, stream);
+  if (e != hipSuccess || a.part_acc == nullptr) return e;
+  if (!solo) return launch_prefill_segments(a, stream);
+  const int64_t n = (int64_t)a.n_layers * a.batch * a.chunk * a.Hq * a.D;
+  prefill_f32_units_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, stream>>>(a, n);
+  return hipGetLastError();
+}
+
+}  // namespace kvg

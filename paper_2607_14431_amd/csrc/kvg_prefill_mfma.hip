@@ -305,7 +305,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
   {
     const int64_t qrow = kShared ? (((int64_t)l * a.batch + (row_ok ? b : 0)) * a.chunk + (row_ok ? row : 0)) * a.Hq + h
                                  : (((int64_t)l * a.batch + b) * a.chunk + (row_ok ? row : 0)) * a.Hq + h;
-    const uint16_t* qp = a.q + qrow * D;
+    const uint16_t* qp = static_cast<const uint16_t*>(a.q) + qrow * D;
     const uint16_t* qlp = a.q_lo + qrow * D;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {

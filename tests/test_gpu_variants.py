@@ -31,6 +31,52 @@ def test_group8_prefill(dtype, D, Hq, Hkv, ctxs, chunk, qsig, div, windows):
     _prefill_case(dtype, D, Hq, Hkv, ctxs, chunk, qsig, windows, div)
 
 
+# fp32 caches: tiles of 32 (row, head) pairs, key blocks of 32, waves of 128, splits of 512
+F32_CASES = [
+    (64, 4, 2, [0, 31], 1, -1, 0, (0, 0)),
+    (64, 2, 2, [511, 100], 33, -1, 0, (0, 40)),
+    (128, 8, 1, [512], 65, 2, 2, (0,)),
+    (128, 8, 2, [127, 128], 17, -1, 0, (0, 150)),
+    (256, 4, 1, [1100], 40, -1, 0, (0, 513)),
+    (256, 8, 1, [0, 30], 31, 2, 2, (0,)),
+]
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,ctxs,chunk,qsig,div,windows", F32_CASES)
+def test_f32_prefill(D, Hq, Hkv, ctxs, chunk, qsig, div, windows):
+    _prefill_case("f32", D, Hq, Hkv, ctxs, chunk, qsig, windows, div)
+
+
+def test_f32_prefill_unit_per_workgroup():
+    # one layer's call is small (a workgroup per 128 keys), the same layer among others is not
+    import numpy as np
+    import torch
+
+    from paper_2607_14431_amd import kvg
+    D, Hq, Hkv, ctx, chunk, L = 128, 8, 4, 1100, 40, 8
+    windows = tuple(100 * i for i in range(L))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    n_pages = (ctx + chunk + 15) // 16
+    cache = kvg.Cache.allocate(L, n_pages, Hq, Hkv, D, torch.float32, windows=windows)
+    cache.k_pool.normal_(generator=g)
+    cache.v_pool.normal_(generator=g)
+    table = torch.randperm(n_pages, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda()[None]
+    seqs = kvg.Seqs(table, torch.tensor([ctx], dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda"), ctx)
+    q, k, v = (torch.randn((L, 1, chunk, h, D), device="cuda", generator=g) for h in (Hq, Hkv, Hkv))
+    rp = kvg.rope(10000.0, kvg.KVG_ROPE_HALF)
+
+    def run(l0, n):
+        out = torch.empty((n, 1, chunk, Hq, D), device="cuda")
+        ws = torch.empty(kvg.kvg_prefill_workspace_bytes(cache, seqs, n, chunk), dtype=torch.uint8, device="cuda")
+        s = slice(l0, l0 + n)
+        kvg.kvg_prefill_attn(cache, seqs, rp, l0, n, chunk, q[s], k[s], v[s], 1.0 / np.sqrt(D), out, ws)
+        return out
+
+    together = run(0, L)
+    for layer in range(L):
+        assert torch.equal(run(layer, 1)[0], together[layer])
+
+
 # The comparison's single pass: rows read as vectors and element by element, fewer elements than
 # lanes, references that have to be raised (spread > e^300), infinities.
 @pytest.mark.parametrize("rows,V,scale", [(1, 1, 1.0), (3, 7, 1.0), (2, 64, 1.0), (3, 4095, 5.0), (2, 4100, 5.0),
