@@ -147,9 +147,10 @@ int kvg_merkle_root(const uint8_t* digests_dev, uint64_t n_leaves, uint8_t* root
   uint64_t n = n_leaves;
   int which = 0;
   do {
-    const uint64_t n_out = (n + 1) / 2;
+    const int levels = kvg::merkle_levels(n);
+    const uint64_t n_out = (n + (1u << levels) - 1) >> levels;
     uint8_t* dst = (n_out == 1) ? root_dev : buf[which];
-    const hipError_t e = kvg::launch_merkle_level(src, n, dst, s);
+    const hipError_t e = kvg::launch_merkle_levels(src, n, dst, s);
     if (e != hipSuccess) return KVG_E_HIP;
     src = dst;
     n = n_out;

@@ -27,7 +27,13 @@ struct DedupArgs {
 };
 
 hipError_t launch_leaf_digests(const DigestArgs& a, hipStream_t stream);
-hipError_t launch_merkle_level(const uint8_t* in, uint64_t n_in, uint8_t* out, hipStream_t stream);
+// Tree levels that one launch over n nodes computes.  A subtree per workgroup while each has a CU to itself;
+// above that the narrow levels of two would queue on the same SIMDs (262,144 leaves: 128 us a launch per
+// level, 143 with subtrees from the leaves on, 114 with one level first).
+constexpr int kCus = 256, kSubtreeLevels = 9;
+inline int merkle_levels(uint64_t n) { return n > (uint64_t)kCus << kSubtreeLevels ? 1 : kSubtreeLevels; }
+// those levels: in [n_in][32] to out [ceil(n_in / 2^levels)][32]
+hipError_t launch_merkle_levels(const uint8_t* in, uint64_t n_in, uint8_t* out, hipStream_t stream);
 hipError_t launch_dedup(const DedupArgs& a, hipStream_t stream);
 
 }  // namespace kvg

@@ -164,3 +164,37 @@ def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window):
     assert torch.isfinite(together).all()
     for b in range(B):
         assert torch.equal(together[:, b:b + 1].view(torch.int32), decode([b]).view(torch.int32)), f"context {ctxs[b]}"
+
+
+# Two waves per 64 leaves (up to 512 x 64 leaves of equal length): one set and two sets a workgroup, partial
+# sets, one and several blocks; a ragged last leaf and one leaf too many take a lane per leaf
+@pytest.mark.parametrize("n,leaf,short", [(1, 64, 0), (65, 128, 0), (65, 128, 9), (16_384, 64, 0), (16_385, 64, 0),
+                                          (32_767, 64, 0), (32_768, 64, 64), (32_769, 64, 0)])
+def test_few_leaves(n, leaf, short):
+    import hashlib
+
+    import numpy as np
+    import torch
+
+    from paper_2607_14431_amd import kvg
+    data = np.random.default_rng(n).integers(0, 256, size=n * leaf - short, dtype=np.uint8)
+    got = torch.zeros(((n * leaf - short + leaf - 1) // leaf, 32), dtype=torch.uint8, device="cuda")
+    kvg.kvg_leaf_digests(torch.from_numpy(data).cuda(), leaf, got)
+    raw = data.tobytes()
+    want = [hashlib.sha256(raw[i:i + leaf]).digest() for i in range(0, len(raw), leaf)]
+    assert got.cpu().numpy().tobytes() == b"".join(want)
+
+
+# Subtrees of 512 nodes (odd counts at every level, one launch, two, three) and one level first
+@pytest.mark.parametrize("n", [1, 2, 511, 512, 513, 1023, 1025, 131_072, 131_073, 262_145, 300_001])
+def test_merkle_subtrees(n):
+    import numpy as np
+    import torch
+
+    from oracle.digest import merkle_root
+    from paper_2607_14431_amd import kvg
+    leaves = np.random.default_rng(n).integers(0, 256, size=(n, 32), dtype=np.uint8)
+    root = torch.zeros(32, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(kvg.kvg_merkle_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    kvg.kvg_merkle_root(torch.from_numpy(leaves).cuda(), n, root, ws)
+    assert root.cpu().numpy().tobytes() == merkle_root(leaves)
