@@ -37,26 +37,35 @@ struct RotItem {
   float x[2][E];   // [0]: vector at e0, [1]: partner vector (half pairing only)
 };
 
+// An item's raw vectors: at e0, and at e0 + D/2 (half pairing only).
+struct RawItem {
+  uint4 a, b;
+};
+
 template <typename T>
-__device__ __forceinline__ void rotate_item(const T* row, int e0, int half, int pairing,
-                                            const float* cs, RotItem<T>& it) {
+__device__ __forceinline__ RawItem load_item(const T* row, int e0, int half, int pairing) {
+  RawItem it;
+  it.a = ld16(row + e0);
+  it.b = pairing == 0 ? ld16(row + e0 + half) : make_uint4(0, 0, 0, 0);
+  return it;
+}
+
+template <typename T>
+__device__ __forceinline__ void rotate_item(const RawItem& raw, int e0, int pairing, const float* cs, RotItem<T>& it) {
   constexpr int E = Elem<T>::kPerVec;
   if (pairing == 0) {
-    const uint4 va = ld16(row + e0);
-    const uint4 vb = ld16(row + e0 + half);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      float a = Elem<T>::get(va, e), b = Elem<T>::get(vb, e);
+      float a = Elem<T>::get(raw.a, e), b = Elem<T>::get(raw.b, e);
       const int p = e0 + e;
       rotate_pair(a, b, cs[2 * p], cs[2 * p + 1]);
       it.x[0][e] = a;
       it.x[1][e] = b;
     }
   } else {
-    const uint4 va = ld16(row + e0);
 #pragma unroll
     for (int e = 0; e < E; e += 2) {
-      float a = Elem<T>::get(va, e), b = Elem<T>::get(va, e + 1);
+      float a = Elem<T>::get(raw.a, e), b = Elem<T>::get(raw.a, e + 1);
       const int p = (e0 + e) >> 1;
       rotate_pair(a, b, cs[2 * p], cs[2 * p + 1]);
       it.x[0][e] = a;
@@ -110,6 +119,41 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
   const int64_t pos = a.start_pos[b] + t;
   const int D = a.D, half = D >> 1;
 
+  const int items_per_row = (a.pairing == 0) ? (half / E) : (D / E);
+  const int vec_per_row = D / E;
+  const int n_k = page_ok ? a.Hkv * items_per_row : 0, n_v = page_ok ? a.Hkv * vec_per_row : 0;
+  const int n_q = a.q_raw != nullptr ? a.Hq * items_per_row : 0;
+  const int l_begin = blockIdx.y * a.layers_per_block;
+  const int l_end = min(l_begin + a.layers_per_block, a.n_layers);
+  const int row = t % kPage;
+
+  auto raw_tok = [&](int l) -> int64_t { return ((int64_t)l * a.batch + b) * a.chunk + i; };
+  auto load_rot = [&](const void* raw, int n_heads, int l, int it) {
+    const int h = it / items_per_row;
+    return load_item<R>(reinterpret_cast<const R*>(raw) + (raw_tok(l) * n_heads + h) * D, (it - h * items_per_row) * E, half,
+                        a.pairing);
+  };
+  auto load_v = [&](int l, int it) {
+    return ld16(reinterpret_cast<const R*>(a.v_raw) + raw_tok(l) * a.Hkv * D + it * E);
+  };
+  // A thread's first item of each kind, requested together and before the layer's stores, the first
+  // layer's before the angles: each kind waiting for its own loads took 10 us of a 512-row chunk
+  // with 16 + 8 + 8 heads x 256 instead of 7, and 630 instead of 617 of a 3,950-token block's 48 layers.  Requesting
+  // the next layer's ahead of this one's stores costs registers and with them wavefronts: 641.
+  struct First {
+    RawItem k, q;
+    uint4 v;
+  };
+  const int t0 = threadIdx.x;
+  auto fetch = [&](int l) {
+    First f{};
+    if (t0 < n_k) f.k = load_rot(a.k_raw, a.Hkv, l, t0);
+    if (t0 < n_v) f.v = load_v(l, t0);
+    if (t0 < n_q) f.q = load_rot(a.q_raw, a.Hq, l, t0);
+    return f;
+  };
+  First cur = fetch(l_begin);
+
   __shared__ float cs[2 * kMaxHalfDim];
   for (int p = threadIdx.x; p < half; p += blockDim.x) {
     double s, c;
@@ -119,71 +163,58 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
   }
   __syncthreads();
 
-  const int items_per_row = (a.pairing == 0) ? (half / E) : (D / E);
-  const int vec_per_row = D / E;
-  const int l_begin = blockIdx.y * a.layers_per_block;
-  const int l_end = min(l_begin + a.layers_per_block, a.n_layers);
-  const int row = t % kPage;
-
   for (int l = l_begin; l < l_end; ++l) {
-    const int64_t raw_tok = ((int64_t)l * a.batch + b) * a.chunk + i;
     const int64_t lbase = (int64_t)(a.layer0 + l) * a.layer_elems;
     T* kpool = reinterpret_cast<T*>(a.k_pool) + lbase;
     T* vpool = reinterpret_cast<T*>(a.v_pool) + lbase;
-    const R* kraw = reinterpret_cast<const R*>(a.k_raw) + raw_tok * a.Hkv * D;
-    const R* vraw = reinterpret_cast<const R*>(a.v_raw) + raw_tok * a.Hkv * D;
 
-    if (page_ok) {
-      // keys: rotate, round, store through the block table
-      for (int it = threadIdx.x; it < a.Hkv * items_per_row; it += blockDim.x) {
-        const int h = it / items_per_row;
-        const int e0 = (it - h * items_per_row) * E;
-        RotItem<R> r;
-        rotate_item<R>(kraw + (int64_t)h * D, e0, half, a.pairing, cs, r);
-        T* dst = kpool + (((int64_t)page * a.Hkv + h) * kPage + row) * D;
-        store_elems<T, E>(dst + e0, r.x[0]);
-        if (a.pairing == 0) store_elems<T, E>(dst + e0 + half, r.x[1]);
-      }
-      // values: copy (rounded to the storage type when it differs from the raw type)
-      for (int it = threadIdx.x; it < a.Hkv * vec_per_row; it += blockDim.x) {
-        const int h = it / vec_per_row;
-        const int e0 = (it - h * vec_per_row) * E;
-        T* dst = vpool + (((int64_t)page * a.Hkv + h) * kPage + row) * D + e0;
-        const uint4 raw = ld16(vraw + (int64_t)h * D + e0);
-        if constexpr (std::is_same<T, R>::value) {
-          st16(dst, raw);
-        } else {
-          float x[E];
+    // keys: rotate, round, store through the block table
+    for (int it = t0; it < n_k; it += blockDim.x) {
+      const RawItem raw = it == t0 ? cur.k : load_rot(a.k_raw, a.Hkv, l, it);
+      const int h = it / items_per_row;
+      const int e0 = (it - h * items_per_row) * E;
+      RotItem<R> r;
+      rotate_item<R>(raw, e0, a.pairing, cs, r);
+      T* dst = kpool + (((int64_t)page * a.Hkv + h) * kPage + row) * D;
+      store_elems<T, E>(dst + e0, r.x[0]);
+      if (a.pairing == 0) store_elems<T, E>(dst + e0 + half, r.x[1]);
+    }
+    // values: copy (rounded to the storage type when it differs from the raw type)
+    for (int it = t0; it < n_v; it += blockDim.x) {
+      const uint4 raw = it == t0 ? cur.v : load_v(l, it);
+      const int h = it / vec_per_row;
+      const int e0 = (it - h * vec_per_row) * E;
+      T* dst = vpool + (((int64_t)page * a.Hkv + h) * kPage + row) * D + e0;
+      if constexpr (std::is_same<T, R>::value) {
+        st16(dst, raw);
+      } else {
+        float x[E];
 #pragma unroll
-          for (int e = 0; e < E; ++e) x[e] = Elem<R>::get(raw, e);
-          store_elems<T, E>(dst, x);
-        }
+        for (int e = 0; e < E; ++e) x[e] = Elem<R>::get(raw, e);
+        store_elems<T, E>(dst, x);
       }
     }
-    if (a.q_raw != nullptr) {
-      const R* qraw = reinterpret_cast<const R*>(a.q_raw) + raw_tok * a.Hq * D;
-      for (int it = threadIdx.x; it < a.Hq * items_per_row; it += blockDim.x) {
-        const int h = it / items_per_row;
-        const int e0 = (it - h * items_per_row) * E;
-        RotItem<R> r;
-        rotate_item<R>(qraw + (int64_t)h * D, e0, half, a.pairing, cs, r);
-        const int64_t qoff = (raw_tok * a.Hq + h) * D;
-        if constexpr (sizeof(R) == 2) {
-          if (a.q_out_bf16) {                      // bf16 hi + lo queries (bf16 and fp8 caches)
-            uint16_t* qh = reinterpret_cast<uint16_t*>(a.q_out) + qoff;
-            uint16_t* ql = reinterpret_cast<uint16_t*>(a.q_out_lo) + qoff;
-            store_split<E>(qh + e0, ql + e0, r.x[0]);
-            if (a.pairing == 0) store_split<E>(qh + e0 + half, ql + e0 + half, r.x[1]);
-            continue;
-          }
-        }
-        {
-          float* q = reinterpret_cast<float*>(a.q_out) + qoff;
-          store_vec_f32<R>(q + e0, r.x[0]);
-          if (a.pairing == 0) store_vec_f32<R>(q + e0 + half, r.x[1]);
+    for (int it = t0; it < n_q; it += blockDim.x) {
+      const RawItem raw = it == t0 ? cur.q : load_rot(a.q_raw, a.Hq, l, it);
+      const int h = it / items_per_row;
+      const int e0 = (it - h * items_per_row) * E;
+      RotItem<R> r;
+      rotate_item<R>(raw, e0, a.pairing, cs, r);
+      const int64_t qoff = (raw_tok(l) * a.Hq + h) * D;
+      if constexpr (sizeof(R) == 2) {
+        if (a.q_out_bf16) {                        // bf16 hi + lo queries (bf16 and fp8 caches)
+          uint16_t* qh = reinterpret_cast<uint16_t*>(a.q_out) + qoff;
+          uint16_t* ql = reinterpret_cast<uint16_t*>(a.q_out_lo) + qoff;
+          store_split<E>(qh + e0, ql + e0, r.x[0]);
+          if (a.pairing == 0) store_split<E>(qh + e0 + half, ql + e0 + half, r.x[1]);
+          continue;
         }
       }
+      float* q = reinterpret_cast<float*>(a.q_out) + qoff;
+      store_vec_f32<R>(q + e0, r.x[0]);
+      if (a.pairing == 0) store_vec_f32<R>(q + e0 + half, r.x[1]);
     }
+    if (l + 1 < l_end) cur = fetch(l + 1);
   }
 }
 
