@@ -88,17 +88,18 @@ constexpr int64_t kF32SoloWorkgroups = 128;
 // Workspace of an fp32 cache's prefill: rotated queries, split partials.
 struct F32Ws {
   size_t q, acc, ml, total;
-  bool solo, parts;
 };
 
-F32Ws f32_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows) {
-  F32Ws w;
-  const size_t nrow_heads = (size_t)n_layers * s->batch * rows * c->n_q_heads;
+bool f32_solo(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows) {
   const int64_t n_wg = (int64_t)n_layers * s->batch * c->n_kv_heads * n_split_max(s, rows) *
                        (((int64_t)rows * (c->n_q_heads / c->n_kv_heads) + 31) / 32);
-  w.solo = n_wg <= kF32SoloWorkgroups && (int64_t)s->max_ctx_len + rows > kSplit / kvg::kF32Units;
-  w.parts = w.solo || n_split_max(s, rows) > 1;
-  const size_t ns = w.parts ? (size_t)n_split_max(s, rows) * (w.solo ? kvg::kF32Units : 1) : 0;
+  return n_wg <= kF32SoloWorkgroups && (int64_t)s->max_ctx_len + rows > kSplit / kvg::kF32Units;
+}
+
+F32Ws f32_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows, bool solo) {
+  F32Ws w;
+  const size_t nrow_heads = (size_t)n_layers * s->batch * rows * c->n_q_heads;
+  const size_t ns = (size_t)n_split_max(s, rows) * (solo ? kvg::kF32Units : 1);
   w.q = align_up(nrow_heads * c->head_dim * sizeof(float));
   w.acc = align_up(nrow_heads * ns * c->head_dim * sizeof(float));
   w.ml = align_up(nrow_heads * ns * 2 * sizeof(float));
@@ -169,8 +170,11 @@ int check_raw(const void* k_raw, const void* v_raw) {
 int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t layer0, int32_t n_layers,
              int32_t rows, const void* q_raw, const void* k_raw, const void* v_raw, float scale,
              float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
-  const F32Ws w = f32_ws(c, s, n_layers, rows);
-  if (ws == nullptr || ws_bytes < w.total) return KVG_E_WORKSPACE;
+  if (ws == nullptr || ws_bytes < f32_ws(c, s, n_layers, rows, false).total) return KVG_E_WORKSPACE;
+  // the bytes are the same either way: a workspace made for a longer chunk, which takes a workgroup
+  // per split, may be too small for a shorter one's units
+  const bool solo = f32_solo(c, s, n_layers, rows) && ws_bytes >= f32_ws(c, s, n_layers, rows, true).total;
+  const F32Ws w = f32_ws(c, s, n_layers, rows, solo);
   kvg::PrefillArgs a;
   std::memset(&a, 0, sizeof(a));
   a.k_pool = c->k_pool;
@@ -195,7 +199,7 @@ int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t l
   a.n_qt = (int)(((int64_t)rows * a.group + 31) / 32);
   a.n_split_max = n_split_max(s, rows);
   fill_windows(c, layer0, n_layers, a.window);
-  if (w.parts) {
+  if (solo || a.n_split_max > 1) {
     a.part_acc = reinterpret_cast<float*>(static_cast<char*>(ws) + w.q);
     a.part_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + w.q + w.acc);
   }
@@ -204,7 +208,7 @@ int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t l
   ap.q_raw = q_raw;
   ap.q_out = ws;
   const int st = hip_status(kvg::launch_append(ap, c->dtype, stream));
-  return st == KVG_OK ? hip_status(kvg::launch_prefill_f32(a, w.solo, stream)) : st;
+  return st == KVG_OK ? hip_status(kvg::launch_prefill_f32(a, solo, stream)) : st;
 }
 
 // Workspace of the decode kernels: the split partials.
@@ -276,14 +280,13 @@ DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, size
 }
 
 // What the size query returns: enough for a call of this size, and for a wave per unit wherever a
-// call no larger than this one takes it: four partials per split of every row, which only
-// windowed layers (whose rows hold more splits than their windows touch) let exceed the resident
-// waves.
+// call no larger than this one takes it: four partials per split of every row, which with
+// windowed layers (whose rows hold more splits than their windows touch) exceed the resident
+// waves.  The same with and without windows, so one workspace serves caches of one shape.
 size_t decode_ws_bytes(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
   const size_t unit_bytes = (size_t)(c->n_q_heads / c->n_kv_heads) * (c->head_dim + 2) * sizeof(float);
   const size_t layout = (size_t)n_layers * s->batch * c->n_kv_heads * n_split_max(s, 1) * 4;
-  const size_t most = c->layer_window != nullptr ? 4 * kSoloWaves : kSoloWaves;
-  const size_t units = c->dtype == KVG_F32 ? 0 : std::min(most, layout);
+  const size_t units = c->dtype == KVG_F32 ? 0 : std::min<size_t>(4 * kSoloWaves, layout);
   return std::max(decode_ws(c, s, n_layers).total, units * unit_bytes + 2 * kAlign);
 }
 
@@ -571,7 +574,7 @@ size_t kvg_prefill_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs,
   if (check_cache(cache) != KVG_OK || seqs == nullptr || n_layers <= 0 || chunk_len <= 0 || seqs->batch <= 0)
     return 0;
   if (use_mfma(cache)) return mfma_ws(cache, seqs, n_layers, chunk_len);
-  return f32_ws(cache, seqs, n_layers, chunk_len).total;
+  return f32_ws(cache, seqs, n_layers, chunk_len, f32_solo(cache, seqs, n_layers, chunk_len)).total;
 }
 
 int kvg_prefill_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope, int32_t layer0,

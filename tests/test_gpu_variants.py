@@ -65,9 +65,10 @@ def test_f32_prefill_unit_per_workgroup():
     q, k, v = (torch.randn((L, 1, chunk, h, D), device="cuda", generator=g) for h in (Hq, Hkv, Hkv))
     rp = kvg.rope(10000.0, kvg.KVG_ROPE_HALF)
 
-    def run(l0, n):
+    def run(l0, n, ws_bytes=None):
         out = torch.empty((n, 1, chunk, Hq, D), device="cuda")
-        ws = torch.empty(kvg.kvg_prefill_workspace_bytes(cache, seqs, n, chunk), dtype=torch.uint8, device="cuda")
+        ws_bytes = ws_bytes or kvg.kvg_prefill_workspace_bytes(cache, seqs, n, chunk)
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
         s = slice(l0, l0 + n)
         kvg.kvg_prefill_attn(cache, seqs, rp, l0, n, chunk, q[s], k[s], v[s], 1.0 / np.sqrt(D), out, ws)
         return out
@@ -75,6 +76,13 @@ def test_f32_prefill_unit_per_workgroup():
     together = run(0, L)
     for layer in range(L):
         assert torch.equal(run(layer, 1)[0], together[layer])
+    # a workspace without room for the units' partials: one partial per split and row
+    rows, splits = chunk * Hq, (ctx + chunk + 511) // 512
+    small = rows * D * 4 + rows * splits * (D + 2) * 4
+    assert small % 256 == 0 and small < kvg.kvg_prefill_workspace_bytes(cache, seqs, 1, chunk)
+    assert torch.equal(run(3, 1, small)[0], together[3])
+    with pytest.raises(kvg.KvgError):
+        run(3, 1, small - 1)
 
 
 # The comparison's single pass: rows read as vectors and element by element, fewer elements than
@@ -198,3 +206,18 @@ def test_merkle_subtrees(n):
     ws = torch.empty(kvg.kvg_merkle_workspace_bytes(n), dtype=torch.uint8, device="cuda")
     kvg.kvg_merkle_root(torch.from_numpy(leaves).cuda(), n, root, ws)
     assert root.cpu().numpy().tobytes() == merkle_root(leaves)
+
+
+def test_decode_workspace_serves_windowed_caches():
+    # the size asked for without windows is enough with them (12B-class stack, 5 of 6 layers windowed)
+    import torch
+
+    from paper_2607_14431_amd import kvg
+    for dtype in (torch.bfloat16, torch.float8_e4m3fn, torch.float32):
+        for layers, ctx in ((1, 100), (6, 5000), (48, 4672)):
+            seqs = kvg.Seqs(torch.zeros((1, 400), dtype=torch.int32, device="cuda"),
+                            torch.tensor([ctx], dtype=torch.int32, device="cuda"),
+                            torch.zeros(1, dtype=torch.int64, device="cuda"), ctx)
+            sizes = [kvg.kvg_decode_workspace_bytes(kvg.Cache.allocate(layers, 1, 4, 2, 64, dtype, windows=w), seqs, layers)
+                     for w in (None, tuple(0 if (i + 1) % 6 == 0 else 1024 for i in range(layers)))]
+            assert sizes[0] == sizes[1] > 0
