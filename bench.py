@@ -402,7 +402,7 @@ def window_bench(args) -> dict:
         "prefill_TFLOPs": round(pf_tflops, 2),
         "phases_ms": {"deposit": round(t_dep * len(pairs), 3), "graft": round(t_gra * len(pairs), 3),
                       "prefill": round(t_pre, 3), "decode": round(t_dec * T, 3)},
-        "roofline": {"kernel": "kvg_decode_attn: decode_kernel<bf16, 256, 2> + decode_merge_kernel",
+        "roofline": {"kernel": "kvg_decode_attn: decode_mfma_kernel<bf16, 256> + merge",
                      "bound": "hbm", "achieved": round(dec_gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(dec_gbps / HBM_PEAK_GBPS, 4),
                      "traffic": measured_traffic("traffic_12b_window32k.md", "decode_bytes_per_launch"),
@@ -1022,7 +1022,7 @@ def fp8_figures(h, kvg, torch, stream, w) -> dict:
                "bound": "hbm", "achieved": round(pay / (avg["graft"] * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBPS,
                "unit": "GB/s", "frac": round(pay / (avg["graft"] * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                "bytes_per_launch": pay, "ms": round(avg["graft"], 4), "deposit_ms": round(avg["deposit"], 4)},
-           "fp8 E4M3 cache: decode_kernel + decode_merge_kernel (not in the step)": {
+           "fp8 E4M3 cache: decode_mfma_kernel + merge (not in the step)": {
                "bound": "hbm", "achieved": round(dec_gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                "frac": round(dec_gbps / HBM_PEAK_GBPS, 4), "bytes_per_launch": round(dec_bytes),
                "avg_launch_us": round(avg["decode"] * 1e3, 2), "tok_s": round(w8.batch / (avg["decode"] * 1e-3), 1)},
