@@ -155,9 +155,8 @@ kvg::AppendArgs append_args(const kvg_cache* c, const kvg_seqs* s, const kvg_rop
 
 int hip_status(hipError_t e) { return e == hipSuccess ? KVG_OK : KVG_E_HIP; }
 
-// A launch of `wgs` workgroups of `threads` threads fits the dispatch limits (grid size in
-// threads below 2^32).  Every launch of a call is checked before the first one is enqueued.
-bool fits_grid(int64_t wgs, int threads) { return wgs >= 0 && wgs * (int64_t)threads <= (int64_t)UINT32_MAX; }
+// Every launch of a call is checked before the first one is enqueued.
+using kvg::fits_grid;
 
 // The append's grid: (batch * chunk) x layer groups of 256 threads.
 bool append_fits(const kvg_seqs* s, int32_t chunk) { return fits_grid((int64_t)s->batch * chunk, 256); }

@@ -758,7 +758,7 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream) {
   const dim3 grid((unsigned)n_rows);
   if (a.solo)
     merge_splits_kernel<true><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
-  else if (a.n_split_max > 16 && merge_lds(a) <= 65536)
+  else if (a.n_split_max > 16 && merge_lds(a) <= 65536 && fits_grid(n_rows, kMergeThreads))   // the host checked 256 threads a row
     merge_splits_kernel<false><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
   else
     decode_merge_kernel<<<grid, kThreads, 0, stream>>>(a);

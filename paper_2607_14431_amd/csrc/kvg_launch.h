@@ -8,6 +8,10 @@
 
 namespace kvg {
 
+// A launch of `wgs` workgroups of `threads` threads fits the dispatch limits (grid size in
+// threads below 2^32).
+inline bool fits_grid(int64_t wgs, int threads) { return wgs >= 0 && wgs * (int64_t)threads <= (int64_t)UINT32_MAX; }
+
 // `dtype` is the cache's storage dtype code (kDtypeF32, kDtypeBf16, kDtypeFp8).
 hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t stream);
 hipError_t launch_deposit(const CopyArgs& a, hipStream_t stream);

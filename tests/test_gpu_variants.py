@@ -221,3 +221,35 @@ def test_decode_workspace_serves_windowed_caches():
             sizes = [kvg.kvg_decode_workspace_bytes(kvg.Cache.allocate(layers, 1, 4, 2, 64, dtype, windows=w), seqs, layers)
                      for w in (None, tuple(0 if (i + 1) % 6 == 0 else 1024 for i in range(layers)))]
             assert sizes[0] == sizes[1] > 0
+
+
+def test_decode_merge_grid_of_many_rows():
+    """More rows (layers x sequences x query heads) than fit a grid of 1,024-lane workgroups, over more
+    than 16 splits: the call runs, and a slice of its layers on its own gives the same bytes."""
+    import torch
+
+    from paper_2607_14431_amd import kvg
+    L, Hq, Hkv, D, ctx, max_ctx = 1 << 19, 8, 1, 64, 700, 8192
+    assert L * Hq * 1024 > 2 ** 32 - 1 >= L * Hq * 256
+    g = torch.Generator(device="cuda").manual_seed(3)
+    cache = kvg.Cache.allocate(L, 2, Hq, Hkv, D, torch.bfloat16)
+    for pool in (cache.k_pool, cache.v_pool):
+        pool.normal_(generator=g)
+    # the new token's page is no other key's
+    table = torch.zeros((1, max_ctx // 16 + 1), dtype=torch.int32, device="cuda")
+    table[0, ctx // 16] = 1
+    seqs = kvg.Seqs(table, torch.tensor([ctx], dtype=torch.int32, device="cuda"),
+                    torch.zeros(1, dtype=torch.int64, device="cuda"), max_ctx)
+    q, k, v = (torch.randn((L, 1, 1, h, D), generator=g, device="cuda", dtype=torch.bfloat16) for h in (Hq, Hkv, Hkv))
+
+    def decode(l0, n):
+        out = torch.full((n, 1, 1, Hq, D), float("nan"), device="cuda")
+        ws = kvg.decode_workspace(cache, seqs, n)
+        s = slice(l0, l0 + n)
+        kvg.kvg_decode_attn(cache, seqs, kvg.rope(), l0, n, q[s], k[s], v[s], D ** -0.5, out, ws)
+        return out
+
+    together = decode(0, L)
+    assert torch.isfinite(together).all()
+    for l0 in (0, L // 2 - 1, L - 2):
+        assert torch.equal(decode(l0, 2), together[l0:l0 + 2])
