@@ -394,7 +394,7 @@ int kvg_logits(const float* hidden_dev, int32_t rows, int32_t hidden, const uint
 /* Per row r of two logit sets a, b (fp32 [rows][vocab], device): kl_dev[r] =
  * KL(softmax(a_r) || softmax(b_r)) in fp64 (fixed-order sums: byte-equal rows give exactly
  * 0), argmax_a_dev[r] / argmax_b_dev[r] = the first index of each row's maximum (int32).
- * All outputs device.  Errors: KVG_E_INVAL, KVG_E_HIP. */
+ * All outputs device.  Errors: KVG_E_INVAL, KVG_E_SHAPE (2^24 rows or more), KVG_E_HIP. */
 int kvg_logit_compare(const float* a_dev, const float* b_dev, int32_t rows, int32_t vocab, double* kl_dev,
                       int32_t* argmax_a_dev, int32_t* argmax_b_dev, void* stream);
 

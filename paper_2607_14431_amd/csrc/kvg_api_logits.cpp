@@ -73,6 +73,7 @@ int kvg_logit_compare(const float* a_dev, const float* b_dev, int32_t rows, int3
   if (a_dev == nullptr || b_dev == nullptr || kl_dev == nullptr || argmax_a_dev == nullptr ||
       argmax_b_dev == nullptr || rows <= 0 || vocab <= 0)
     return KVG_E_INVAL;
+  if (rows > kvg::kMaxCompareRows) return KVG_E_SHAPE;
   kvg::CompareArgs c;
   c.a = a_dev;
   c.b = b_dev;

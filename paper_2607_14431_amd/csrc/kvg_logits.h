@@ -39,6 +39,9 @@ struct PackArgs {
   int32_t V, H;
 };
 
+// Rows of one comparison at most (as many as fitted one launch of 256 lanes a row).
+constexpr int32_t kMaxCompareRows = (1 << 24) - 1;
+
 struct CompareArgs {
   const float* a;            // [rows][V] fp32
   const float* b;            // [rows][V] fp32

@@ -25,6 +25,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 namespace kvg {
 
 namespace {
@@ -360,13 +362,26 @@ hipError_t launch_logits_pack(const PackArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_logit_compare(const CompareArgs& c, hipStream_t stream) {
-  const bool vec = c.V % 4 == 0 && reinterpret_cast<uintptr_t>(c.a) % 16 == 0 && reinterpret_cast<uintptr_t>(c.b) % 16 == 0;
-  if (vec)
-    logit_compare_kernel<true><<<dim3((unsigned)c.rows), kCompareThreads, 0, stream>>>(c);
-  else
-    logit_compare_kernel<false><<<dim3((unsigned)c.rows), kCompareThreads, 0, stream>>>(c);
-  return hipGetLastError();
+hipError_t launch_logit_compare(const CompareArgs& call, hipStream_t stream) {
+  constexpr int32_t kRows = 1 << 20;             // of a launch: 2^30 threads
+  const bool vec = call.V % 4 == 0 && reinterpret_cast<uintptr_t>(call.a) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(call.b) % 16 == 0;
+  CompareArgs c = call;
+  for (int32_t row = 0; row < call.rows; row += kRows) {
+    c.rows = std::min(call.rows - row, kRows);
+    if (vec)
+      logit_compare_kernel<true><<<dim3((unsigned)c.rows), kCompareThreads, 0, stream>>>(c);
+    else
+      logit_compare_kernel<false><<<dim3((unsigned)c.rows), kCompareThreads, 0, stream>>>(c);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    c.a += (int64_t)kRows * c.V;
+    c.b += (int64_t)kRows * c.V;
+    c.kl += kRows;
+    c.arg_a += kRows;
+    c.arg_b += kRows;
+  }
+  return hipSuccess;
 }
 
 }  // namespace kvg

@@ -235,6 +235,7 @@ def test_logits_validation():
         return kvg.raw_call("kvg_logit_compare", P(a), P(b), rows, V, P(kl), P(ia), P(ib), None)
     assert cmp(a=0) == -1 and cmp(b=0) == -1 and cmp(kl=0) == -1 and cmp(ia=0) == -1 and cmp(ib=0) == -1
     assert cmp(rows=0) == -1 and cmp(V=-5) == -1
+    assert cmp(rows=1 << 24) == -2
 
 
 def test_prefill_workspace_with_shared_pages():

@@ -253,3 +253,21 @@ def test_decode_merge_grid_of_many_rows():
     assert torch.isfinite(together).all()
     for l0 in (0, L // 2 - 1, L - 2):
         assert torch.equal(decode(l0, 2), together[l0:l0 + 2])
+
+
+def test_logit_compare_of_many_rows():
+    """More rows than fit a grid of 1,024-lane workgroups (2^22 of them): every row is compared."""
+    import torch
+
+    from paper_2607_14431_amd import kvg
+    rows, V = (1 << 22) + 3, 2
+    a = torch.randn((rows, V), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    b = a.flip(1).contiguous()
+    kl = torch.full((rows,), float("nan"), dtype=torch.float64, device="cuda")
+    ia, ib = (torch.full((rows,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    kvg.kvg_logit_compare(a, b, kl, ia, ib)
+    d = a[:, 0].double() - a[:, 1].double()
+    want = torch.tanh(d / 2) * d                     # two logits exchanged: (p0 - p1) (a0 - a1)
+    # a handful of fp64 roundings (1.1e-16) of terms below |a| + |b| + 1 < 20
+    assert torch.allclose(kl, want, rtol=0, atol=1e-13)
+    assert torch.equal(ia.long(), a.argmax(1)) and torch.equal(ib.long(), b.argmax(1))
