@@ -560,6 +560,35 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
   if (n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;     // written by the split kernel
   const float* ml = a.part_ml + row_head * a.n_split_max * 2;
   const float* acc = a.part_acc + row_head * a.n_split_max * a.D;
+  constexpr int kLdsSplits = 2048;
+  if (n_split <= kLdsSplits) {
+    // Many splits of many rows: the (reference, sum) pairs are staged in LDS by the whole workgroup in
+    // one round trip, and each lane requests 16 splits' values at a time; the arithmetic and its
+    // order are combine_splits' own.
+    __shared__ float s_ml[2 * kLdsSplits];
+    for (int t = threadIdx.x; t < 2 * n_split; t += kThreads) s_ml[t] = ml[t];
+    __syncthreads();
+    float m = -INFINITY;
+    for (int s = 0; s < n_split; ++s) m = fmaxf(m, s_ml[2 * s]);
+    for (int d = threadIdx.x; d < a.D; d += kThreads) {
+      float lsum = 0.0f, o = 0.0f;
+      for (int s0 = 0; s0 < n_split; s0 += U) {
+        float av[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) av[u] = acc[min(s0 + u, n_split - 1) * a.D + d];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int s = min(s0 + u, n_split - 1);
+          const float f = merge_factor(s_ml[2 * s], m);
+          const bool in = s0 + u < n_split;
+          lsum = in ? fmaf(s_ml[2 * s + 1], f, lsum) : lsum;
+          o = in ? fmaf(av[u], f, o) : o;
+        }
+      }
+      a.out[row_head * a.D + d] = o / lsum;
+    }
+    return;
+  }
   for (int d = threadIdx.x; d < a.D; d += kThreads)
     a.out[row_head * a.D + d] = combine_splits(ml, acc + d, a.D, n_split);
 }
@@ -568,8 +597,7 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
 // units of a split merged in order, then the splits in ascending order, combine_splits' own
 // arithmetic.  A workgroup per (layer, sequence, query head): the splits' (reference, sum) pairs
 // and weights are worked out once, in LDS; the lane groups then bring kMergeChunk splits' values
-// at a time (every partial requested at once), and one lane per element sums them in order.  256
-// rows of 66 splits took 15 us on one group of lanes, 11 us here.
+// at a time (every partial requested at once), and one lane per element sums them in order.
 constexpr int kMergeThreads = 1024;
 constexpr int kMergeChunk = 32;
 template <bool kSolo>
@@ -670,7 +698,13 @@ __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const Decod
   if (gi == 0) a.out[row_head * D + d] = o / lsum;
 }
 
-// Bytes of LDS merge_splits_kernel takes; a decode with more splits than fit combines without it.
+// merge_splits_kernel<false> serves rows that leave lanes idle: up to two workgroups on each of the 256 CUs.
+// Above, a row's 256 lanes are enough and most of its 1,024 only wait.  16 query heads x 256, over 66 splits: 256 rows
+// 10.2 us against 11.8 on 256 lanes, 512 rows 12.4 against 13.0, 1,024 rows 22.5 against 17.1, 24,576 rows 654 against 313;
+// over 18 splits: 5.2 / 6.3, 6.3 / 6.6, 11.0 / 8.6.  More splits than fit its LDS combine on 256 lanes too.
+constexpr int64_t kMergeRows = 512;
+constexpr size_t kMergeLds = 65536 - 256;      // dynamic: its static arrays and this stay within 64 KiB
+// Bytes of dynamic LDS it takes.
 size_t merge_lds(const DecodeArgs& a) {
   return ((size_t)a.n_split_max * (a.solo ? 8 : 2) + (size_t)kMergeChunk * a.D) * sizeof(float);
 }
@@ -758,7 +792,7 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream) {
   const dim3 grid((unsigned)n_rows);
   if (a.solo)
     merge_splits_kernel<true><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
-  else if (a.n_split_max > 16 && merge_lds(a) <= 65536 && fits_grid(n_rows, kMergeThreads))   // the host checked 256 threads a row
+  else if (a.n_split_max > 16 && merge_lds(a) <= kMergeLds && n_rows <= kMergeRows)
     merge_splits_kernel<false><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
   else
     decode_merge_kernel<<<grid, kThreads, 0, stream>>>(a);

@@ -271,3 +271,43 @@ def test_logit_compare_of_many_rows():
     # a handful of fp64 roundings (1.1e-16) of terms below |a| + |b| + 1 < 20
     assert torch.allclose(kl, want, rtol=0, atol=1e-13)
     assert torch.equal(ia.long(), a.argmax(1)) and torch.equal(ib.long(), b.argmax(1))
+
+
+# The merges of a decode's splits: up to 512 rows (sequences x query heads) and more of them over more than
+# 16 splits, at most 16 splits, and units (one sequence alone; not fp32).  Same bytes.
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp8", 128), ("bf16", 256), ("f32", 64), ("f32", 256)])
+def test_decode_merges_agree(dtype, D):
+    import torch
+
+    from gpu_helpers import TORCH_DTYPE
+    from paper_2607_14431_amd import kvg
+    Hq, Hkv, B, long = 32, 4, 20, 9000
+    ctxs = [[8100, 511, 512, 1100, 5][b % 5] for b in range(B - 1)] + [long]
+    per_seq = long // 16 + 1
+    g = torch.Generator(device="cuda").manual_seed(D)
+    cache = kvg.Cache.allocate(1, B * per_seq, Hq, Hkv, D, TORCH_DTYPE[dtype])
+    for pool in (cache.k_pool, cache.v_pool):
+        pool.copy_((torch.randn(pool.shape, generator=g, device="cuda") * 0.5).to(pool.dtype))
+    tables = torch.randperm(B * per_seq, generator=g, device="cuda").to(torch.int32).view(B, per_seq)
+    lens = torch.tensor(ctxs, dtype=torch.int32, device="cuda")
+    start = torch.arange(B, device="cuda") * 100
+    raw = [torch.randn((1, B, 1, h, D), generator=g, device="cuda").to(cache.raw_dtype) for h in (Hq, Hkv, Hkv)]
+
+    def decode(rows):
+        max_ctx = max(ctxs[b] for b in rows)
+        seqs = kvg.Seqs(tables[rows].contiguous(), lens[rows].contiguous(), start[rows].contiguous(), max_ctx)
+        out = torch.full((1, len(rows), 1, Hq, D), float("nan"), device="cuda")
+        ws = kvg.decode_workspace(cache, seqs, 1)
+        kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, 1, *(t[:, rows].contiguous() for t in raw), D ** -0.5, out, ws)
+        return out, len(rows) * Hq, (max_ctx + 512) // 512
+
+    every = list(range(B))
+    together, rows, splits = decode(every)
+    assert torch.isfinite(together).all() and rows > 512 and splits > 16
+    some, few_splits = every[10:], every[:10]
+    for part, want in ((some, lambda r, s: r <= 512 and s > 16 and len(some) * Hkv * s * 4 > 1280),
+                       (few_splits, lambda r, s: s <= 16 and len(few_splits) * Hkv * s * 4 > 1280),
+                       ([3], lambda r, s: Hkv * s * 4 <= 1280), ([B - 1], lambda r, s: Hkv * s * 4 <= 1280)):
+        out, r, s = decode(part)
+        assert want(r, s)
+        assert torch.equal(out.view(torch.int32), together[:, part].view(torch.int32)), part
