@@ -285,7 +285,8 @@ size_t kvg_decode_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs, 
  * (the last W of them in a layer with window W; ranges entirely before the window are
  * skipped).
  * Grouped-query split-K over fixed 512-token ranges of logical index (in a windowed layer
- * counted from the page of the first visible key): each range yields a partial (reference
+ * as many as the visible keys fill, from the first visible key on, or from its page on with the last
+ * range up to 15 tokens longer): each range yields a partial (reference
  * max, sum, weighted V) in fp32 and the partials are combined in ascending range order, so the
  * bytes depend neither on the batch nor on which path filled the cache.  bf16 and fp8 caches
  * take a range as four units of 128 tokens, each a softmax state of its own on MFMA, merged in

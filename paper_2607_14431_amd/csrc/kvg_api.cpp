@@ -226,7 +226,7 @@ int shared_splits(const kvg_cache* c, const kvg_seqs* s) {
 
 // The layers and splits of a decode's grid (DecodeArgs): every split of full-attention layers, less the
 // shared ones (the shared-split kernel's), and of windowed layers as many as the longest of
-// their windows can touch from the page of its first key on.
+// their windows has.
 struct DecodeGrid {
   int n_full = 0, n_split_full = 0, n_split_win = 0;
   uint8_t order[kvg::kMaxWindowLayers] = {};
@@ -242,7 +242,7 @@ DecodeGrid decode_grid(const kvg_cache* c, const kvg_seqs* s, int32_t layer0, in
     if (window(l) == 0)
       ++d.n_full;
     else
-      d.n_split_win = std::max<int64_t>(d.n_split_win, std::min<int64_t>(n_split, (window(l) + kPage - 1 + kSplit - 1) / kSplit));
+      d.n_split_win = std::max<int64_t>(d.n_split_win, std::min<int64_t>(n_split, (window(l) + kSplit - 1) / kSplit));
   if (d.n_full != n_layers) {                 // windows: at most kMaxWindowLayers layers (checked)
     int full = 0, windowed = d.n_full;
     for (int l = 0; l < n_layers && l < kvg::kMaxWindowLayers; ++l) d.order[window(l) == 0 ? full++ : windowed++] = (uint8_t)l;
@@ -255,7 +255,7 @@ DecodeGrid decode_grid(const kvg_cache* c, const kvg_seqs* s, int32_t layer0, in
 // instead of every split: as long as the waves of all units are resident at once, five on each of 256
 // CUs.  One 12B-class layer over 4.6k keys (72 splits): 36 us with a wave per split, 20 with a
 // wave per unit; 4 sequences (296): 43 and 41; 8 (592): 56 and 63.  A windowed layer's
-// splits are those its window can touch.
+// splits are those its window has.
 constexpr int kSoloWaves = 5 * 256;
 bool decode_solo(const kvg_cache* c, const kvg_seqs* s, const DecodeGrid& grid) {
   return c->dtype != KVG_F32 && shared_splits(c, s) == 0 && grid.items * 4 <= kSoloWaves && n_split_max(s, 1) <= kSoloWaves / 4;
@@ -280,7 +280,7 @@ DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, size
 
 // What the size query returns: enough for a call of this size, and for a wave per unit wherever a
 // call no larger than this one takes it: four partials per split of every row, which with
-// windowed layers (whose rows hold more splits than their windows touch) exceed the resident
+// windowed layers (whose rows hold more splits than their windows have) exceed the resident
 // waves.  The same with and without windows, so one workspace serves caches of one shape.
 size_t decode_ws_bytes(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
   const size_t unit_bytes = (size_t)(c->n_q_heads / c->n_kv_heads) * (c->head_dim + 2) * sizeof(float);

@@ -402,13 +402,13 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
   if (ctx < 0 || ctx > a.max_ctx_len) return;
   const int n_keys = ctx + 1;                     // the new token is key ctx
   const int lo = window_start(win, n_keys);
-  const int base = split_base(lo);
-  const int n_split = split_count(n_keys, base);
+  const int n_split = split_count(n_keys, lo);
   if (s >= n_split) return;
-  const int k0 = base + s * kSplit;               // the split's keys [k0, k1), those below lo masked
+  const int k0 = lo + s * kSplit;                 // the split's keys [k0, k1)
   const int k1 = min(k0 + kSplit, n_keys);
+  const int kb = k0 & ~(kPage - 1);               // teams start at the page holding k0
   const bool last_split = s == n_split - 1;
-  if (win != 0) sp.init(bt, k0 / kPage, a.max_pages, tid & 63);
+  if (win != 0) sp.init(bt, kb / kPage, a.max_pages, tid & 63);
 
   __shared__ float cs[2 * kMaxHalfDim];
   __shared__ uint4 new_k[NCH], new_v[NCH];
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
     const int32_t page = sp.page_of(j);
     const bool valid = page >= 0 && page < a.n_pages;
     rw.lds = j == ctx;
-    rw.ok = rw.lds || (valid && j >= lo);
+    rw.ok = rw.lds || (valid && j >= k0);
     const int64_t roff = (((int64_t)(valid ? page : 0) * a.Hkv + g) * kPage + (j % kPage)) * D;
 #pragma unroll
     for (int i = 0; i < W::CPL; ++i) rw.k[i] = ld16_stream(kpool + roff + (wk.tl + W::TL * i) * W::CH);
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
       for (int j = 0; j < W::CPL; ++j)
         wk.set_q(h, j, storage_chunk<D>(reinterpret_cast<const float*>(raw_q) + h * D, wk.q_chunk(j), true, a.pairing, cs));
   };
-  wk.run(k0, k1, a.scale_log2, load, prologue);
+  wk.run(kb, k1, a.scale_log2, load, prologue);
 
   wk.to_lds(s_acc, s_ml);
   __syncthreads();
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
     const int ctx = a.ctx_lens[b];
     if (ctx < 0 || ctx > a.max_ctx_len) return;
     const int win = layer_window(a, l);
-    const int n_split = split_count(ctx + 1, split_base(window_start(win, ctx + 1)));
+    const int n_split = split_count(ctx + 1, window_start(win, ctx + 1));
     if (n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;   // written by the split kernel
     float m = -INFINITY;
 #pragma unroll
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
   const int ctx = a.ctx_lens[b];
   if (ctx < 0 || ctx > a.max_ctx_len) return;
   const int win = layer_window(a, l);
-  const int n_split = split_count(ctx + 1, split_base(window_start(win, ctx + 1)));
+  const int n_split = split_count(ctx + 1, window_start(win, ctx + 1));
   if (n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;     // written by the split kernel
   const float* ml = a.part_ml + row_head * a.n_split_max * 2;
   const float* acc = a.part_acc + row_head * a.n_split_max * a.D;
@@ -614,10 +614,10 @@ __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const Decod
   const int ctx = a.ctx_lens[b];
   if (ctx < 0 || ctx > a.max_ctx_len) return;
   const int win = layer_window(a, l);
-  const int base = split_base(window_start(win, ctx + 1));
-  const int n_split = split_count(ctx + 1, base);
+  const int lo = window_start(win, ctx + 1);
+  const int n_split = split_count(ctx + 1, lo);
   if (!kSolo && n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;   // written by the split kernel
-  const int n_unit = (ctx - base) / kUnit + 1;             // units that hold keys (kSolo)
+  const int n_unit = min((ctx - split_base(lo)) / kUnit + 1, 4 * n_split);   // units that hold keys (kSolo)
   if (kSolo && n_unit == 1) return;                        // written by the split kernel
   extern __shared__ float s_mem[];
   float* s_m = s_mem;                                      // [split] reference, then weight

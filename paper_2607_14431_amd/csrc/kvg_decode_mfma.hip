@@ -1,9 +1,9 @@
 // Decode attention of bf16 and fp8 caches on MFMA: one new token per sequence, split over keys.
 //
 // Work item = (layer, sequence, KV head g, split s of kSplit = 512 keys), one wave each.  The
-// split is four units of 128 keys; each unit starts from an empty softmax state, and the units of a
-// split are merged in order.  Splits are combined in ascending order by the merge kernels.
-// Everything is a function of the row's own length and window, so a sequence's bytes depend neither
+// split is four units of 128 keys (a window's last one up to 15 keys longer: split_base); each unit
+// starts from an empty softmax state, and the units of a split are merged in order.  Splits are
+// combined in ascending order by the merge kernels.  Everything is a function of the row's own length and window, so a sequence's bytes depend neither
 // on its batch nor on the pages' places.
 //
 // What bounds it: HBM, when the launch fills the chip.  Keys and values go from the pages straight
@@ -185,13 +185,14 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   const int n_keys = ctx + 1;                        // the new token is key ctx
   const int lo = window_start(win, n_keys);
   const int base = split_base(lo);
-  const int n_split = split_count(n_keys, base);
+  const int n_split = split_count(n_keys, lo);
   if (s >= n_split) return;
   const int k0 = base + s * kSplit + unit0 * kUnit;  // this wave's keys [k0, k1), page aligned
-  const int k1 = min(kSolo ? k0 + kUnit : k0 + kSplit, n_keys);
+  const bool to_end = s == n_split - 1 && (!kSolo || unit0 == 3);   // the last unit takes what is left
+  const int k1 = to_end ? n_keys : min(kSolo ? k0 + kUnit : k0 + kSplit, n_keys);
   if (kSolo && k0 >= k1) return;                     // an empty unit (never read)
   const int n_stages = (k1 - k0 + SK - 1) / SK;
-  if (win != 0) pg = bt[min(k0 / kPage + lane, a.max_pages - 1)];   // a split is at most 32 pages
+  if (win != 0) pg = bt[min(k0 / kPage + lane, a.max_pages - 1)];   // a split is at most 33 pages
   const bool has_new = ctx < k1;                     // this wave owns the new token
 
   const int64_t lbase = (int64_t)(a.layer0 + l) * a.layer_elems;
@@ -438,7 +439,7 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
     asm volatile("" ::: "memory");
     issue(st, i + kStages);
     if constexpr (!kSolo) {
-      if ((i + 1) % kUnitStages == 0 || i + 1 == n_stages) {   // end of a unit
+      if (((i + 1) % kUnitStages == 0 && i + 1 < 4 * kUnitStages) || i + 1 == n_stages) {   // end of a unit
         const float lu = sum_over_groups(lsum);
         if (i < kUnitStages) {
           m_run = m;

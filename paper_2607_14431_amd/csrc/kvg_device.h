@@ -181,7 +181,7 @@ struct DecodeArgs {
   int32_t n_shared_split;     // splits [0, n) of full-attention layers come from the shared-split kernel
   // The grid: n_full full-attention layers with n_split_full splits per (sequence, KV head) (item i is
   // split n_shared_split + i), then the windowed layers with n_split_win, as many as any of their
-  // windows can touch.  layer_order: the launch's layers in that order (only read when some
+  // windows has.  layer_order: the launch's layers in that order (only read when some
   // are windowed).
   int32_t n_full, n_split_full, n_split_win;
   uint8_t layer_order[kMaxWindowLayers];
@@ -248,10 +248,11 @@ __device__ __forceinline__ int window_start(int W, int n_keys) {
   return W > 0 && n_keys > W ? n_keys - W : 0;
 }
 
-// Split-K plan of a row that sees keys [lo, n_keys): splits of kSplit keys from lo on
-// (split s = keys [lo + kSplit s, lo + kSplit (s + 1))), a function of the row's own
-// length and window only.  Full attention (lo = 0) splits at multiples of kSplit.
-// The decode's splits start at the page of the first visible key, so that whole pages are read.
+// Split-K plan of a row that sees keys [lo, n_keys): as many splits as kSplit-key ranges counted from
+// lo on, a function of the row's own length and window only.  Full attention (lo = 0) splits at
+// multiples of kSplit.  The fp32 decode's split s is keys [lo + kSplit s, lo + kSplit (s + 1)); the MFMA
+// decode's starts at split_base(lo) + kSplit s, so that whole pages are read, and its last split runs to
+// n_keys, up to kPage - 1 keys more: a further split for those would be a wave of a few keys.
 __device__ __forceinline__ int split_base(int lo) { return lo & ~(kPage - 1); }
 __device__ __forceinline__ int split_count(int n_keys, int lo) { return (n_keys - lo + kSplit - 1) / kSplit; }
 

@@ -133,6 +133,13 @@ DECODE_CASES = [
     ("fp8", 256, 8, 1, [129, 1030], 2, (0, 128)),
     ("fp8", 128, 4, 1, [255, 31], 2, (0, 17)),
     ("fp8", 64, 16, 2, [639, 383], 2, (0, 600)),
+    # windows of whole splits that start inside a page: the last unit holds up to 143 keys
+    ("bf16", 256, 2, 1, [520, 1037, 1200], 3, (1024, 512)),
+    ("bf16", 64, 4, 2, [1039, 523], 2, (512, 1024)),
+    ("bf16", 128, 8, 1, [1036], 2, (512, 128)),
+    ("fp8", 256, 4, 2, [1550, 527], 2, (1536, 512)),
+    ("fp8", 64, 8, 1, [1033, 1023], 2, (512, 1024)),
+    ("f32", 64, 4, 2, [1033, 700], 2, (512, 513)),
 ]
 
 
