@@ -291,9 +291,10 @@ size_t kvg_decode_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs, 
  * bytes depend neither on the batch nor on which path filled the cache.  bf16 and fp8 caches
  * take a range as four units of 128 tokens, each a softmax state of its own on MFMA, merged in
  * order; they hold the rotated query and the softmax weights as bf16 high and low parts (each
- * score and each weighted sum is the sum of both products); fp32 caches use fp32 vector arithmetic.  Two launches: the
- * split kernel (which also rotates the queries and appends the new token) and the combine
- * kernel.  Layouts as kvg_prefill_attn with chunk_len = 1.
+ * score and each weighted sum is the sum of both products; the weights of a row of at most 64 keys
+ * have a third part, which makes them exact); fp32 caches use fp32 vector arithmetic.  Two
+ * launches: the split kernel (which also rotates the queries and appends the new token) and the
+ * combine kernel.  Layouts as kvg_prefill_attn with chunk_len = 1.
  * ws_dev: kvg_decode_workspace_bytes() bytes of scratch (contents undefined after the call).
  * Errors: as kvg_prefill_attn. */
 int kvg_decode_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope,

@@ -35,6 +35,7 @@ namespace kvg {
 namespace {
 
 constexpr int kStageBytes = 16384;     // K and V of one stage
+constexpr int kFewKeys = 64;           // rows of at most so many keys take exact weights
 constexpr int kStream = 2;             // buffer load policy: nontemporal (every row is read once)
 constexpr int kLgkmWait = 0xC07F;      // s_waitcnt operand: lgkmcnt(0) alone
 // s_waitcnt operand that waits for vmcnt <= n alone (gfx9 encoding: bits 3:0 and 15:14)
@@ -332,7 +333,36 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   auto unit_o = [&](int d) -> f32x4 {
     return (f32x4){add_ror8(o[d][0]), add_ror8(o[d][1]), add_ror8(o[d][2]), add_ror8(o[d][3])};
   };
-  auto stage = [&](auto st, int i) {
+  // O^T += V^T P^T over the keys of a stage's block
+  auto add_values = [&](const lds_char* lds, int blk, const uint32_t (&pw)[2 * NTL]) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+      const uint32_t row = blk * BK * RB;
+      if constexpr (kFp8) {
+        const i32x2 x = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(lds + row + (v_lane ^ (uint32_t)(16 * d))));
+        o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(widen_fp8x8((uint32_t)x.x, (uint32_t)x.y)),
+                                                       as_bf16x8(make_uint4(pw[0], pw[1], pw[2], pw[3])), o[d], 0, 0, 0);
+      } else {
+        const uint32_t at = row + (v_lane ^ (uint32_t)(32 * d));
+        const i16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds + at));
+        if constexpr (NTL == 2) {
+          const i16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds + at + 16 * RB));
+          const uint2 u0 = __builtin_bit_cast(uint2, x0), u1 = __builtin_bit_cast(uint2, x1);
+          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(make_uint4(u0.x, u0.y, u1.x, u1.y)),
+                                                         as_bf16x8(make_uint4(pw[0], pw[1], pw[2], pw[3])), o[d], 0, 0, 0);
+        } else {
+          const i16x4 p = __builtin_bit_cast(i16x4, make_uint2(pw[0], pw[1]));
+          o[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x0, p, o[d], 0, 0, 0);
+        }
+      }
+    }
+  };
+  // kFew, a row of a few keys: no rounding but the queries' is left in its result.  Scores are scaled before the
+  // reference is taken from them (the largest weight is exactly 1) and the weights keep a third part,
+  // which makes them exact: 16 keys 3.1e-6 -> 2.9e-6 off the 64-bit result, a single key's value as it is.
+  // A copy of the loop, because the tests in it cost the others 6% (fp8 at head_dim 256).
+  auto stage = [&](auto st, int i, auto few) {
+    constexpr bool kFew = decltype(few)::value;
     // stage i has landed: the loads of the kStages - 1 later ones may be in flight
     __builtin_amdgcn_s_waitcnt(vm_wait((kStages - 1) * kLoads));
     asm volatile("" ::: "memory");
@@ -383,12 +413,17 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
             sc[t][e] = (key >= lo && key < k1) ? sc[t][e] : -INFINITY;
           }
       }
+      if constexpr (kFew) {
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) sc[t] *= a.scale_log2;
+      }
+      const float scale = kFew ? 1.0f : a.scale_log2;
       float mx = -INFINITY;
 #pragma unroll
       for (int t = 0; t < NTL; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[t][e]);
-      const float mx2 = max_over_groups(mx) * a.scale_log2;
+      const float mx2 = max_over_groups(mx) * scale;
       const bool raised = mx2 > m;
       if (__builtin_amdgcn_ballot_w64(raised) != 0) {
         const float alpha = raised ? __builtin_amdgcn_exp2f(m - mx2) : 1.0f;
@@ -404,34 +439,32 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
       for (int t = 0; t < NTL; ++t)
 #pragma unroll
         for (int e = 0; e < 4; e += 2) {
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[t][e], a.scale_log2, -m_ref));
-          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[t][e + 1], a.scale_log2, -m_ref));
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[t][e], scale, -m_ref));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[t][e + 1], scale, -m_ref));
           lsum += p0;
           lsum += p1;
+          if constexpr (kFew) {
+            sc[t][e] = p0;
+            sc[t][e + 1] = p1;
+          }
           const bf16x2 h = __builtin_convertvector((f32x2){p0, p1}, bf16x2);
           const uint32_t lw = pack_bf16_rne(p0 - (float)h.x, p1 - (float)h.y);
           pw[2 * t + e / 2] = is_lo ? lw : __builtin_bit_cast(uint32_t, h);
         }
+      add_values(lds, blk, pw);
+      if constexpr (kFew) {
+        // what hi and lo leave of a weight, exactly (columns 0-7)
 #pragma unroll
-      for (int d = 0; d < ND; ++d) {
-        const uint32_t row = blk * BK * RB;
-        if constexpr (kFp8) {
-          const i32x2 x = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2*)(lds + row + (v_lane ^ (uint32_t)(16 * d))));
-          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(widen_fp8x8((uint32_t)x.x, (uint32_t)x.y)),
-                                                         as_bf16x8(make_uint4(pw[0], pw[1], pw[2], pw[3])), o[d], 0, 0, 0);
-        } else {
-          const uint32_t at = row + (v_lane ^ (uint32_t)(32 * d));
-          const i16x4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds + at));
-          if constexpr (NTL == 2) {
-            const i16x4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(lds + at + 16 * RB));
-            const uint2 u0 = __builtin_bit_cast(uint2, x0), u1 = __builtin_bit_cast(uint2, x1);
-            o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(make_uint4(u0.x, u0.y, u1.x, u1.y)),
-                                                           as_bf16x8(make_uint4(pw[0], pw[1], pw[2], pw[3])), o[d], 0, 0, 0);
-          } else {
-            const i16x4 p = __builtin_bit_cast(i16x4, make_uint2(pw[0], pw[1]));
-            o[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x0, p, o[d], 0, 0, 0);
+        for (int t = 0; t < NTL; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; e += 2) {
+            const float p0 = sc[t][e], p1 = sc[t][e + 1];
+            const bf16x2 h = __builtin_convertvector((f32x2){p0, p1}, bf16x2);
+            const float r0 = p0 - (float)h.x, r1 = p1 - (float)h.y;
+            const bf16x2 lw = __builtin_convertvector((f32x2){r0, r1}, bf16x2);
+            pw[2 * t + e / 2] = is_lo ? 0u : pack_bf16_rne(r0 - (float)lw.x, r1 - (float)lw.y);
           }
-        }
+        add_values(lds, blk, pw);
       }
     }
     // the stage's reads have returned: its memory takes stage i + kStages
@@ -466,13 +499,19 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
       }
     }
   };
-  for (int i = 0; i < n_stages; i += kStages) {
-    stage(S0{}, i);
-    if (i + 1 < n_stages) stage(S1{}, i + 1);
-    if constexpr (kStages > 2) {
-      if (i + 2 < n_stages) stage(S2{}, i + 2);
+  auto walk = [&](auto few) {
+    for (int i = 0; i < n_stages; i += kStages) {
+      stage(S0{}, i, few);
+      if (i + 1 < n_stages) stage(S1{}, i + 1, few);
+      if constexpr (kStages > 2) {
+        if (i + 2 < n_stages) stage(S2{}, i + 2, few);
+      }
     }
-  }
+  };
+  if (n_keys - lo <= kFewKeys)
+    walk(std::true_type{});
+  else
+    walk(std::false_type{});
 
   // the empty loads past the last stage write LDS too: none may outlive the wave
   __builtin_amdgcn_s_waitcnt(vm_wait(0));
