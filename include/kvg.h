@@ -262,8 +262,10 @@ size_t kvg_prefill_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs,
  * with fp32 softmax and accumulation (j > n - W as well in a layer with window W).
  * bf16 and fp8 caches use bf16 MFMA for Q K^T and P V (each rotated query carried as a bf16
  * high part and a bf16 low part, both multiplied with every key, so a score is as accurate as
- * with the fp32 query; P rounded to bf16; fp8 rows widened to bf16 exactly); fp32 caches use
- * fp32 matrix arithmetic.
+ * with the fp32 query; P rounded to bf16; fp8 rows widened to bf16 exactly).  With 8 query heads per
+ * KV head P keeps a bf16 remainder for the first 64 keys (head_dim 64 in fp8: 256) and in layers
+ * with windows of at most 64 keys (rows of 128 bytes 128, of 64 bytes 256), and is exact for rows of
+ * at most 64 keys.  fp32 caches use fp32 matrix arithmetic.
  * q_raw_dev: [n_layers][batch][chunk_len][n_q_heads][head_dim] of the raw dtype (the cache
  * dtype, bf16 for an fp8 cache), pre-rotation;
  * k_raw_dev, v_raw_dev as kvg_append; out_dev: [n_layers][batch][chunk_len][n_q_heads]

@@ -98,14 +98,17 @@ struct SwzFp8 {
   }
 };
 
+// Windows of at most this many keys of RB bytes are left to a kernel of their own (see `parts`).
+constexpr int prefill_exact_keys(int RB) { return RB >= 256 ? 64 : 64 * 256 / RB; }
+
 // T: cache storage (uint16_t bf16, uint8_t fp8 E4M3).  fp8 tiles are staged as bytes (half the
 // HBM, DMA and LDS traffic) and widened to bf16 fragments exactly before the MFMAs.
 // NW: waves per workgroup (prefill_mfma_waves), 32 query rows each.
-// kTight: 8 query heads per KV head.  Their softmax is the exact variant described at soft_piece,
-// and their keys are cut into segments of kSplit (absolute multiples of 512), a workgroup each,
+// kTight: 8 query heads per KV head (2: layers with windows of at most prefill_exact_keys).  Their
+// softmax is the exact variant described at soft_piece, and their keys are cut into segments of kSplit (absolute multiples of 512), a workgroup each,
 // whose partials prefill_segments_kernel combines: one row over 8k keys takes 33 us, 259 us when
 // a workgroup walks all keys (43 us on the vector path it replaces).
-template <typename T, int D, int NW, bool kShared, bool kTight>
+template <typename T, int D, int NW, bool kShared, int kTight>
 __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs a) {
   constexpr bool kFp8 = sizeof(T) == 1;
   constexpr int RB = D * (int)sizeof(T);   // bytes per cache row
@@ -183,6 +186,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     // row's window are neither loaded nor visited, tiles below this wave's are visited
     // (every wave takes part in the loads) but not computed
     const int W = layer_window(a, l);
+    if (kTight && (kTight == 2) != (W > 0 && W <= prefill_exact_keys(RB))) return;   // the other launch's layer
     kt_begin = window_start(W, ctx + i0 + 1) / kTileKeys;
     // keys below key_lo (the shared pages, whose part came from the shared-split mode) are
     // not visited on full-attention layers; the floor never passes the workgroup's first row
@@ -353,12 +357,20 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
   int32_t pg_next = page_of_tile(kt_begin);
   issue(tile_rsrc(kpool, kt_begin, pg_next), tile_rsrc(vpool, kt_begin, pg_next), Stage0{}, 0, kTileLoads);
   pg_next = page_of_tile(kt_begin + 1);
-  // exact (kTight, the tile of keys 0-63): the weights keep a bf16 remainder too.  A row of a few
-  // keys has no other rounding, and on the vector path, one team per key, its weights were exact:
-  // 3 rows over nothing were 1.4e-6 off the 64-bit result, 3.8e-4 with weights rounded once.
-  auto tile = [&](auto stage, int kt, auto exact) {
+  // parts (kTight): how many bf16 parts a weight keeps.  A row of a few keys has no other rounding, and on the
+  // vector path its weights were exact as long as each of its teams (16, of rows below 256 bytes
+  // 4096 / RB) took one key: 3 rows over nothing are 1.26e-6 off the 64-bit result, 3.8e-4 with weights
+  // rounded once; a window of 16 keys 3.0e-6 against 6.7e-4.  Up to four keys a team that path was the better
+  // one, beyond one rounding is as good.  So two parts in the tiles of the first prefill_exact_keys (one
+  // tile, of 64-byte rows four) and in every tile of windows of at most as many (kTight 2), and for rows of at most
+  // 64 keys, which see no other tiles, a third, which makes the weights exact, and the reference taken from
+  // the scaled scores, so that the largest is 1.
+  constexpr int kExactKeys = RB > 64 ? kTileKeys : prefill_exact_keys(RB);
+  const bool few = kTight && row_n - row_lo < kTileKeys;
+  const float s_scale = few ? a.scale_log2 : 1.0f, p_scale = few ? 1.0f : a.scale_log2;   // exact tiles
+  auto tile = [&](auto stage, int kt, auto parts) __attribute__((always_inline)) {
     constexpr int ST = decltype(stage)::value;
-    constexpr bool kExact = decltype(exact)::value;
+    constexpr bool kExact = decltype(parts)::value > 1, kThird = decltype(parts)::value > 2;
     using Next = std::integral_constant<int, 1 - ST>;
     // vmcnt(0): this wave's share of tile kt (and the next page id) has arrived
     __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -457,19 +469,23 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     // weights there measured 0.5% slower on the 31B-class suffix).
     // Branch-free: exp2(-inf - finite) = 0 for a first raise, and the value of an unraised
     // lane (possibly NaN) is discarded by the select.
-    uint4 pf[4], pl[kExact ? 4 : 1];
+    uint4 pf[4], pl[kExact ? 4 : 1], pt[kThird ? 4 : 1];
     struct SoftState {
       float mx, alpha, m_ref, psum;
       bool raised;
     };
     auto soft_piece = [&](int kb, int j, SoftState& st) {
+      const float scale = kExact ? p_scale : a.scale_log2;
       if (j < 4) {
         if (j == 0) st.mx = -INFINITY;
 #pragma unroll
-        for (int r = 4 * j; r < 4 * j + 4; ++r) st.mx = fmaxf(st.mx, s[kb][r]);
+        for (int r = 4 * j; r < 4 * j + 4; ++r) {
+          if constexpr (kExact) s[kb][r] *= s_scale;
+          st.mx = fmaxf(st.mx, s[kb][r]);
+        }
       } else if (j == 4) {
         const float2 mh = halves32(st.mx);
-        const float mx2 = fmaxf(mh.x, mh.y) * a.scale_log2;
+        const float mx2 = fmaxf(mh.x, mh.y) * scale;
         st.raised = mx2 > m_run + (kTight ? 0.0f : kRescale);
         st.alpha = st.raised ? __builtin_amdgcn_exp2f(m_run - mx2) : 1.0f;
         m_run = st.raised ? mx2 : m_run;
@@ -480,7 +496,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
       } else if (j < 13) {
 #pragma unroll
         for (int r = 2 * (j - 5); r < 2 * (j - 5) + 2; ++r) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], a.scale_log2, -st.m_ref));
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], scale, -st.m_ref));
           s[kb][r] = p;
           if constexpr (!kTight || kExact) st.psum += p;
         }
@@ -500,7 +516,10 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
 #pragma unroll
           for (int w = 0; w < 4; ++w) {
             const bf16x2 h = __builtin_bit_cast(bf16x2, (&f.x)[w]);
-            (&pl[2 * kb + hs].x)[w] = pack_bf16_rne(s[kb][8 * hs + 2 * w] - (float)h.x, s[kb][8 * hs + 2 * w + 1] - (float)h.y);
+            const float x = s[kb][8 * hs + 2 * w] - (float)h.x, y = s[kb][8 * hs + 2 * w + 1] - (float)h.y;
+            const bf16x2 lw = __builtin_convertvector((f32x2){x, y}, bf16x2);
+            (&pl[2 * kb + hs].x)[w] = __builtin_bit_cast(uint32_t, lw);
+            if constexpr (kThird) (&pt[2 * kb + hs].x)[w] = few ? pack_bf16_rne(x - (float)lw.x, y - (float)lw.y) : 0u;
           }
         }
         if constexpr (kTight) {
@@ -587,6 +606,8 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
       o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pf[t / ND]), o[d], 0, 0, 0);
       if constexpr (kExact)
         o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pl[t / ND]), o[d], 0, 0, 0);
+      if constexpr (kThird)
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pt[t / ND]), o[d], 0, 0, 0);
 #pragma unroll
       for (int j = t * kSoftPieces / (2 * ND); j < (t + 1) * kSoftPieces / (2 * ND); ++j) soft_piece(1, j, st1);
       __builtin_amdgcn_sched_barrier(0);
@@ -600,21 +621,34 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
       o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pf[t / ND]), o[d], 0, 0, 0);
       if constexpr (kExact)
         o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pl[t / ND]), o[d], 0, 0, 0);
+      if constexpr (kThird)
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[t % RV]), as_bf16x8(pt[t / ND]), o[d], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  if constexpr (kTight) {
-    if (kt_begin == 0) {
-      tile(Stage0{}, 0, std::true_type{});
-    } else {
-      tile(Stage0{}, kt_begin, std::false_type{});
-    }
-    if (kt_begin + 1 < n_tiles) tile(Stage1{}, kt_begin + 1, std::false_type{});
+  using Parts1 = std::integral_constant<int, 1>;
+  using Parts2 = std::integral_constant<int, 2>;
+  using Parts3 = std::integral_constant<int, 3>;
+  // tile kt in the second and later places of a segment
+  auto step = [&](auto stage, int kt) __attribute__((always_inline)) {
+    if constexpr (kTight == 2)
+      tile(stage, kt, Parts3{});
+    else if constexpr (kTight == 1 && kExactKeys > kTileKeys)
+      kt < kExactKeys / kTileKeys ? tile(stage, kt, Parts2{}) : tile(stage, kt, Parts1{});
+    else
+      tile(stage, kt, Parts1{});
+  };
+  if constexpr (kTight == 1) {
+    if (kt_begin == 0)
+      tile(Stage0{}, 0, Parts3{});
+    else
+      step(Stage0{}, kt_begin);
+    if (kt_begin + 1 < n_tiles) step(Stage1{}, kt_begin + 1);
     kt_begin += 2;
   }
   for (int kt = kt_begin; kt < n_tiles; kt += 2) {
-    tile(Stage0{}, kt, std::false_type{});
-    if (kt + 1 < n_tiles) tile(Stage1{}, kt + 1, std::false_type{});
+    step(Stage0{}, kt);
+    if (kt + 1 < n_tiles) step(Stage1{}, kt + 1);
   }
 
   // ---- shared split: the partial (reference, sum, unnormalised O) of this lane's row in the
@@ -657,7 +691,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
 
 }  // namespace
 
-template <typename T, bool kShared, bool kTight>
+template <typename T, bool kShared, int kTight>
 hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t stream) {
   const int64_t n_wg = kShared ? (int64_t)a.n_layers * a.Hkv * a.n_shared_split * a.n_qt
                                : (int64_t)a.n_layers * a.batch * a.Hkv * prefill_head_sets(a.D, a.group) * a.n_qt *
@@ -682,18 +716,28 @@ int prefill_mfma_waves(int D) { return D <= 128 ? 8 : 4; }
 // per KV head at head_dim 256 take two workgroups of 4 heads.
 int prefill_head_sets(int D, int group) { return std::max(1, group / prefill_mfma_waves(D)); }
 
+// 8 query heads per KV head: the layers with short windows, and the others, in a launch each
+template <typename T>
+hipError_t launch_prefill_tight(const PrefillArgs& a, hipStream_t stream) {
+  int n_short = 0;
+  for (int l = 0; l < std::min<int>(a.n_layers, kMaxWindowLayers); ++l)
+    n_short += a.window[l] > 0 && a.window[l] <= prefill_exact_keys(a.D * (int)sizeof(T));
+  const hipError_t e = n_short > 0 ? launch_prefill_t<T, false, 2>(a, stream) : hipSuccess;
+  return e != hipSuccess || n_short == a.n_layers ? e : launch_prefill_t<T, false, 1>(a, stream);
+}
+
 hipError_t launch_prefill_mfma(const PrefillArgs& a, int dtype, hipStream_t stream) {
   const bool tight = a.group > 4;
   if (dtype == kDtypeBf16)
-    return tight ? launch_prefill_t<uint16_t, false, true>(a, stream) : launch_prefill_t<uint16_t, false, false>(a, stream);
+    return tight ? launch_prefill_tight<uint16_t>(a, stream) : launch_prefill_t<uint16_t, false, 0>(a, stream);
   if (dtype == kDtypeFp8)
-    return tight ? launch_prefill_t<uint8_t, false, true>(a, stream) : launch_prefill_t<uint8_t, false, false>(a, stream);
+    return tight ? launch_prefill_tight<uint8_t>(a, stream) : launch_prefill_t<uint8_t, false, 0>(a, stream);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_shared_splits(const PrefillArgs& a, int dtype, hipStream_t stream) {
-  if (dtype == kDtypeBf16) return launch_prefill_t<uint16_t, true, false>(a, stream);
-  if (dtype == kDtypeFp8) return launch_prefill_t<uint8_t, true, false>(a, stream);
+  if (dtype == kDtypeBf16) return launch_prefill_t<uint16_t, true, 0>(a, stream);
+  if (dtype == kDtypeFp8) return launch_prefill_t<uint8_t, true, 0>(a, stream);
   return hipErrorInvalidValue;
 }
 

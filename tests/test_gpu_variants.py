@@ -323,16 +323,18 @@ def test_decode_merges_agree(dtype, D):
 # Rows of at most 64 keys: the weights are exact in fp32.  Position 0 leaves bf16 queries as they are, so what
 # is left is fp32 arithmetic: a score is off by a few 2^-24 of the sum of its terms' magnitudes (below 8 here), an
 # output by as much relatively; weights of 16 bits alone would leave 2^-18.6 = 2.5e-6.
-@pytest.mark.parametrize("window", [0, 9])
-@pytest.mark.parametrize("dtype,D,Hq,Hkv", [("bf16", 64, 8, 1), ("bf16", 128, 4, 2), ("bf16", 256, 2, 2), ("fp8", 64, 2, 1),
-                                            ("fp8", 256, 8, 1)])
-def test_decode_of_few_keys_has_exact_weights(dtype, D, Hq, Hkv, window):
+@pytest.mark.parametrize("window", [0, 9, 64])
+@pytest.mark.parametrize("call,dtype,D,Hq,Hkv", [
+    ("decode", "bf16", 64, 8, 1), ("decode", "bf16", 128, 4, 2), ("decode", "bf16", 256, 2, 2), ("decode", "fp8", 64, 2, 1),
+    ("decode", "fp8", 256, 8, 1), ("prefill", "bf16", 64, 8, 1), ("prefill", "bf16", 128, 16, 2), ("prefill", "bf16", 256, 8, 1),
+    ("prefill", "fp8", 64, 8, 1), ("prefill", "fp8", 128, 8, 1), ("prefill", "fp8", 256, 8, 1)])
+def test_few_keys_have_exact_weights(call, dtype, D, Hq, Hkv, window):
     import torch
 
     from gpu_helpers import TORCH_DTYPE
     from paper_2607_14431_amd import kvg
-    ctxs = [0, 1, 7, 15, 16, 30, 63]
-    B, per_seq, G = len(ctxs), 4, Hq // Hkv
+    ctxs = [0, 1, 7, 15, 16, 30, 63] + ([64, 73, 127, 200, 600] if window else [])
+    B, per_seq, G = len(ctxs), max(ctxs) // 16 + 1, Hq // Hkv
     g = torch.Generator(device="cuda").manual_seed(D + window)
     cache = kvg.Cache.allocate(1, B * per_seq, Hq, Hkv, D, TORCH_DTYPE[dtype], windows=(window,))
     for pool in (cache.k_pool, cache.v_pool):
@@ -342,8 +344,12 @@ def test_decode_of_few_keys_has_exact_weights(dtype, D, Hq, Hkv, window):
     q, k, v = (torch.randn((1, B, 1, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
     out = torch.full((1, B, 1, Hq, D), float("nan"), device="cuda")
     seqs = kvg.Seqs(tables, lens, -lens.long(), max(ctxs))
-    ws = kvg.decode_workspace(cache, seqs, 1)
-    kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, 1, q, k, v, 3.0 * D ** -0.5, out, ws)
+    if call == "decode":
+        ws = kvg.decode_workspace(cache, seqs, 1)
+        kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, 1, q, k, v, 3.0 * D ** -0.5, out, ws)
+    else:
+        ws = torch.empty(kvg.kvg_prefill_workspace_bytes(cache, seqs, 1, 1), dtype=torch.uint8, device="cuda")
+        kvg.kvg_prefill_attn(cache, seqs, kvg.rope(), 0, 1, 1, q, k, v, 3.0 * D ** -0.5, out, ws)
     for b, n in enumerate(ctxs):
         lo = max(0, n + 1 - window) if window else 0
         rows = [cache.k_pool, cache.v_pool]
