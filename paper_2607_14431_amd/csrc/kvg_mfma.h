@@ -4,6 +4,8 @@
 
 #include "kvg_device.h"
 
+#include <math.h>
+
 namespace kvg {
 
 namespace {
@@ -41,6 +43,18 @@ __device__ __forceinline__ bf16x8 as_bf16x8(const uint4& v) { return __builtin_b
 // two fp32 -> packed bf16, round to nearest even (v_cvt_pk_bf16_f32)
 __device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
+}
+
+// whether every element is a finite number (0 x is 0 for those alone)
+template <int N>
+__device__ __forceinline__ bool all_finite(const f32x16 (&o)[N]) {
+  float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int d = 0; d < N; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r % 4] = fmaf(o[d][r], 0.0f, z[r % 4]);
+  const float sum = (z[0] + z[1]) + (z[2] + z[3]);
+  return sum == 0.0f;
 }
 
 // eight fp8 values (two words) -> eight bf16 values, exactly

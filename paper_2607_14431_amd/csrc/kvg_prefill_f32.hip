@@ -29,6 +29,7 @@
 #include "kvg_mfma.h"
 #include "kvg_rows.h"
 
+#include <float.h>
 #include <math.h>
 
 #include <type_traits>
@@ -138,11 +139,7 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillA
   }
 
   f32x16 o[ND];
-#pragma unroll
-  for (int d = 0; d < ND; ++d)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
-  float m_run = -INFINITY, l_run = 0.0f;
+  float m_run, l_run;
 
   // K rows of block i: lane % 32's row; V rows of block i: key 8 (r / 4) + 4 half + r % 4.  Rows past the
   // range are rows of a page of the pool: K's are masked, V's are replaced by zeros.
@@ -151,8 +148,6 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillA
     return kpool + ((lrow < kPage ? ra : rb) + lrow % kPage) * D + 4 * half;
   };
   FloatVec<4> kf[LK];
-  const float* kp = k_ptr(0);
-  const float* kp_next = kp;
   // Up to head_dim 128 a block's K goes through the wave's own LDS (buffer_load ... lds, 1 KiB of
   // consecutive bytes per load; 16-byte chunks at position chunk ^ (row mod 16)): a lane's 16 bytes of
   // a row straight from L2 took ~90 cycles a load, as long as the MFMAs.  The next block's is
@@ -175,121 +170,168 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillA
       }
     }
   };
-  if (n_blocks > 0) {
-    if constexpr (kStaged) {
-      stage_k(0);
-    } else {
+  auto take_finite = [](FloatVec<NB>& v) {
+    FloatVec<NB> rest;
 #pragma unroll
-      for (int j = 0; j < LK; ++j) kf[j] = __builtin_bit_cast(FloatVec<4>, ld16(kp + 8 * j));
+    for (int d = 0; d < NB; ++d) {
+      const bool ok = fabsf(v.x[d]) <= FLT_MAX;
+      rest.x[d] = ok ? 0.0f : v.x[d];
+      v.x[d] = ok ? v.x[d] : 0.0f;
     }
-  }
-  for (int i = 0; i < n_blocks; ++i) {
-    const int kb = key_begin + 32 * i;
-    kp_next = k_ptr(i + 1);                                    // past the last block: rows never used
-    const int64_t va = page_row(2 * i), vb = page_row(2 * i + 1);
-    const float* vp0 = vpool + (va + 4 * half) * D + ND * lrow;
-    const float* vp1 = vpool + (vb + 4 * half) * D + ND * lrow;
-    FloatVec<NB> vf[LV];
-    auto vfetch = [&](int x) {                                 // step x mod 16 of pass x / 16
-      const int r = x % 16;
-      const float* p = (r < 8 ? vp0 : vp1) + (8 * ((r / 4) & 1) + r % 4) * D + NB * (x / 16);
-      vf[x % LV] = *reinterpret_cast<const FloatVec<NB>*>(p);
-    };
-
-    f32x16 c[4];
+    return rest;
+  };
+  // the values `bad` of keys `key` (lanes 0-31) and key + 4 (lanes 32-63), weighted p, for the rows that see them
+  auto add_seen = [&](f32x16 (&ob)[NB], const FloatVec<NB>& bad, float p, int key) {
+    bool any = false;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int d = 0; d < NB; ++d) any = any || bad.x[d] != 0.0f;
+    if (__builtin_amdgcn_ballot_w64(any) == 0) return;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) c[x][r] = 0.0f;
-    auto kread = [&](int j) -> FloatVec<4> {
-      return __builtin_bit_cast(FloatVec<4>, *reinterpret_cast<const lds_u32x4*>(k_lds + (k_lane ^ (uint32_t)(32 * j))));
-    };
-    if constexpr (kStaged) {
-      __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): the block's K
-      asm volatile("" ::: "memory");
+    for (int hf = 0; hf < 2; ++hf) {
+      const bool sees = key + 4 * hf <= row_n && key + 4 * hf >= row_lo;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) kf[j] = kread(j);
+      for (int d = 0; d < NB; ++d) {
+        const f32x16 t = __builtin_amdgcn_mfma_f32_32x32x2f32(half == hf ? bad.x[d] : 0.0f, p, ob[d], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ob[d][r] = sees ? t[r] : ob[d][r];
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+  };
+  // The wave's blocks.  A masked key weighs 0, and 0 times an Inf or NaN among its values would reach the
+  // rows that do not see it.  Only if a row's result is not finite are the blocks taken again, `careful`: such
+  // values count for the rows that see their key alone.
+  for (bool careful = false;; careful = true) {
+    const float* kp = k_ptr(0);
+    const float* kp_next = kp;
+    m_run = -INFINITY;
+    l_run = 0.0f;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const FloatVec<4> k = kf[j % LK];
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
+    if (n_blocks > 0) {
       if constexpr (kStaged) {
-        if (j + 4 < NJ) kf[(j + 4) % LK] = kread(j + 4);
+        stage_k(0);
       } else {
-        kf[j % LK] = __builtin_bit_cast(FloatVec<4>, ld16((j + LK < NJ ? kp : kp_next) + 8 * ((j + LK) % NJ)));
-      }
-      if (j >= NJ - LV) vfetch(j - (NJ - LV));
-      const FloatVec<4> qj = kStaged ? q[kStaged ? j : 0] : kread(j);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) c[j % 4] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.x[e], qj.x[e], c[j % 4], 0, 0, 0);
-    }
-    kp = kp_next;
-    if constexpr (kStaged) {
-      __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): the reads have returned
-      asm volatile("" ::: "memory");
-      if (i + 1 < n_blocks) stage_k(i + 1);
-    }
-    f32x16 s;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = (c[0][r] + c[1][r]) + (c[2][r] + c[3][r]);
-    if (kb + 31 > ctx + first || kb < mask_lo) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = kb + half * 4 + (r >> 2) * 8 + (r & 3);
-        s[r] = (key <= row_n && key >= row_lo) ? s[r] : -INFINITY;
+        for (int j = 0; j < LK; ++j) kf[j] = __builtin_bit_cast(FloatVec<4>, ld16(kp + 8 * j));
       }
     }
-    float mx = -INFINITY;
+    for (int i = 0; i < n_blocks; ++i) {
+      const int kb = key_begin + 32 * i;
+      kp_next = k_ptr(i + 1);                                    // past the last block: rows never used
+      const int64_t va = page_row(2 * i), vb = page_row(2 * i + 1);
+      const float* vp0 = vpool + (va + 4 * half) * D + ND * lrow;
+      const float* vp1 = vpool + (vb + 4 * half) * D + ND * lrow;
+      FloatVec<NB> vf[LV];
+      auto vfetch = [&](int x) {                                 // step x mod 16 of pass x / 16
+        const int r = x % 16;
+        const float* p = (r < 8 ? vp0 : vp1) + (8 * ((r / 4) & 1) + r % 4) * D + NB * (x / 16);
+        vf[x % LV] = *reinterpret_cast<const FloatVec<NB>*>(p);
+      };
+
+      f32x16 c[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    const float2 mh = halves32(mx);
-    // the block's own state (reference: its largest score), folded into the wave's
-    const float m_blk = fmaxf(mh.x, mh.y) * a.scale_log2;
-    const float m_ref = m_blk == -INFINITY ? 0.0f : m_blk;     // no key seen: every p is 0
-    float psum = 0.0f;
+      for (int x = 0; x < 4; ++x)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      s[r] = __builtin_amdgcn_exp2f(s[r] * a.scale_log2 - m_ref);
-      psum += s[r];
-    }
-    const float2 ph = halves32(psum);
-    const float m_new = fmaxf(m_run, m_blk);
-    const float f_run = merge_factor(m_run, m_new), f_blk = merge_factor(m_blk, m_new);
-    l_run = fold(l_run, f_run, ph.x + ph.y, f_blk);
-    m_run = m_new;
-    const bool edge = kb + 32 > tile_hi || kb < tile_lo;
+        for (int r = 0; r < 16; ++r) c[x][r] = 0.0f;
+      auto kread = [&](int j) -> FloatVec<4> {
+        return __builtin_bit_cast(FloatVec<4>, *reinterpret_cast<const lds_u32x4*>(k_lds + (k_lane ^ (uint32_t)(32 * j))));
+      };
+      if constexpr (kStaged) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): the block's K
+        asm volatile("" ::: "memory");
 #pragma unroll
-    for (int pass = 0; pass < ND / NB; ++pass) {
-      f32x16 ob[NB];
+        for (int j = 0; j < 4; ++j) kf[j] = kread(j);
+      }
 #pragma unroll
-      for (int d = 0; d < NB; ++d)
+      for (int j = 0; j < NJ; ++j) {
+        const FloatVec<4> k = kf[j % LK];
+        if constexpr (kStaged) {
+          if (j + 4 < NJ) kf[(j + 4) % LK] = kread(j + 4);
+        } else {
+          kf[j % LK] = __builtin_bit_cast(FloatVec<4>, ld16((j + LK < NJ ? kp : kp_next) + 8 * ((j + LK) % NJ)));
+        }
+        if (j >= NJ - LV) vfetch(j - (NJ - LV));
+        const FloatVec<4> qj = kStaged ? q[kStaged ? j : 0] : kread(j);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ob[d][r] = 0.0f;
-      auto pv = [&](auto masked) {
+        for (int e = 0; e < 4; ++e) c[j % 4] = __builtin_amdgcn_mfma_f32_32x32x2f32(k.x[e], qj.x[e], c[j % 4], 0, 0, 0);
+      }
+      kp = kp_next;
+      if constexpr (kStaged) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);                      // lgkmcnt(0): the reads have returned
+        asm volatile("" ::: "memory");
+        if (i + 1 < n_blocks) stage_k(i + 1);
+      }
+      f32x16 s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = (c[0][r] + c[1][r]) + (c[2][r] + c[3][r]);
+      if (kb + 31 > ctx + first || kb < mask_lo) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int x = 16 * pass + r;
-          FloatVec<NB> v = vf[x % LV];
-          if (x + LV < 16 * (ND / NB)) vfetch(x + LV);
-          if constexpr (decltype(masked)::value) {
-            const int key = kb + half * 4 + (r >> 2) * 8 + (r & 3);
-            const bool in = key >= tile_lo && key < tile_hi;
-#pragma unroll
-            for (int d = 0; d < NB; ++d) v.x[d] = in ? v.x[d] : 0.0f;
-          }
-#pragma unroll
-          for (int d = 0; d < NB; ++d) ob[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.x[d], s[r], ob[d], 0, 0, 0);
+          const int key = kb + half * 4 + (r >> 2) * 8 + (r & 3);
+          s[r] = (key <= row_n && key >= row_lo) ? s[r] : -INFINITY;
         }
-      };
-      if (edge)
-        pv(std::true_type{});
-      else
-        pv(std::false_type{});
+      }
+      float mx = -INFINITY;
 #pragma unroll
-      for (int d = 0; d < NB; ++d)
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+      const float2 mh = halves32(mx);
+      // the block's own state (reference: its largest score), folded into the wave's
+      const float m_blk = fmaxf(mh.x, mh.y) * a.scale_log2;
+      const float m_ref = m_blk == -INFINITY ? 0.0f : m_blk;     // no key seen: every p is 0
+      float psum = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[NB * pass + d][r] = fold(o[NB * pass + d][r], f_run, ob[d][r], f_blk);
+      for (int r = 0; r < 16; ++r) {
+        s[r] = __builtin_amdgcn_exp2f(s[r] * a.scale_log2 - m_ref);
+        psum += s[r];
+      }
+      const float2 ph = halves32(psum);
+      const float m_new = fmaxf(m_run, m_blk);
+      const float f_run = merge_factor(m_run, m_new), f_blk = merge_factor(m_blk, m_new);
+      l_run = fold(l_run, f_run, ph.x + ph.y, f_blk);
+      m_run = m_new;
+      const bool edge = kb + 32 > tile_hi || kb < tile_lo;
+#pragma unroll
+      for (int pass = 0; pass < ND / NB; ++pass) {
+        f32x16 ob[NB];
+#pragma unroll
+        for (int d = 0; d < NB; ++d)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) ob[d][r] = 0.0f;
+        auto pv = [&](auto masked) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int x = 16 * pass + r;
+            FloatVec<NB> v = vf[x % LV];
+            if (x + LV < 16 * (ND / NB)) vfetch(x + LV);
+            FloatVec<NB> bad;                                    // its Inf and NaN values, zeros elsewhere
+            if constexpr (decltype(masked)::value) {
+              const int key = kb + half * 4 + (r >> 2) * 8 + (r & 3);
+              const bool in = key >= tile_lo && key < tile_hi;
+#pragma unroll
+              for (int d = 0; d < NB; ++d) v.x[d] = in ? v.x[d] : 0.0f;
+              if (careful) bad = take_finite(v);
+            }
+#pragma unroll
+            for (int d = 0; d < NB; ++d) ob[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(v.x[d], s[r], ob[d], 0, 0, 0);
+            if constexpr (decltype(masked)::value) {
+              if (careful) add_seen(ob, bad, s[r], kb + (r >> 2) * 8 + (r & 3));
+            }
+          }
+        };
+        if (edge || careful)
+          pv(std::true_type{});
+        else
+          pv(std::false_type{});
+#pragma unroll
+        for (int d = 0; d < NB; ++d)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[NB * pass + d][r] = fold(o[NB * pass + d][r], f_run, ob[d][r], f_blk);
+      }
     }
+    if (careful || __builtin_amdgcn_ballot_w64(row_ok && !all_finite(o)) == 0) break;
   }
 
   __syncthreads();                                             // every wave is past its K blocks

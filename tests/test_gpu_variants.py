@@ -361,3 +361,51 @@ def test_few_keys_have_exact_weights(call, dtype, D, Hq, Hkv, window):
             assert ((got - want).norm() / want.norm()).item() <= 1e-6, (n, h)
             if n + 1 - lo == 1:
                 assert torch.equal(got, want)
+
+
+# Inf and NaN among the values (and NaN among the keys) of tokens that a row does not see leave it as it is:
+# later tokens of its chunk, tokens below its window in the same key block, page or tile.
+@pytest.mark.parametrize("dtype,D,Hq,Hkv,windows", [
+    ("f32", 64, 4, 2, (0, 40)), ("f32", 128, 4, 4, (0, 9)), ("f32", 256, 8, 1, (0, 300))])
+def test_prefill_rows_take_nothing_from_masked_values(dtype, D, Hq, Hkv, windows):
+    import torch
+
+    from gpu_helpers import TORCH_DTYPE, attention_close
+    from paper_2607_14431_amd import kvg
+    L, ctx, chunk = 2, 700, 75
+    n_pages = (ctx + chunk + 15) // 16
+    g = torch.Generator(device="cuda").manual_seed(D)
+    cache = kvg.Cache.allocate(L, n_pages, Hq, Hkv, D, TORCH_DTYPE[dtype], windows=windows)
+    for pool in (cache.k_pool, cache.v_pool):
+        pool.copy_((torch.randn(pool.shape, generator=g, device="cuda") * 0.5).to(pool.dtype))
+    table = torch.randperm(n_pages, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda()[None]
+    seqs = kvg.Seqs(table, torch.tensor([ctx], dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda"), ctx)
+    q, k, v = (torch.randn((L, 1, chunk, h, D), device="cuda", generator=g).to(cache.raw_dtype) for h in (Hq, Hkv, Hkv))
+
+    def run():
+        out = torch.full((L, 1, chunk, Hq, D), float("nan"), device="cuda")
+        ws = torch.empty(kvg.kvg_prefill_workspace_bytes(cache, seqs, L, chunk), dtype=torch.uint8, device="cuda")
+        kvg.kvg_prefill_attn(cache, seqs, kvg.rope(), 0, L, chunk, q, k, v, D ** -0.5, out, ws)
+        return out
+
+    clean = run()
+    assert torch.isfinite(clean).all()
+    # chunk rows (an fp8 cache's appended values saturate) and cached tokens
+    bad = {680, 693} | (set() if dtype == "fp8" else {ctx + 40, ctx + 57})
+    for n in bad:
+        if n >= ctx:
+            v[:, 0, n - ctx, :, ::3] = float("inf") if n % 2 else float("nan")
+        else:
+            pool = cache.v_pool.view(torch.uint8) if dtype == "fp8" else cache.v_pool
+            pool[:, int(table[0, n // 16]), :, n % 16, 1::3] = 0x7F if dtype == "fp8" else float("-inf")
+    got = run()
+    for layer, w in enumerate(windows):
+        for i in range(chunk):
+            sees = any(n <= ctx + i and (w == 0 or n > ctx + i - w) for n in bad)
+            row, want = got[layer, 0, i], clean[layer, 0, i]
+            if sees:
+                assert not torch.isfinite(row).all(), (layer, i)
+            elif dtype == "f32":
+                assert torch.equal(row, want), (layer, i)
+            else:
+                attention_close(row.cpu().numpy(), want.cpu().numpy(), dtype)
