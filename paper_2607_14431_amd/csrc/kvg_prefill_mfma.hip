@@ -101,6 +101,10 @@ struct SwzFp8 {
 // Windows of at most this many keys of RB bytes are left to a kernel of their own (see `parts`).
 constexpr int prefill_exact_keys(int RB) { return RB >= 256 ? 64 : 64 * 256 / RB; }
 
+// one element of a row
+__device__ __forceinline__ float load_elem(const uint16_t* p) { return bf16_bits_to_f32(*p); }
+__device__ __forceinline__ float load_elem(const uint8_t* p) { return Elem<uint8_t>::get(make_uint4(*p, 0, 0, 0), 0); }
+
 // T: cache storage (uint16_t bf16, uint8_t fp8 E4M3).  fp8 tiles are staged as bytes (half the
 // HBM, DMA and LDS traffic) and widened to bf16 fragments exactly before the MFMAs.
 // NW: waves per workgroup (prefill_mfma_waves), 32 query rows each.
@@ -638,6 +642,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
     else
       tile(stage, kt, Parts1{});
   };
+  const int kt_first = kt_begin;
   if constexpr (kTight == 1) {
     if (kt_begin == 0)
       tile(Stage0{}, 0, Parts3{});
@@ -649,6 +654,57 @@ __global__ __launch_bounds__(64 * NW) void prefill_mfma_kernel(const PrefillArgs
   for (int kt = kt_begin; kt < n_tiles; kt += 2) {
     step(Stage0{}, kt);
     if (kt + 1 < n_tiles) step(Stage1{}, kt + 1);
+  }
+
+  // ---- kTight: a masked key weighs 0, and 0 times an Inf or NaN among its values would reach the rows that do
+  // not see it.  Rows whose result is not finite are taken again from their own keys alone, a key
+  // per lane for the scores, then a dimension per lane.
+  if constexpr (kTight != 0) {
+    const uint64_t off = __builtin_amdgcn_ballot_w64(row_ok && !all_finite(o));
+    const uint32_t rows = (uint32_t)off | (uint32_t)(off >> 32);
+    row_ok = row_ok && !((rows >> lrow) & 1);
+    for (uint32_t left = rows; left != 0; left &= left - 1) {
+      const int at = __builtin_ctz(left);
+      const int r_row = __builtin_amdgcn_readlane(row, at);
+      const int k0 = max(kt_first * kTileKeys, __builtin_amdgcn_readlane(row_lo, at));
+      const int k1 = min(n_tiles * kTileKeys, __builtin_amdgcn_readlane(row_n, at) + 1);
+      const float m = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m_run), at));
+      const int64_t rh = (((int64_t)l * a.batch + b) * a.chunk + r_row) * a.Hq + h;
+      const uint16_t* qp = static_cast<const uint16_t*>(a.q) + rh * D;
+      const uint16_t* qlp = a.q_lo + rh * D;
+      auto slab = [&](int key) -> int64_t {
+        const int32_t page = bt[key / kPage];
+        return (((int64_t)(page >= 0 && page < a.n_pages ? page : 0) * a.Hkv + g) * kPage + key % kPage) * D;
+      };
+      float l_row = 0.0f, acc[D / 64];
+#pragma unroll
+      for (int x = 0; x < D / 64; ++x) acc[x] = 0.0f;
+      for (int c = k0; c < k1; c += 64) {
+        const int key = c + lane;
+        const T* kr = kpool + slab(min(key, k1 - 1));
+        float sc = 0.0f;
+        for (int e = 0; e < D; ++e) sc = fmaf(bf16_bits_to_f32(qp[e]) + bf16_bits_to_f32(qlp[e]), load_elem(kr + e), sc);
+        const float p = key < k1 ? __builtin_amdgcn_exp2f(sc * a.scale_log2 - m) : 0.0f;
+        l_row += p;
+        for (int t = c; t < min(c + 64, k1); ++t) {
+          const float pt = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p), t - c));
+          const T* vr = vpool + slab(t);
+#pragma unroll
+          for (int x = 0; x < D / 64; ++x) acc[x] = fmaf(pt, load_elem(vr + 64 * x + lane), acc[x]);
+        }
+      }
+#pragma unroll
+      for (int x = 1; x < 64; x *= 2) l_row += __shfl_xor(l_row, x);
+      const int64_t pidx = rh * a.n_split_max + split;
+#pragma unroll
+      for (int x = 0; x < D / 64; ++x) {
+        if (a.part_acc != nullptr)
+          a.part_acc[pidx * D + 64 * x + lane] = acc[x];
+        else
+          a.out[rh * D + 64 * x + lane] = acc[x] / l_row;
+      }
+      if (a.part_acc != nullptr && lane == 0) *reinterpret_cast<float2*>(a.part_ml + pidx * 2) = make_float2(m, l_row);
+    }
   }
 
   // ---- shared split: the partial (reference, sum, unnormalised O) of this lane's row in the

@@ -366,7 +366,9 @@ def test_few_keys_have_exact_weights(call, dtype, D, Hq, Hkv, window):
 # Inf and NaN among the values (and NaN among the keys) of tokens that a row does not see leave it as it is:
 # later tokens of its chunk, tokens below its window in the same key block, page or tile.
 @pytest.mark.parametrize("dtype,D,Hq,Hkv,windows", [
-    ("f32", 64, 4, 2, (0, 40)), ("f32", 128, 4, 4, (0, 9)), ("f32", 256, 8, 1, (0, 300))])
+    ("f32", 64, 4, 2, (0, 40)), ("f32", 128, 4, 4, (0, 9)), ("f32", 256, 8, 1, (0, 300)),
+    ("bf16", 64, 8, 1, (0, 40)), ("bf16", 128, 16, 2, (0, 300)), ("bf16", 256, 8, 1, (0, 70)),
+    ("fp8", 64, 8, 1, (33, 300)), ("fp8", 128, 8, 1, (40, 9)), ("fp8", 256, 8, 1, (600, 70))])
 def test_prefill_rows_take_nothing_from_masked_values(dtype, D, Hq, Hkv, windows):
     import torch
 
