@@ -142,8 +142,8 @@ struct SplitWorker {
 
   // Branches in the consume functions are uniform over the wavefront (ballots), so the
   // loads of later rows stay in flight across them.  A key that is not ok contributes
-  // p = 0: its row is a real key's row (a key past the split loads key k1 - 1; the
-  // decode's new token is taken from LDS), so 0 * V adds nothing.  Only a block-table
+  // p = 0: its row is a visible key's row (a key past the split loads key k1 - 1, one
+  // below the window its first; the decode's new token is taken from LDS), so 0 * V adds nothing.  Only a block-table
   // entry outside the pool (whose outputs are unspecified) can bring other bytes.
   __device__ __forceinline__ void fix_row(Row& rw) {
     if (__builtin_amdgcn_ballot_w64(rw.lds) != 0) {
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(const DecodeArgs a) {
     const bool valid = page >= 0 && page < a.n_pages;
     rw.lds = j == ctx;
     rw.ok = rw.lds || (valid && j >= k0);
-    const int64_t roff = (((int64_t)(valid ? page : 0) * a.Hkv + g) * kPage + (j % kPage)) * D;
+    const int64_t roff = (((int64_t)(valid ? page : 0) * a.Hkv + g) * kPage + (max(j, k0) % kPage)) * D;
 #pragma unroll
     for (int i = 0; i < W::CPL; ++i) rw.k[i] = ld16_stream(kpool + roff + (wk.tl + W::TL * i) * W::CH);
 #pragma unroll

@@ -204,12 +204,13 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   // ---- direct loads of stage i: load j covers slots [64 j, 64 j + 64) of the K rows (then of the V
   // rows): row (64 j + lane) / NCH, position (64 j + lane) % NCH.  A slab's resource ends at its
   // last row below k1, so rows past it read as zeros (weighted 0); past the last stage
-  // every resource is empty.
+  // every resource is empty.  The first stage's value rows below the window are zeros too (an offset
+  // past the slab): an Inf or NaN there, times 0, would reach the result.
   constexpr int RPL = 64 / NCH;                      // rows per load
   const int lr = lane / NCH;
   const uint32_t k_off = lr * RB + 16 * ((lane % NCH) ^ SW::k(lr));
   const uint32_t v_off = lr * RB + 16 * ((lane % NCH) ^ SW::v(lr));
-  auto issue = [&](auto st, int i) {
+  auto issue = [&](auto st, int i, auto first) {
     lds_char* dst = (lds_char*)(lds_void*)stage_mem(st);
 #pragma unroll
     for (int p = 0; p < PS; ++p) {
@@ -225,7 +226,8 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
         const int r0 = j * RPL;                      // row in the page
         const int rs = p * kPage + r0;               // row in the stage
         const uint32_t ok = r0 * RB + (k_off ^ (16 * SW::k(rs)));
-        const uint32_t ov = r0 * RB + (v_off ^ (16 * SW::v(rs)));
+        uint32_t ov = r0 * RB + (v_off ^ (16 * SW::v(rs)));
+        if (decltype(first)::value && p == 0) ov = k0 + r0 + lr < lo ? kPage * RB : ov;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lds_void*)(dst + rs * RB), 16, ok, 0, 0, kStream);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void*)(dst + SK * RB + rs * RB), 16, ov, 0, 0, kStream);
       }
@@ -234,8 +236,8 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
   using S2 = std::integral_constant<int, 2>;
-  issue(S0{}, 0);
-  if constexpr (kStages > 2) issue(S1{}, 1);
+  issue(S0{}, 0, std::true_type{});
+  if constexpr (kStages > 2) issue(S1{}, 1, std::false_type{});
 
   // ---- rotation table in the last stage's memory (its first loads come after it is read),
   // rotated queries, the new token's rows (written to the cache, kept for LDS)
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   }
   lds_ready();                                       // the stage's memory is free for its loads
   static_assert(4 * D + 2 * 8 * D * 2 <= kStageBytes, "table and queries fit a stage");
-  issue(std::integral_constant<int, kStages - 1>{}, kStages - 1);
+  issue(std::integral_constant<int, kStages - 1>{}, kStages - 1, std::false_type{});
 
   // ---- state of the unit and of the split's units so far (lane: head `col` % 8, dims 16 d + 4 grp
   // + 0..3 of O, its own keys' part of the sum)
@@ -470,7 +472,7 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
     // the stage's reads have returned: its memory takes stage i + kStages
     __builtin_amdgcn_s_waitcnt(kLgkmWait);
     asm volatile("" ::: "memory");
-    issue(st, i + kStages);
+    issue(st, i + kStages, std::false_type{});
     if constexpr (!kSolo) {
       if (((i + 1) % kUnitStages == 0 && i + 1 < 4 * kUnitStages) || i + 1 == n_stages) {   // end of a unit
         const float lu = sum_over_groups(lsum);

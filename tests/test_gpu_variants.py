@@ -411,3 +411,33 @@ def test_prefill_rows_take_nothing_from_masked_values(dtype, D, Hq, Hkv, windows
                 assert torch.equal(row, want), (layer, i)
             else:
                 attention_close(row.cpu().numpy(), want.cpu().numpy(), dtype)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 256), ("fp8", 64), ("fp8", 128), ("f32", 64), ("f32", 256)])
+def test_windowed_decode_takes_nothing_from_below_its_window(dtype, D):
+    import torch
+
+    from gpu_helpers import INT_VIEW, TORCH_DTYPE
+    from paper_2607_14431_amd import kvg
+    Hq, Hkv, window, ctxs = 8, 2, 100, [104, 1000, 1011, 1012]
+    B, per_seq = len(ctxs), max(ctxs) // 16 + 1
+    g = torch.Generator(device="cuda").manual_seed(D)
+    cache = kvg.Cache.allocate(1, B * per_seq, Hq, Hkv, D, TORCH_DTYPE[dtype], windows=(window,))
+    for pool in (cache.k_pool, cache.v_pool):
+        pool.copy_((torch.randn(pool.shape, generator=g, device="cuda") * 0.5).to(pool.dtype))
+    tables = torch.randperm(B * per_seq, generator=g, device="cuda").to(torch.int32).view(B, per_seq)
+    lens = torch.tensor(ctxs, dtype=torch.int32, device="cuda")
+    raw = [torch.randn((1, B, 1, h, D), generator=g, device="cuda").to(cache.raw_dtype) for h in (Hq, Hkv, Hkv)]
+    seqs = kvg.Seqs(tables, lens, torch.zeros(B, dtype=torch.int64, device="cuda"), max(ctxs))
+
+    def run():
+        out = torch.full((1, B, 1, Hq, D), float("nan"), device="cuda")
+        kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, 1, *raw, D ** -0.5, out, kvg.decode_workspace(cache, seqs, 1))
+        return out
+
+    clean = run()
+    for b, ctx in enumerate(ctxs):
+        for n in range((ctx + 1 - window) // 16 * 16, ctx + 1 - window):
+            for pool in (cache.k_pool, cache.v_pool):
+                pool.view(INT_VIEW[dtype])[:, int(tables[b, n // 16]), :, n % 16] = 0x7F if dtype == "fp8" else -1    # NaN
+    assert torch.isfinite(clean).all() and torch.equal(run(), clean)
