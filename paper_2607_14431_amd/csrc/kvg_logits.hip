@@ -197,14 +197,13 @@ __global__ __launch_bounds__(kThreads) void logit_head_kernel(const LogitArgs a)
 }
 
 // ---------------------------------------------------------------------------- comparison
-// One workgroup per row (the call has no workspace to combine more in), so a row is bound by what
-// one CU reads and exponentiates.  One pass over both rows: with a reference r the running sums
+// One workgroup per row at most (the call has no workspace to combine more in), so a long row is bound by
+// what one CU reads and exponentiates.  One pass over both rows: with a reference r the running sums
 //   A = sum e^(a - r_a),  T = sum e^(a - r_a) (a - b),  B = sum e^(b - r_b)
 // give lse_a = r_a + log A, lse_b = r_b + log B and KL = T / A - (lse_a - lse_b), two
 // exponentials an element.  fp64's range lets a lane keep its first value as the reference until
-// one exceeds it by e^300.  50 rows of 262,144: 151 us; three passes (maximum, sums, KL) of
+// one exceeds it by e^300.  50 rows of 262,144: 141 us; three passes (maximum, sums, KL) of
 // 256 lanes with the library's exp: 1,108 us.
-constexpr int kCompareThreads = 1024;
 constexpr double kRaise = 300.0;
 
 struct ArgMax {
@@ -261,31 +260,48 @@ __device__ __forceinline__ void add_element(RowSums& s, float af, float bf, int 
   s.sb += exp_table(b - s.rb, tab);
 }
 
-// x and y over the larger of their references
-__device__ __forceinline__ RowSums merge_sums(const RowSums& x, const RowSums& y, const double* tab) {
-  RowSums r;
-  r.ma = better(x.ma, y.ma);
-  r.mb = better(x.mb, y.mb);
-  r.ra = fmax(x.ra, y.ra);
-  r.rb = fmax(x.rb, y.rb);
-  const double xa = exp_table(x.ra - r.ra, tab), ya = exp_table(y.ra - r.ra, tab);
-  r.sa = x.sa * xa + y.sa * ya;
-  r.t = x.t * xa + y.t * ya;
-  r.sb = x.sb * exp_table(x.rb - r.rb, tab) + y.sb * exp_table(y.rb - r.rb, tab);
-  return r;
+struct Refs {
+  double a, b;
+};
+struct Sums {
+  double a, b, t;
+  ArgMax ma, mb;
+};
+__device__ __forceinline__ Refs shuffle(const Refs& x, int m) { return {__shfl_xor(x.a, m), __shfl_xor(x.b, m)}; }
+__device__ __forceinline__ Sums shuffle(const Sums& x, int m) {
+  return {__shfl_xor(x.a, m), __shfl_xor(x.b, m), __shfl_xor(x.t, m), {__shfl_xor(x.ma.v, m), __shfl_xor(x.ma.i, m)},
+          {__shfl_xor(x.mb.v, m), __shfl_xor(x.mb.i, m)}};
 }
 
-// kVec: rows of 16-byte vectors (V a multiple of 4 and both buffers aligned)
-template <bool kVec>
-__global__ __launch_bounds__(kCompareThreads) void logit_compare_kernel(const CompareArgs c) {
+// x combined with y over the row's lanes: over a wave by shuffles, over several waves in their order
+template <int kLanes, typename X, typename Op>
+__device__ __forceinline__ X over_row(X x, Op op, X* sh) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) x = op(x, shuffle(x, m));
+  if constexpr (kLanes > 64) {
+    if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64] = x;
+    __syncthreads();
+    x = sh[0];
+#pragma unroll
+    for (int w = 1; w < kLanes / 64; ++w) x = op(x, sh[w]);
+  }
+  return x;
+}
+
+// kVec: rows of 16-byte vectors (V a multiple of 4 and both buffers aligned).  kLanes: of a row.
+template <bool kVec, int kLanes>
+__global__ __launch_bounds__(kLanes < kThreads ? kThreads : kLanes, 8) void logit_compare_kernel(const CompareArgs c) {
+  constexpr int kRowsPer = kLanes < kThreads ? kThreads / kLanes : 1;
   __shared__ double tab[64];
-  __shared__ RowSums sh[kCompareThreads / 64];
-  const int64_t base = (int64_t)blockIdx.x * c.V;
-  const float* a = c.a + base;
-  const float* b = c.b + base;
-  const int tid = threadIdx.x;
-  if (tid < 64) tab[tid] = exp2(tid / 64.0);
+  __shared__ Refs sh_refs[kLanes / 64];
+  __shared__ Sums sh_sums[kLanes / 64];
+  const int tid = threadIdx.x % kLanes;
+  const int row = blockIdx.x * kRowsPer + threadIdx.x / kLanes;
+  if (threadIdx.x < 64) tab[threadIdx.x] = exp2(threadIdx.x / 64.0);
   __syncthreads();
+  if (row >= c.rows) return;                       // whole waves (kLanes 64)
+  const float* a = c.a + (int64_t)row * c.V;
+  const float* b = c.b + (int64_t)row * c.V;
 
   // a reference far below every finite logit stands for "none yet" (it is raised at the first)
   RowSums s{-1e300, -1e300, 0.0, 0.0, 0.0, {-INFINITY, c.V}, {-INFINITY, c.V}};
@@ -296,9 +312,9 @@ __global__ __launch_bounds__(kCompareThreads) void logit_compare_kernel(const Co
     // the next vectors are requested before the current ones are used (the last lanes' re-read
     // their own)
     float4 na = a4[min(tid, n4 - 1)], nb = b4[min(tid, n4 - 1)];
-    for (int i = tid; i < n4; i += kCompareThreads) {
+    for (int i = tid; i < n4; i += kLanes) {
       const float4 x = na, y = nb;
-      const int next = min(i + kCompareThreads, n4 - 1);
+      const int next = min(i + kLanes, n4 - 1);
       na = a4[next];
       nb = b4[next];
       add_element(s, x.x, y.x, 4 * i, tab);
@@ -307,31 +323,24 @@ __global__ __launch_bounds__(kCompareThreads) void logit_compare_kernel(const Co
       add_element(s, x.w, y.w, 4 * i + 3, tab);
     }
   } else {
-    for (int i = tid; i < c.V; i += kCompareThreads) add_element(s, a[i], b[i], i, tab);
+    for (int i = tid; i < c.V; i += kLanes) add_element(s, a[i], b[i], i, tab);
   }
 
-  // fixed tree: lanes xor 32 .. 1, then the waves in order
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    RowSums o;
-    o.ra = __shfl_xor(s.ra, m);
-    o.rb = __shfl_xor(s.rb, m);
-    o.sa = __shfl_xor(s.sa, m);
-    o.sb = __shfl_xor(s.sb, m);
-    o.t = __shfl_xor(s.t, m);
-    o.ma = {__shfl_xor(s.ma.v, m), __shfl_xor(s.ma.i, m)};
-    o.mb = {__shfl_xor(s.mb.v, m), __shfl_xor(s.mb.i, m)};
-    s = merge_sums(s, o, tab);
-  }
-  if (tid % 64 == 0) sh[tid / 64] = s;
-  __syncthreads();
+  // every lane's sums over the row's largest references, then added in a fixed tree
+  const Refs r = over_row<kLanes>(
+      Refs{s.ra, s.rb}, [](const Refs& x, const Refs& y) { return Refs{fmax(x.a, y.a), fmax(x.b, y.b)}; }, sh_refs);
+  const double fa = exp_table(s.ra - r.a, tab);
+  const Sums sum = over_row<kLanes>(
+      Sums{s.sa * fa, s.sb * exp_table(s.rb - r.b, tab), s.t * fa, s.ma, s.mb},
+      [](const Sums& x, const Sums& y) {
+        return Sums{x.a + y.a, x.b + y.b, x.t + y.t, better(x.ma, y.ma), better(x.mb, y.mb)};
+      },
+      sh_sums);
   if (tid == 0) {
-    RowSums r = sh[0];
-    for (int w = 1; w < kCompareThreads / 64; ++w) r = merge_sums(r, sh[w], tab);
-    const double lse_a = r.ra + log(r.sa), lse_b = r.rb + log(r.sb);
-    c.kl[blockIdx.x] = r.t / r.sa - (lse_a - lse_b);
-    c.arg_a[blockIdx.x] = r.ma.i;
-    c.arg_b[blockIdx.x] = r.mb.i;
+    const double lse_a = r.a + log(sum.a), lse_b = r.b + log(sum.b);
+    c.kl[row] = sum.t / sum.a - (lse_a - lse_b);
+    c.arg_a[row] = sum.ma.i;
+    c.arg_b[row] = sum.mb.i;
   }
 }
 
@@ -362,6 +371,25 @@ hipError_t launch_logits_pack(const PackArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Lanes of a row, by its length alone (a row's bytes do not depend on the others): what a lane does beside its
+// elements (references, factors, sums over the lanes) is 2 us of a wave's time and 5 of 16 waves'.
+//   us, 64 / 256 / 1024 lanes   1 row               1,000 rows             10,000 rows
+//   V 100                       5.1 / 5.0 / 7.6     5.6 / 7.5 / 24.7       17 / 44 / 211
+//   V 512                       5.2 / 5.1 / 7.6     6.3 / 7.8 / 24.9       22 / 45 / 216
+//   V 2,048                     9.3 / 5.6 / 8.2     12 / 11 / 29           54 / 66 / 256
+//   V 8,192                     29 / 10 / 12        35 / 26 / 43           196 / 207 / 399
+//   V 16,384                    54 / 17 / 16        63 / 45 / 60           374 / 382 / 569
+// 256 lanes in three passes: 7.9, 8.0 and 37 at V 100; 39, 96 and 748 at V 16,384.
+template <bool kVec>
+void launch_compare(const CompareArgs& c, hipStream_t stream) {
+  if (c.V <= 512)
+    logit_compare_kernel<kVec, 64><<<dim3((unsigned)((c.rows + 3) / 4)), kThreads, 0, stream>>>(c);
+  else if (c.V <= 12288)
+    logit_compare_kernel<kVec, 256><<<dim3((unsigned)c.rows), kThreads, 0, stream>>>(c);
+  else
+    logit_compare_kernel<kVec, 1024><<<dim3((unsigned)c.rows), 1024, 0, stream>>>(c);
+}
+
 hipError_t launch_logit_compare(const CompareArgs& call, hipStream_t stream) {
   constexpr int32_t kRows = 1 << 20;             // of a launch: 2^30 threads
   const bool vec = call.V % 4 == 0 && reinterpret_cast<uintptr_t>(call.a) % 16 == 0 &&
@@ -370,9 +398,9 @@ hipError_t launch_logit_compare(const CompareArgs& call, hipStream_t stream) {
   for (int32_t row = 0; row < call.rows; row += kRows) {
     c.rows = std::min(call.rows - row, kRows);
     if (vec)
-      logit_compare_kernel<true><<<dim3((unsigned)c.rows), kCompareThreads, 0, stream>>>(c);
+      launch_compare<true>(c, stream);
     else
-      logit_compare_kernel<false><<<dim3((unsigned)c.rows), kCompareThreads, 0, stream>>>(c);
+      launch_compare<false>(c, stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     c.a += (int64_t)kRows * c.V;

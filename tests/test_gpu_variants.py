@@ -85,10 +85,11 @@ def test_f32_prefill_unit_per_workgroup():
         run(3, 1, small - 1)
 
 
-# The comparison's single pass: rows read as vectors and element by element, fewer elements than
-# lanes, references that have to be raised (spread > e^300), infinities.
+# The comparison's single pass: a wave, 4 and 16 waves a row, rows read as vectors and element by element, fewer elements
+# than lanes, references that have to be raised (spread > e^300), infinities.
 @pytest.mark.parametrize("rows,V,scale", [(1, 1, 1.0), (3, 7, 1.0), (2, 64, 1.0), (3, 4095, 5.0), (2, 4100, 5.0),
-                                          (2, 33_000, 300.0), (1, 10_001, 2000.0)])
+                                          (2, 33_000, 300.0), (1, 10_001, 2000.0), (5, 512, 5.0),
+                                          (2, 513, 300.0), (6, 511, 2000.0), (2, 12_288, 5.0), (2, 12_289, 5.0)])
 def test_logit_compare_pass(rows, V, scale):
     import numpy as np
     import torch
