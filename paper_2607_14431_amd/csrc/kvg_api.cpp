@@ -252,13 +252,20 @@ DecodeGrid decode_grid(const kvg_cache* c, const kvg_seqs* s, int32_t layer0, in
 }
 
 // Decodes that leave the chip idle give every 128-key unit of a split a wave (DecodeArgs.solo)
-// instead of every split: as long as the waves of all units are resident at once, five on each of 256
-// CUs.  One 12B-class layer over 4.6k keys (72 splits): 36 us with a wave per split, 20 with a
-// wave per unit; 4 sequences (296): 43 and 41; 8 (592): 56 and 63.  A windowed layer's
-// splits are those its window has.
-constexpr int kSoloWaves = 5 * 256;
+// instead of every split, where a row can have several units: as long as the waves of all units are resident at
+// once, by their LDS five on each of 256 CUs, ten at rows of at most 128 bytes.  One 12B-class layer over
+// 4.6k keys (72 splits): 36 us with a wave per split, 20 with a wave per unit; 4 sequences (296): 43 and
+// 41; 8 (592): 56 and 63.  Not below two units' keys: a wave per split then has few more keys than a wave per
+// unit, and one split needs no merge (4 layers x 8 sequences over 200 keys, head_dim 128: 12.7 us against 17.4; over 300
+// keys 16.1 and 17.4, but 24 layers of one sequence at head_dim 256 24.3 and 21.2).  A windowed layer's splits are
+// those its window can touch.
+int solo_waves(const kvg_cache* c) {
+  return 256 * (kvg::kLdsBytes / (2 * kvg::decode_stage_bytes(c->head_dim * (int)elem_bytes(c))));
+}
 bool decode_solo(const kvg_cache* c, const kvg_seqs* s, const DecodeGrid& grid) {
-  return c->dtype != KVG_F32 && shared_splits(c, s) == 0 && grid.items * 4 <= kSoloWaves && n_split_max(s, 1) <= kSoloWaves / 4;
+  const int waves = solo_waves(c);
+  return c->dtype != KVG_F32 && shared_splits(c, s) == 0 && s->max_ctx_len >= 2 * kvg::kUnit && grid.items * 4 <= waves &&
+         n_split_max(s, 1) <= waves / 4;
 }
 
 struct DecodeWs {
@@ -285,7 +292,7 @@ DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, size
 size_t decode_ws_bytes(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
   const size_t unit_bytes = (size_t)(c->n_q_heads / c->n_kv_heads) * (c->head_dim + 2) * sizeof(float);
   const size_t layout = (size_t)n_layers * s->batch * c->n_kv_heads * n_split_max(s, 1) * 4;
-  const size_t units = c->dtype == KVG_F32 ? 0 : std::min<size_t>(4 * kSoloWaves, layout);
+  const size_t units = c->dtype == KVG_F32 ? 0 : std::min<size_t>(4 * (size_t)solo_waves(c), layout);
   return std::max(decode_ws(c, s, n_layers).total, units * unit_bytes + 2 * kAlign);
 }
 

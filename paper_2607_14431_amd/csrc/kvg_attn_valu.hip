@@ -598,9 +598,8 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
 // arithmetic.  A workgroup per (layer, sequence, query head): the splits' (reference, sum) pairs
 // and weights are worked out once, in LDS; the lane groups then bring kMergeChunk splits' values
 // at a time (every partial requested at once), and one lane per element sums them in order.
-constexpr int kMergeThreads = 1024;
 constexpr int kMergeChunk = 32;
-template <bool kSolo>
+template <bool kSolo, int kMergeThreads>
 __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const DecodeArgs a) {
   constexpr int U = kSolo ? 4 : 1;                         // partials per split
   const int64_t row_head = blockIdx.x;
@@ -703,6 +702,9 @@ __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const Decod
 // 10.2 us against 11.8 on 256 lanes, 512 rows 12.4 against 13.0, 1,024 rows 22.5 against 17.1, 24,576 rows 654 against 313;
 // over 18 splits: 5.2 / 6.3, 6.3 / 6.6, 11.0 / 8.6.  More splits than fit its LDS combine on 256 lanes too.
 constexpr int64_t kMergeRows = 512;
+// Units of up to so many splits are merged on 256 lanes a row (4 layers x 8 sequences, 512 rows over one split: 17 us
+// a call against 21; 768 rows over 3: 25.8 / 28.3), of more on 1,024.
+constexpr int kMergeFewSplits = 4;
 constexpr size_t kMergeLds = 65536 - 256;      // dynamic: its static arrays and this stay within 64 KiB
 // Bytes of dynamic LDS it takes.
 size_t merge_lds(const DecodeArgs& a) {
@@ -788,12 +790,15 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream) {
                        : dtype == kDtypeF32 ? launch_decode_f32(a, stream)
                                             : launch_decode_mfma(a, dtype, stream);
   if (e != hipSuccess) return e;
+  if (a.n_split_max == 1 && a.n_shared_split == 0 && !a.solo) return hipSuccess;   // every row is written
   const int64_t n_rows = (int64_t)a.n_layers * a.batch * a.Hq;
   const dim3 grid((unsigned)n_rows);
-  if (a.solo)
-    merge_splits_kernel<true><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
+  if (a.solo && a.n_split_max <= kMergeFewSplits)
+    merge_splits_kernel<true, 256><<<grid, 256, merge_lds(a), stream>>>(a);
+  else if (a.solo)
+    merge_splits_kernel<true, 1024><<<grid, 1024, merge_lds(a), stream>>>(a);
   else if (a.n_split_max > 16 && merge_lds(a) <= kMergeLds && n_rows <= kMergeRows)
-    merge_splits_kernel<false><<<grid, kMergeThreads, merge_lds(a), stream>>>(a);
+    merge_splits_kernel<false, 1024><<<grid, 1024, merge_lds(a), stream>>>(a);
   else
     decode_merge_kernel<<<grid, kThreads, 0, stream>>>(a);
   return hipGetLastError();

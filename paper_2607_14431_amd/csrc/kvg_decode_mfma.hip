@@ -8,8 +8,8 @@
 //
 // What bounds it: HBM, when the launch fills the chip.  Keys and values go from the pages straight
 // into LDS (buffer_load ... lds, whole (page, head) slabs, 1 KiB of consecutive bytes per
-// instruction), 16 KiB per stage and kStages stages deep, without a register; a workgroup is
-// one wave, so a CU holds four or five and their starts and ends overlap.  The arithmetic is
+// instruction), kStages stages deep, without a register; a workgroup is one wave, so a CU holds
+// three to ten (launch_decode_type) and their starts and ends overlap.  The arithmetic is
 // small beside that: a 16-key tile's scores for up to 8 query heads are D / 32
 // v_mfma_f32_16x16x32_bf16 (A = 16 keys, B = the heads' queries: bf16 high parts in columns 0-7, low
 // parts in columns 8-15, the two halves added by one row rotation), the weights leave the
@@ -19,8 +19,7 @@
 // one dot product per key and head) a pair of keys took ~200 instructions in a row, which bound
 // every launch that left CUs idle.
 //
-// kSolo: a wave per unit instead of per split, with more stages in flight, for launches that
-// leave CUs idle; the four units of a split leave four partials, which merge_splits_kernel merges with
+// kSolo: a wave per unit instead of per split, for launches that leave CUs idle; the four units of a split leave four partials, which merge_splits_kernel merges with
 // the same operations in the same order, so the bytes are the same.
 #include "kvg_launch.h"
 #include "kvg_mfma.h"
@@ -34,7 +33,6 @@ namespace kvg {
 
 namespace {
 
-constexpr int kStageBytes = 16384;     // K and V of one stage
 constexpr int kFewKeys = 64;           // rows of at most so many keys take exact weights
 constexpr int kStream = 2;             // buffer load policy: nontemporal (every row is read once)
 constexpr int kLgkmWait = 0xC07F;      // s_waitcnt operand: lgkmcnt(0) alone
@@ -88,36 +86,33 @@ __device__ __forceinline__ void lds_ready() {
   asm volatile("" ::: "memory");
 }
 
-template <int S>
+template <int S, int BYTES>
 __device__ __forceinline__ uint4* stage_memory() {
-  __shared__ __attribute__((aligned(1024))) uint4 mem[kStageBytes / 16];
+  __shared__ __attribute__((aligned(1024))) uint4 mem[BYTES / 16];
   return mem;
 }
 
-template <typename T, int D, bool kSolo>
+// kStages: stages of K and V in flight, per wave
+template <typename T, int D, bool kSolo, int kStages>
 __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const DecodeArgs a) {
   constexpr bool kFp8 = sizeof(T) == 1;
   using R = uint16_t;                                // raw inputs are bf16
   constexpr int RB = D * (int)sizeof(T);             // bytes per cache row
   constexpr int NCH = RB / 16;
+  constexpr int kStageBytes = decode_stage_bytes(RB);     // K and V of one stage
   constexpr int SK = kStageBytes / 2 / RB;           // keys per stage
   constexpr int PS = SK / kPage;                     // pages per stage
   constexpr int BK = SK < 32 ? SK : 32;              // keys per softmax block
   constexpr int NTL = BK / 16;                       // 16-key tiles of a block
   constexpr int NS = D / 32;                         // MFMA steps of a score tile
   constexpr int ND = D / 16;                         // 16-wide blocks of head_dim
-  // Stages in flight: a solo wave's unit is short (four stages were no faster than two, which
-  // let five workgroups share a CU instead of two); a whole split of wide rows runs faster with three
-  // (16 sequences x 4.6k keys at head_dim 256: bf16 117 -> 105 us, fp8 72 -> 66), of fp8 rows of
-  // head_dim 128 with two (69 against 78).
-  constexpr int kStages = !kSolo && RB >= 256 ? 3 : 2;
   constexpr int kLoads = kStageBytes / 1024;         // direct loads per stage
   constexpr int kUnitStages = kUnit / SK;
   static_assert(kUnit % SK == 0 && SK % BK == 0 && (kStages - 1) * kLoads <= 63, "stage");
   using SW = SwzDecode<RB, kFp8>;
   // one LDS object per stage, so that the compiler can tell the stage being read from those
   // being loaded; K rows, then V rows
-  auto stage_mem = [&](auto st) -> uint4* { return stage_memory<decltype(st)::value>(); };
+  auto stage_mem = [&](auto st) -> uint4* { return stage_memory<decltype(st)::value, kStageBytes>(); };
 
   // ---- work item (the order of decode_kernel: sequence fastest; with a shared window runs of 64
   // items go to one XCD)
@@ -241,7 +236,7 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
 
   // ---- rotation table in the last stage's memory (its first loads come after it is read),
   // rotated queries, the new token's rows (written to the cache, kept for LDS)
-  float* cs = reinterpret_cast<float*>(stage_memory<kStages - 1>());
+  float* cs = reinterpret_cast<float*>(stage_memory<kStages - 1, kStageBytes>());
 #pragma unroll
   for (int i = 0; i < NTH; ++i) {
     const int p = lane + 64 * i;
@@ -550,24 +545,43 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
 
 }  // namespace
 
-template <typename T, bool kSolo>
+template <typename T, bool kSolo, int kStages>
 hipError_t launch_decode_mfma_t(const DecodeArgs& a, hipStream_t stream) {
   const int64_t n_wg = decode_items(a) * (kSolo ? 4 : 1);
   const dim3 grid((unsigned)n_wg);
   switch (a.D) {
-    case 64: decode_mfma_kernel<T, 64, kSolo><<<grid, 64, 0, stream>>>(a); break;
-    case 128: decode_mfma_kernel<T, 128, kSolo><<<grid, 64, 0, stream>>>(a); break;
-    case 256: decode_mfma_kernel<T, 256, kSolo><<<grid, 64, 0, stream>>>(a); break;
+    case 64: decode_mfma_kernel<T, 64, kSolo, 2><<<grid, 64, 0, stream>>>(a); break;
+    case 128: decode_mfma_kernel<T, 128, kSolo, sizeof(T) == 2 ? kStages : 2><<<grid, 64, 0, stream>>>(a); break;
+    case 256: decode_mfma_kernel<T, 256, kSolo, kStages><<<grid, 64, 0, stream>>>(a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
+// Stages in flight of a wave per split.  Rows of at least 256 bytes (16 KiB stages): three, which leave room for
+// three waves on a CU, 768 in all, and run faster than two with five (16 sequences x 4.6k keys at head_dim 256:
+// bf16 117 -> 105 us, fp8 72 -> 66).  A launch of a little more than one or two rounds of those pays for a whole
+// round more, and takes two: us at head_dim 256 with three / two stages, bf16 and fp8,
+//   792 splits   95 / 78,  62 / 46      1,224   108 / 127,  66 / 83
+//   1,008       102 / 88,  64 / 55      1,440   124 / 138,  72 / 90
+//   1,728       162 / 157, 97 / 94      2,016   173 / 178, 101 / 107
+//   2,592       232 / 230, 134 / 138    3,168   289 / 291, 165 / 170
+// Four stages leave two waves a CU: 168 and 125 at 1,728.  Two waves that share a split, half each, were no
+// faster either (158, 100).  Shorter rows have 8 KiB stages, two of them: ten waves a CU, whose 32-key blocks, one
+// after the other, are what bounds them (64-byte rows, 8 heads x 64 sequences over 30k keys: 487 us with
+// 16 KiB stages, 328).
+template <typename T>
+hipError_t launch_decode_type(const DecodeArgs& a, hipStream_t stream) {
+  if (a.solo) return launch_decode_mfma_t<T, true, 2>(a, stream);
+  constexpr int64_t kRound = 3 * 256;
+  const int64_t n = decode_items(a), over = n % kRound;
+  const bool two = n > kRound && n < 3 * kRound && over > 0 && over <= kRound / 3;
+  return two ? launch_decode_mfma_t<T, false, 2>(a, stream) : launch_decode_mfma_t<T, false, 3>(a, stream);
+}
+
 hipError_t launch_decode_mfma(const DecodeArgs& a, int dtype, hipStream_t stream) {
-  if (dtype == kDtypeBf16)
-    return a.solo ? launch_decode_mfma_t<uint16_t, true>(a, stream) : launch_decode_mfma_t<uint16_t, false>(a, stream);
-  if (dtype == kDtypeFp8)
-    return a.solo ? launch_decode_mfma_t<uint8_t, true>(a, stream) : launch_decode_mfma_t<uint8_t, false>(a, stream);
+  if (dtype == kDtypeBf16) return launch_decode_type<uint16_t>(a, stream);
+  if (dtype == kDtypeFp8) return launch_decode_type<uint8_t>(a, stream);
   return hipErrorInvalidValue;
 }
 

@@ -47,7 +47,10 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream);
 inline int64_t decode_items(const DecodeArgs& a) {
   return (int64_t)a.batch * a.Hkv * ((int64_t)a.n_full * a.n_split_full + (int64_t)(a.n_layers - a.n_full) * a.n_split_win);
 }
-// its split kernel for bf16 and fp8 caches (kvg_decode_mfma.hip)
+// its split kernel for bf16 and fp8 caches (kvg_decode_mfma.hip); K and V bytes of one of its stages, for cache
+// rows of RB bytes
+constexpr int kLdsBytes = 160 << 10;       // of a CU
+constexpr int decode_stage_bytes(int RB) { return RB >= 256 ? 16384 : 8192; }
 hipError_t launch_decode_mfma(const DecodeArgs& a, int dtype, hipStream_t stream);
 
 

@@ -1,6 +1,6 @@
-"""Chunked-prefill and decode attention (bf16 MFMA path and fp32 VALU path) against the oracle with
+"""Chunked-prefill and decode attention (bf16, fp8 and fp32 caches) against the oracle with
 ragged chunks, per-sequence context lengths that are not tile multiples, several query
-tiles, GQA groups 1/2/4 and a peaky variant (queries scaled x8 plus diagonal needles) whose
+tiles, GQA groups 1/2/4/8 and a peaky variant (queries scaled x8 plus diagonal needles) whose
 outputs are far above the tolerance.  Sliding-window layers (row i sees keys (i - W, i],
 Sec. 4.3's windowed layers) run beside global ones, with windows of one key, windows that end
 inside a key tile (64) or a decode split (512), and windows longer than the context.  Both
@@ -29,10 +29,10 @@ CASES = [
     ("bf16", 256, 4, 2, [300, 17], 96, 2, 8),     # peaky: q sigma 4, needles k = q / 8
     ("bf16", 256, 4, 2, [300, 17], 96, 2, 2),     # harsh: needles k = q / 2, score std ~8
     ("bf16", 128, 8, 2, [700, 3], 70, 2, 2),      # harsh, group 4, D 128 (8 waves)
-    ("bf16", 128, 16, 2, [600, 40], 90, 2, 2),    # harsh, group 8 (vector ALU path)
+    ("bf16", 128, 16, 2, [600, 40], 90, 2, 2),    # harsh, group 8
     ("f32", 64, 4, 2, [33, 250], 40, 0, 0),
     ("f32", 64, 4, 2, [100], 24, 3, 8),           # peaky fp32
-    # fp8 E4M3 caches (bf16 inputs): MFMA for groups 1, 2, 4 at D 256, 128, 64; VALU for group 8
+    # fp8 E4M3 caches (bf16 inputs): groups 1, 2, 4 and 8 at D 256, 128, 64
     ("fp8", 256, 4, 2, [0, 77, 600], 130, -1, 0),
     ("fp8", 128, 4, 4, [64, 1000], 200, -1, 0),
     ("fp8", 64, 2, 1, [129], 257, -1, 0),
@@ -63,8 +63,8 @@ WINDOW_CASES = [
     ("bf16", 256, 4, 2, [0, 700], 130, (100, 0, 1)),          # MFMA group 2
     ("bf16", 128, 4, 4, [77, 1000], 200, (64, 513, 5000)),     # MFMA group 1
     ("bf16", 128, 16, 4, [300], 150, (250, 0, 37)),            # MFMA group 4
-    ("bf16", 128, 16, 2, [600, 40], 90, (600, 65, 0)),         # VALU group 8
-    ("f32", 64, 4, 2, [1100, 3], 45, (512, 1, 700)),           # fp32 VALU
+    ("bf16", 128, 16, 2, [600, 40], 90, (600, 65, 0)),         # MFMA group 8
+    ("f32", 64, 4, 2, [1100, 3], 45, (512, 1, 700)),           # fp32
     ("fp8", 256, 4, 2, [0, 700], 130, (100, 0, 1)),           # fp8 MFMA
 ]
 
@@ -254,9 +254,9 @@ def _decode_case(dtype, D, Hq, Hkv, ctxs, steps, windows, qsig=None, div=0, pair
 
 def test_decode_bytes_do_not_depend_on_the_batch():
     """A sequence's decode output is the same bytes alone (3 splits in the workspace) and
-    beside a sequence long enough that the workspace holds more than 16 splits, which the
-    merge combines with its general loop instead of one round of loads; on a global and a
-    windowed layer."""
+    beside a sequence long enough that the workspace holds more than 16 splits, which another
+    merge combines; on a global and a windowed layer.  Both calls are small enough for a wave per
+    128-key unit."""
     from paper_2607_14431_amd import kvg
     dtype, D, Hq, Hkv, windows = "bf16", 128, 4, 2, (0, 700)
     L, ctxs = len(windows), [1500, 9000]

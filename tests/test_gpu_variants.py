@@ -150,16 +150,20 @@ def test_decode_units(dtype, D, Hq, Hkv, ctxs, steps, windows):
     _decode_case(dtype, D, Hq, Hkv, ctxs, steps, windows)
 
 
-@pytest.mark.parametrize("dtype,D,window", [("bf16", 256, 0), ("bf16", 128, 700), ("fp8", 256, 100), ("fp8", 64, 0)])
-def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window):
-    """Six sequences together take a wave per split, each alone a wave per 128-key unit.  Same
-    bytes, for contexts of one unit to many splits."""
+@pytest.mark.parametrize("B", [12, 16])
+@pytest.mark.parametrize("dtype,D,window", [("bf16", 256, 0), ("bf16", 256, 700), ("bf16", 128, 700), ("bf16", 64, 100), ("fp8", 256, 100),
+                                            ("fp8", 128, 0), ("fp8", 64, 700)])
+def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window, B):
+    """B sequences together take a wave per split (rows of 256 bytes and more: with 12 sequences two stages in flight,
+    with 16 three), each alone a wave per 128-key unit, or, in a call of its own length below 256 keys, a wave per
+    split that needs no merge.  Same bytes, for contexts of one unit to many splits."""
     import torch
 
     from gpu_helpers import TORCH_DTYPE
     from paper_2607_14431_amd import kvg
-    L, Hq, Hkv, ctxs = 2, 4, 2, [0, 100, 130, 511, 512, 9000]
-    B, per_seq = len(ctxs), (max(ctxs) + 16) // 16
+    L, Hq, Hkv, long = 2, 8, 4, 9000
+    ctxs = [0, 100, 130, 511, 512, long, 255, 256, 127, 1023, 1200, 3000][:B] + [600] * (B - 12)
+    per_seq = (long + 16) // 16
     g = torch.Generator(device="cuda").manual_seed(D + window)
     cache = kvg.Cache.allocate(L, B * per_seq, Hq, Hkv, D, TORCH_DTYPE[dtype], windows=(window, 0))
     for pool in (cache.k_pool, cache.v_pool):
@@ -169,17 +173,28 @@ def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window):
     start = torch.full((B,), 777, dtype=torch.int64, device="cuda")
     raw = [torch.randn((L, B, 1, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv)]
 
-    def decode(rows):
-        seqs = kvg.Seqs(tables[rows].contiguous(), lens[rows].contiguous(), start[rows].contiguous(), max(ctxs))
+    def splits(n_seqs, max_ctx):                      # of the call: a windowed layer's are those its window touches
+        n = (max_ctx + 512) // 512
+        return n_seqs * Hkv * (n + (min(n, (window + 511) // 512) if window else n))
+
+    def decode(rows, max_ctx):
+        seqs = kvg.Seqs(tables[rows].contiguous(), lens[rows].contiguous(), start[rows].contiguous(), max_ctx)
         out = torch.full((L, len(rows), 1, Hq, D), float("nan"), device="cuda")
         ws = kvg.decode_workspace(cache, seqs, L)
         kvg.kvg_decode_attn(cache, seqs, kvg.rope(), 0, L, *(t[:, rows].contiguous() for t in raw), D ** -0.5, out, ws)
         return out
 
-    together = decode(list(range(B)))
+    row_bytes = D * cache.k_pool.element_size()
+    resident = 1280 if row_bytes >= 256 else 2560     # one-wave workgroups
+    n = splits(B, long)
+    assert n * 4 > resident >= splits(1, long) * 4
+    assert row_bytes < 256 or (768 < n < 2304 and 0 < n % 768 <= 256) == (B == 12)
+    together = decode(list(range(B)), long)
     assert torch.isfinite(together).all()
     for b in range(B):
-        assert torch.equal(together[:, b:b + 1].view(torch.int32), decode([b]).view(torch.int32)), f"context {ctxs[b]}"
+        want = together[:, b:b + 1].view(torch.int32)
+        assert torch.equal(want, decode([b], long).view(torch.int32)), f"context {ctxs[b]}"
+        assert torch.equal(want, decode([b], ctxs[b]).view(torch.int32)), f"context {ctxs[b]} in a call of its length"
 
 
 # Two waves per 64 leaves (up to 512 x 64 leaves of equal length): one set and two sets a workgroup, partial
@@ -312,10 +327,10 @@ def test_decode_merges_agree(dtype, D):
     every = list(range(B))
     together, rows, splits = decode(every)
     assert torch.isfinite(together).all() and rows > 512 and splits > 16
-    some, few_splits = every[10:], every[:10]
-    for part, want in ((some, lambda r, s: r <= 512 and s > 16 and len(some) * Hkv * s * 4 > 1280),
-                       (few_splits, lambda r, s: s <= 16 and len(few_splits) * Hkv * s * 4 > 1280),
-                       ([3], lambda r, s: Hkv * s * 4 <= 1280), ([B - 1], lambda r, s: Hkv * s * 4 <= 1280)):
+    some, few_splits = every[10:], every[:11]
+    for part, want in ((some, lambda r, s: r <= 512 and s > 16 and len(some) * Hkv * s * 4 > 2560),
+                       (few_splits, lambda r, s: s <= 16 and len(few_splits) * Hkv * s * 4 > 2560),
+                       ([3], lambda r, s: 1 < s <= 4), ([B - 1], lambda r, s: s > 16 and Hkv * s * 4 <= 1280)):
         out, r, s = decode(part)
         assert want(r, s)
         assert torch.equal(out.view(torch.int32), together[:, part].view(torch.int32)), part
