@@ -96,6 +96,31 @@ bool f32_solo(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t r
   return n_wg <= kF32SoloWorkgroups && (int64_t)s->max_ctx_len + rows > kSplit / kvg::kF32Units;
 }
 
+// Small fp32 prefills take two (row, query head) pairs a workgroup on the vector ALUs (the same bytes): while their
+// waves (two a workgroup), each unit of the keys counted as 64 more for its merge, are few, where a tile's
+// matrix work is mostly padding or sits on few CUs.  us with tiles / pairs at head_dim 64 (4 heads over 2): 1 x 64 rows
+// over 100 keys, 512 waves, 20.4 / 18.4; 1 x 16 over 1k, 576, 20.2 / 17.5; 4 layers x 4 x 16 rows over 100, 1,024, 23.4 /
+// 17.8; 4 x 4 x 2 over 1k, 1,024, 17.7 / 19.5; 1 x 8 over 8k, 2,016, 26.3 / 31.9; with 8 KV heads of one query head, 4 x 4
+// x 8 over 31, 1,024, 16.4 / 23.9.  128 (16 over 4): 1 x 16 over 100, 256, 36 / 20; 4 x 4 x 2 over 100, 512, 31 / 29;
+// 1 x 1 over 8k, 1,008, 30 / 35.  256 (16 over 8): 1 x 4 over 31, 64, 36 / 19; 4 x 4 x 1 over 300, 768, 49 / 37; 1 x 8
+// over 1k, 1,152, 35 / 40.
+bool f32_narrow(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows) {
+  const int64_t tiles = ((int64_t)rows * (c->n_q_heads / c->n_kv_heads) + 1) / 2;
+  const int64_t units = ((int64_t)s->max_ctx_len + rows + kSplit / kvg::kF32Units - 1) / (kSplit / kvg::kF32Units);
+  const int64_t heads = (int64_t)n_layers * s->batch;
+  if (heads > 1024 || tiles > 1024 || units > 1024) return false;      // the products below fit 64 bits
+  const int64_t kv = heads * c->n_kv_heads;
+  const int64_t limit = c->head_dim == 256 ? 1024 : c->head_dim == 128 || kv > 64 ? 640 : 1152;
+  return 2 * kv * tiles * units + 64 * units <= limit;
+}
+
+// How the call runs, given a large enough workspace.
+kvg::F32Form f32_form(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows) {
+  return f32_narrow(c, s, n_layers, rows) ? kvg::F32Form::kNarrow
+         : f32_solo(c, s, n_layers, rows) ? kvg::F32Form::kUnits
+                                          : kvg::F32Form::kSplits;
+}
+
 F32Ws f32_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, int32_t rows, bool solo) {
   F32Ws w;
   const size_t nrow_heads = (size_t)n_layers * s->batch * rows * c->n_q_heads;
@@ -172,8 +197,10 @@ int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t l
   if (ws == nullptr || ws_bytes < f32_ws(c, s, n_layers, rows, false).total) return KVG_E_WORKSPACE;
   // the bytes are the same either way: a workspace made for a longer chunk, which takes a workgroup
   // per split, may be too small for a shorter one's units
-  const bool solo = f32_solo(c, s, n_layers, rows) && ws_bytes >= f32_ws(c, s, n_layers, rows, true).total;
-  const F32Ws w = f32_ws(c, s, n_layers, rows, solo);
+  kvg::F32Form form = f32_form(c, s, n_layers, rows);
+  if (form != kvg::F32Form::kSplits && ws_bytes < f32_ws(c, s, n_layers, rows, true).total) form = kvg::F32Form::kSplits;
+  const bool units = form != kvg::F32Form::kSplits;
+  const F32Ws w = f32_ws(c, s, n_layers, rows, units);
   kvg::PrefillArgs a;
   std::memset(&a, 0, sizeof(a));
   a.k_pool = c->k_pool;
@@ -198,7 +225,7 @@ int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t l
   a.n_qt = (int)(((int64_t)rows * a.group + 31) / 32);
   a.n_split_max = n_split_max(s, rows);
   fill_windows(c, layer0, n_layers, a.window);
-  if (solo || a.n_split_max > 1) {
+  if (units ? (int64_t)s->max_ctx_len + rows > kSplit / kvg::kF32Units : a.n_split_max > 1) {
     a.part_acc = reinterpret_cast<float*>(static_cast<char*>(ws) + w.q);
     a.part_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + w.q + w.acc);
   }
@@ -207,7 +234,7 @@ int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t l
   ap.q_raw = q_raw;
   ap.q_out = ws;
   const int st = hip_status(kvg::launch_append(ap, c->dtype, stream));
-  return st == KVG_OK ? hip_status(kvg::launch_prefill_f32(a, solo, stream)) : st;
+  return st == KVG_OK ? hip_status(kvg::launch_prefill_f32(a, form, stream)) : st;
 }
 
 // Workspace of the decode kernels: the split partials.
@@ -580,7 +607,7 @@ size_t kvg_prefill_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs,
   if (check_cache(cache) != KVG_OK || seqs == nullptr || n_layers <= 0 || chunk_len <= 0 || seqs->batch <= 0)
     return 0;
   if (use_mfma(cache)) return mfma_ws(cache, seqs, n_layers, chunk_len);
-  return f32_ws(cache, seqs, n_layers, chunk_len, f32_solo(cache, seqs, n_layers, chunk_len)).total;
+  return f32_ws(cache, seqs, n_layers, chunk_len, f32_form(cache, seqs, n_layers, chunk_len) != kvg::F32Form::kSplits).total;
 }
 
 int kvg_prefill_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope, int32_t layer0,

@@ -20,10 +20,15 @@ hipError_t launch_graft(const CopyArgs& a, int dtype, hipStream_t stream);
 // relocated), for the host's launch-size checks
 int64_t copy_workgroups(const CopyArgs& a, int dtype);
 // the prefill of an fp32 cache (kvg_prefill_f32.hip): a.q holds fp32 queries, a.n_qt 32-pair tiles,
-// a.n_split_max kSplit-key splits; partials (a.part_acc) where there are several, or units of splits
-// (solo: a workgroup per unit, kF32Units partials a split)
+// a.n_split_max kSplit-key splits.  Partials (a.part_acc) where there are several splits, or, with a workgroup per
+// unit (kF32Units a split), several units
 constexpr int kF32Units = 4;
-hipError_t launch_prefill_f32(const PrefillArgs& a, bool solo, hipStream_t stream);
+enum class F32Form {
+  kSplits,    // a workgroup per split
+  kUnits,     // a workgroup per unit
+  kNarrow,    // a workgroup per unit and a few (row, query head) pairs, on the vector ALUs
+};
+hipError_t launch_prefill_f32(const PrefillArgs& a, F32Form form, hipStream_t stream);
 inline int64_t prefill_f32_workgroups(const PrefillArgs& a) {
   return (int64_t)a.n_layers * a.batch * a.Hkv * a.n_split_max * a.n_qt;
 }

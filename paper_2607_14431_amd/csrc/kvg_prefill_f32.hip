@@ -23,8 +23,9 @@
 // registers, a few loads ahead, K through LDS up to head_dim 128 (V through LDS too would leave one workgroup
 // a CU).  4 layers x 2 x 256 rows x 4 heads over 1k keys, head_dim 64: 169 us a pass on the vector ALUs, where
 // every row read all its keys again; 70 here, 57 of them this kernel; 512 rows over 4k keys, 8 KV heads x
-// 256: 4,627 -> 698.  One row over 8k keys costs more than it did (24 -> 27 us at head_dim 64, 39 -> 74 at
-// 256): 31 of the tile's 32 pairs are padding.
+// 256: 4,627 -> 698.  A few rows over many keys cost more than there, because most of a tile's 32 pairs are padding:
+// one row over 8k keys 21 -> 24 us at head_dim 64 (2 KV heads), 38 -> 58 at 256 (8), 4 layers x 4 such rows 31 -> 38 and
+// 333 -> 547.  Small calls take prefill_f32_narrow_kernel.
 #include "kvg_launch.h"
 #include "kvg_mfma.h"
 #include "kvg_rows.h"
@@ -46,8 +47,40 @@ struct FloatVec {
   float x[N];
 };
 
+__device__ __forceinline__ FloatVec<8> load8(const float* p) {
+  const FloatVec<4> a = __builtin_bit_cast(FloatVec<4>, ld16(p)), b = __builtin_bit_cast(FloatVec<4>, ld16(p + 4));
+  return {{a.x[0], a.x[1], a.x[2], a.x[3], b.x[0], b.x[1], b.x[2], b.x[3]}};
+}
+
+// tiles of P (row, query head) pairs of a sequence and KV head
+__host__ __device__ inline int narrow_tiles(const PrefillArgs& a, int P) { return (int)(((int64_t)a.chunk * a.group + P - 1) / P); }
+
+// Workgroup blockIdx.x of a grid of (tile, slot, KV head, sequence, layer), the tile fastest.  32-bit divisions: the
+// code of 64-bit ones is longer than the rest of a small kernel, and a small call waits for its code.
+struct F32Item {
+  int tile, slot, g, b, l;
+};
+__device__ __forceinline__ F32Item f32_item(const PrefillArgs& a, uint32_t n_tiles, uint32_t n_slots) {
+  uint32_t id = blockIdx.x;
+  F32Item it;
+  it.tile = (int)(id % n_tiles);
+  id /= n_tiles;
+  it.slot = (int)(id % n_slots);
+  id /= n_slots;
+  it.g = (int)(id % (uint32_t)a.Hkv);
+  id /= (uint32_t)a.Hkv;
+  it.b = (int)(id % (uint32_t)a.batch);
+  it.l = (int)(id / (uint32_t)a.batch);
+  return it;
+}
+
 // v f_v + x f_x, rounded alike wherever states are folded
 __device__ __forceinline__ float fold(float v, float f_v, float x, float f_x) { return fmaf(x, f_x, v * f_v); }
+
+// a key's weight in its block, whose reference is m_ref
+__device__ __forceinline__ float block_weight(float score, float scale_log2, float m_ref) {
+  return __builtin_amdgcn_exp2f(fmaf(score, scale_log2, -m_ref));
+}
 
 // Folds the state (pm, pl, pv) of the keys that follow into (m, l, v); (-inf, 0, 0) is the empty one.
 __device__ __forceinline__ void fold_state(float& m, float& l, float& v, float pm, float pl, float pv) {
@@ -77,23 +110,17 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillA
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lrow = lane & 31, half = lane >> 5;
   const int G = a.group;
-  int64_t id = blockIdx.x;
-  const int tile = a.n_qt - 1 - (int)(id % a.n_qt);
-  id /= a.n_qt;
   const int n_slots = a.n_split_max * (kSolo ? kF32Units : 1);
-  const int slot = (int)(id % n_slots);                        // split, or unit of one
-  id /= n_slots;
-  const int g = (int)(id % a.Hkv);
-  id /= a.Hkv;
-  const int b = (int)(id % a.batch);
-  const int l = (int)(id / a.batch);
+  const F32Item it = f32_item(a, a.n_qt, n_slots);
+  const int tile = a.n_qt - 1 - it.tile, slot = it.slot, g = it.g, b = it.b, l = it.l;   // slot: split, or unit of one
   const int ctx = a.ctx_lens[b];
   if (ctx < 0 || ctx > a.max_ctx_len) return;
 
   const int pair = tile * 32 + lrow;
-  const int row = pair / G, h = g * G + pair % G;
+  const int lg = 31 - __builtin_clz(G);                        // G is 1, 2, 4 or 8
+  const int row = pair >> lg, h = g * G + (pair & (G - 1));
   const bool row_ok = row < a.chunk;
-  const int first = tile * 32 / G, last = min((tile * 32 + 31) / G, a.chunk - 1);
+  const int first = tile * 32 >> lg, last = min(tile * 32 + 31 >> lg, a.chunk - 1);
   const int W = layer_window(a, l);
   const int row_n = ctx + row, row_lo = window_start(W, row_n + 1);
   const int mask_lo = window_start(W, ctx + last + 1);        // keys below it are masked for some row
@@ -284,7 +311,7 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillA
       float psum = 0.0f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        s[r] = __builtin_amdgcn_exp2f(s[r] * a.scale_log2 - m_ref);
+        s[r] = block_weight(s[r], a.scale_log2, m_ref);
         psum += s[r];
       }
       const float2 ph = halves32(psum);
@@ -348,7 +375,7 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillA
   __syncthreads();
   for (int t = threadIdx.x; t < 32 * D; t += 64 * kWaves) {
     const int p = t / D, d = t % D;
-    const int prow = (tile * 32 + p) / G, ph = g * G + (tile * 32 + p) % G;
+    const int prow = tile * 32 + p >> lg, ph = g * G + (tile * 32 + p & (G - 1));
     if (prow >= a.chunk) break;
     float m = -INFINITY, lsum = 0.0f, v = 0.0f;
 #pragma unroll
@@ -364,30 +391,247 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_f32_kernel(const PrefillA
   }
 }
 
+// Small calls: P pairs at a time on the vector ALUs, with the operations of a 32-pair tile in its order (the matrix
+// cores' step is an fma chain, lanes 0-31's product first), so with its bytes.  Workgroup = (layer, sequence,
+// KV head, tile of P pairs, unit of 128 keys), two waves of 64 keys: a key per lane for the scores, then the weights
+// through LDS and D / 64 dimensions a lane for the values.  A tile's 32 pairs are mostly padding in such calls, its
+// waves run their blocks one after the other, and its code (20 to 77 KB) takes longer to arrive than the work: what
+// bounds this one is the round trips (page, K and V rows requested together, the rest of K) and its 10 to 14 KB.
+// Queries as scalar loads, a miss each, cost 5 us more at head_dim 256; eight pairs a workgroup, 40 KB of code, 20.
+template <int D, int P>
+__global__ __launch_bounds__(128) void prefill_f32_narrow_kernel(const PrefillArgs a) {
+  constexpr int E = D / 64;                                    // dimensions per lane
+  constexpr int LK = 8;                                        // K loads ahead, 8 dimensions each
+  __shared__ __attribute__((aligned(16))) float s_q[P][D];
+  __shared__ __attribute__((aligned(16))) float s_p[2][P][64];
+  __shared__ float s_o[2][P][D];                               // wave 1's blocks
+  __shared__ float2 s_ml[2][P];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int G = a.group, lg = 31 - __builtin_clz(G);
+  const int n_nt = narrow_tiles(a, P);
+  const int n_slots = a.n_split_max * kF32Units;
+  const F32Item it = f32_item(a, n_nt, n_slots);
+  const int tile = it.tile, slot = it.slot, g = it.g, b = it.b, l = it.l;
+  const int ctx = a.ctx_lens[b];
+  if (ctx < 0 || ctx > a.max_ctx_len) return;
+  const int W = layer_window(a, l);
+  const int first = tile * P >> lg, last = min(tile * P + P - 1 >> lg, a.chunk - 1);
+  const int tile_lo = window_start(W, ctx + first + 1), tile_hi = ctx + last + 1;
+  if (slot * kUnitKeys >= tile_hi || (slot + 1) * kUnitKeys <= tile_lo) return;
+  const int mask_lo = window_start(W, ctx + last + 1);         // keys below it are masked for some row
+
+  const int64_t lbase = (int64_t)(a.layer0 + l) * a.layer_elems;
+  const float* kpool = reinterpret_cast<const float*>(a.k_pool) + lbase;
+  const float* vpool = reinterpret_cast<const float*>(a.v_pool) + lbase;
+  const int key0 = slot * kUnitKeys + 64 * wave;               // lane's key: key0 + lane
+  const int key = key0 + lane;
+  int32_t page = a.block_tables[(int64_t)b * a.max_pages + min(key, tile_hi - 1) / kPage];
+  page = (page >= 0 && page < a.n_pages) ? page : 0;
+  const int64_t slab = ((int64_t)page * a.Hkv + g) * kPage;    // the lane's key's (page, head)
+
+  // pair p's row and query (a pair past the chunk takes the last row's and is not written)
+  auto row_of = [&](int p) { return min(tile * P + p >> lg, a.chunk - 1); };
+  auto head_row = [&](int p) -> int64_t {
+    return (((int64_t)l * a.batch + b) * a.chunk + row_of(p)) * a.Hq + g * G + (tile * P + p & (G - 1));
+  };
+  // V rows of a block, requested before its weights are known.  Rows past tile_hi are rows of a page of the pool
+  // that no pair sees.
+  FloatVec<E> v[32];
+  auto vfetch = [&](int blk) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int64_t pg = __builtin_amdgcn_readlane(page, 32 * blk + kPage * x);
+      const float* vr = vpool + (pg * a.Hkv + g) * kPage * D + E * lane;
+#pragma unroll
+      for (int k = 0; k < kPage; ++k) v[kPage * x + k] = *reinterpret_cast<const FloatVec<E>*>(vr + k * D);
+    }
+  };
+  float m_blk[P], w[P];
+  const bool any_key = key0 < tile_hi && key0 + 64 > tile_lo;
+  // the queries, 16 bytes a thread; the K and V rows are requested before they are waited for
+  constexpr int NQ = P * D / 4;
+  uint4 q_raw = make_uint4(0, 0, 0, 0);
+  static_assert(NQ <= 128, "a chunk of the queries per thread");
+  if ((int)threadIdx.x < NQ) {
+    int64_t qr = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) qr = (int)threadIdx.x / (D / 4) == p ? head_row(p) : qr;
+    q_raw = ld16(reinterpret_cast<const float*>(a.q) + qr * D + 4 * (threadIdx.x % (D / 4)));
+  }
+  FloatVec<8> kf[LK];
+  const float* kr = kpool + (slab + lane % kPage) * D;
+  if (any_key) {
+#pragma unroll
+    for (int j = 0; j < LK; ++j) kf[j] = load8(kr + 8 * j);
+    vfetch(0);
+  }
+  if ((int)threadIdx.x < NQ) st16(&s_q[0][0] + 4 * threadIdx.x, q_raw);
+  __syncthreads();
+  if (any_key) {
+    float c[P][4];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) c[p][x] = 0.0f;
+#pragma unroll 1
+    for (int j0 = 0; j0 < D / 8; j0 += LK) {
+#pragma unroll
+      for (int x = 0; x < LK; ++x) {
+        const FloatVec<8> k = kf[x];
+        kf[x] = load8(kr + 8 * min(j0 + x + LK, D / 8 - 1));
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+          const FloatVec<8> q = load8(&s_q[p][8 * (j0 + x)]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            c[p][x % 4] = fmaf(k.x[e], q.x[e], c[p][x % 4]);
+            c[p][x % 4] = fmaf(k.x[e + 4], q.x[e + 4], c[p][x % 4]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const int row_n = ctx + row_of(p);
+      const float s = (c[p][0] + c[p][1]) + (c[p][2] + c[p][3]);
+      w[p] = key <= row_n && key >= window_start(W, row_n + 1) ? s : -INFINITY;
+      float mx = w[p];
+#pragma unroll
+      for (int x = 16; x >= 1; x >>= 1) mx = fmaxf(mx, __shfl_xor(mx, x));
+      m_blk[p] = mx * a.scale_log2;                            // of the lane's half: its block's
+      const float m_ref = m_blk[p] == -INFINITY ? 0.0f : m_blk[p];
+      s_p[wave][p][lane] = block_weight(w[p], a.scale_log2, m_ref);
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      m_blk[p] = -INFINITY;
+      s_p[wave][p][lane] = 0.0f;
+    }
+  }
+  __syncthreads();
+
+  // the wave's two blocks: (reference, sum, O) each
+  float m[P], lsum[P], o[P][E];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    m[p] = -INFINITY;
+    lsum[p] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[p][e] = 0.0f;
+  }
+#pragma unroll 1
+  for (int blk = 0; blk < 2; ++blk) {
+    const int kb = key0 + 32 * blk;
+    float ps[P][2], ob[P][E];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      ps[p][0] = ps[p][1] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < E; ++e) ob[p][e] = 0.0f;
+    }
+    // a key that a pair does not see adds 0 times 0, whatever its values are
+    const bool masked = kb + 31 > ctx + first || kb < mask_lo;
+    auto octet = [&](int k8) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const float4 wa = *reinterpret_cast<const float4*>(&s_p[wave][p][32 * blk + k8]);
+        const float4 wb = *reinterpret_cast<const float4*>(&s_p[wave][p][32 * blk + k8 + 4]);
+        const float wt[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+        const int row_n = ctx + row_of(p), row_lo = window_start(W, row_n + 1);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            const int x = t + 4 * hf, kk = kb + k8 + x;
+            const bool sees = !masked || (kk <= row_n && kk >= row_lo);
+            ps[p][hf] += wt[x];
+#pragma unroll
+            for (int e = 0; e < E; ++e) ob[p][e] = fmaf(sees ? v[k8 + x].x[e] : 0.0f, wt[x], ob[p][e]);
+          }
+      }
+    };
+    if (kb < tile_hi && kb + 32 > tile_lo) {
+#pragma unroll
+      for (int k8 = 0; k8 < 32; k8 += 8) octet(k8);
+    }
+    if (blk == 0) vfetch(1);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const float mb = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m_blk[p]), 32 * blk));
+      const float lb = ps[p][0] + ps[p][1];
+      if (wave == 0) {
+        const float m_new = fmaxf(m[p], mb), f = merge_factor(m[p], m_new), fb = merge_factor(mb, m_new);
+        lsum[p] = fold(lsum[p], f, lb, fb);
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[p][e] = fold(o[p][e], f, ob[p][e], fb);
+        m[p] = m_new;
+      } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) s_o[blk][p][E * lane + e] = ob[p][e];
+        if (lane == 0) s_ml[blk][p] = make_float2(mb, lb);
+      }
+    }
+  }
+  __syncthreads();
+  if (wave == 1) return;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      const float2 ml = s_ml[blk][p];
+      const float m_new = fmaxf(m[p], ml.x), f = merge_factor(m[p], m_new), fb = merge_factor(ml.x, m_new);
+      lsum[p] = fold(lsum[p], f, ml.y, fb);
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[p][e] = fold(o[p][e], f, s_o[blk][p][E * lane + e], fb);
+      m[p] = m_new;
+    }
+    if (tile * P + p >= a.chunk * G) break;
+    const int64_t rh = head_row(p);
+    FloatVec<E> out;
+    if (a.part_acc == nullptr) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) out.x[e] = o[p][e] / lsum[p];
+      *reinterpret_cast<FloatVec<E>*>(a.out + rh * D + E * lane) = out;
+    } else {
+      const int64_t pidx = rh * n_slots + slot;
+#pragma unroll
+      for (int e = 0; e < E; ++e) out.x[e] = o[p][e];
+      *reinterpret_cast<FloatVec<E>*>(a.part_acc + pidx * D + E * lane) = out;
+      if (lane == 0) *reinterpret_cast<float2*>(a.part_ml + pidx * 2) = make_float2(m[p], lsum[p]);
+    }
+  }
+}
+
 // The units' partials of a row in the order the one-workgroup split takes them, then the splits as
 // combine_splits does.  One element per lane.
-__global__ __launch_bounds__(256) void prefill_f32_units_kernel(const PrefillArgs a, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// NS: splits whose loads are in flight.
+template <int NS>
+__global__ __launch_bounds__(256) void prefill_f32_units_kernel(const PrefillArgs a, uint32_t n) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  const int64_t row_head = i / a.D;
-  const int row = (int)((row_head / a.Hq) % a.chunk);
-  const int b = (int)((row_head / ((int64_t)a.Hq * a.chunk)) % a.batch);
-  const int l = (int)(row_head / ((int64_t)a.Hq * a.chunk * a.batch));
+  const uint32_t D = a.D, row_head = i / D;
+  uint32_t id = row_head / (uint32_t)a.Hq;
+  const int row = (int)(id % (uint32_t)a.chunk);
+  id /= (uint32_t)a.chunk;
+  const int b = (int)(id % (uint32_t)a.batch), l = (int)(id / (uint32_t)a.batch);
   const int ctx = a.ctx_lens[b];
   if (ctx < 0 || ctx > a.max_ctx_len) return;
   const int n_keys = ctx + row + 1;
   const int u0 = window_start(layer_window(a, l), n_keys) / kUnitKeys, u1 = (n_keys - 1) / kUnitKeys;
-  const int64_t p0 = row_head * a.n_split_max * kF32Units;
+  const int64_t p0 = (int64_t)row_head * a.n_split_max * kF32Units;
   const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + p0;
-  const float* acc = a.part_acc + p0 * a.D + i % a.D;
-  constexpr int NS = 2, U = NS * kF32Units;                    // splits and units whose loads are in flight
+  const float* acc = a.part_acc + p0 * D + i % D;
+  constexpr int U = NS * kF32Units, M = 2 * U;                 // units whose loads are in flight
   float m = -INFINITY;
-  for (int u = u0; u <= u1; u += U) {
-    float mv[U];
+  for (int u = u0; u <= u1; u += M) {
+    float mv[M];
 #pragma unroll
-    for (int x = 0; x < U; ++x) mv[x] = ml[min(u + x, u1)].x;
+    for (int x = 0; x < M; ++x) mv[x] = ml[min(u + x, u1)].x;
 #pragma unroll
-    for (int x = 0; x < U; ++x) m = fmaxf(m, mv[x]);
+    for (int x = 0; x < M; ++x) m = fmaxf(m, mv[x]);
   }
   float lsum = 0.0f, o = 0.0f;
   for (int s = u0 / kF32Units; s <= u1 / kF32Units; s += NS) {
@@ -415,6 +659,19 @@ __global__ __launch_bounds__(256) void prefill_f32_units_kernel(const PrefillArg
   a.out[i] = o / lsum;
 }
 
+hipError_t launch_narrow(const PrefillArgs& a, hipStream_t stream) {
+  constexpr int P = 2;
+  const int64_t n_wg = (int64_t)a.n_layers * a.batch * a.Hkv * a.n_split_max * kF32Units * narrow_tiles(a, P);
+  const dim3 grid((unsigned)n_wg);
+  switch (a.D) {
+    case 64: prefill_f32_narrow_kernel<64, P><<<grid, 128, 0, stream>>>(a); break;
+    case 128: prefill_f32_narrow_kernel<128, P><<<grid, 128, 0, stream>>>(a); break;
+    case 256: prefill_f32_narrow_kernel<256, P><<<grid, 128, 0, stream>>>(a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 template <bool kSolo>
 hipError_t launch(const PrefillArgs& a, hipStream_t stream) {
   const dim3 grid((unsigned)(prefill_f32_workgroups(a) * (kSolo ? kF32Units : 1)));
@@ -429,12 +686,20 @@ hipError_t launch(const PrefillArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_prefill_f32(const PrefillArgs& a, bool solo, hipStream_t stream) {
-  const hipError_t e = solo ? launch<true>(a, stream) : launch<false>(a, stream);
+hipError_t launch_prefill_f32(const PrefillArgs& a, F32Form form, hipStream_t stream) {
+  const hipError_t e = form == F32Form::kNarrow ? launch_narrow(a, stream)
+                       : form == F32Form::kUnits ? launch<true>(a, stream)
+                                                 : launch<false>(a, stream);
   if (e != hipSuccess || a.part_acc == nullptr) return e;
-  if (!solo) return launch_prefill_segments(a, stream);
-  const int64_t n = (int64_t)a.n_layers * a.batch * a.chunk * a.Hq * a.D;
-  prefill_f32_units_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, stream>>>(a, n);
+  if (form == F32Form::kSplits) return launch_prefill_segments(a, stream);
+  const int64_t n = (int64_t)a.n_layers * a.batch * a.chunk * a.Hq * a.D;   // few workgroups: below 2^31
+  const dim3 grid((unsigned)((n + 255) / 256));
+  // one row over 8k keys 26 -> 24 us with four splits at a time; over 1k keys 15.6 with two, 16.5 with four, for the
+  // code is longer
+  if (a.n_split_max <= 4)
+    prefill_f32_units_kernel<2><<<grid, 256, 0, stream>>>(a, (uint32_t)n);
+  else
+    prefill_f32_units_kernel<4><<<grid, 256, 0, stream>>>(a, (uint32_t)n);
   return hipGetLastError();
 }
 

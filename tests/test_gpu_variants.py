@@ -85,6 +85,41 @@ def test_f32_prefill_unit_per_workgroup():
         run(3, 1, small - 1)
 
 
+# Small fp32 calls take two (row, head) pairs a workgroup on the vector ALUs: the bytes of the same rows in a call of
+# 32-pair tiles.  Odd pair counts, blocks and units partly and wholly masked, one unit (no combine) and several.
+@pytest.mark.parametrize("D,Hq,Hkv", [(64, 4, 2), (64, 3, 3), (128, 8, 1), (128, 4, 2), (256, 2, 2), (256, 8, 1)])
+@pytest.mark.parametrize("window", [0, 1, 40, 200])
+def test_f32_prefill_pairs_are_tiles(D, Hq, Hkv, window):
+    import torch
+
+    from paper_2607_14431_amd import kvg
+    G, long = Hq // Hkv, 400
+    for ctx in (0, 30, 31, 97, 127, 128, 300, 505):
+        n_pages = (ctx + long + 15) // 16
+        g = torch.Generator(device="cuda").manual_seed(ctx)
+        cache = kvg.Cache.allocate(1, n_pages, Hq, Hkv, D, torch.float32, windows=(window,))
+        for pool in (cache.k_pool, cache.v_pool):
+            pool.normal_(generator=g)
+            pool[:, ctx // 16 + 1:] = float("nan")        # nothing beyond the chunk is read into a result
+        table = torch.arange(n_pages, dtype=torch.int32, device="cuda")[None]
+        seqs = kvg.Seqs(table, torch.tensor([ctx], dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda"), ctx)
+        q, k, v = (torch.randn((1, 1, long, h, D), device="cuda", generator=g) for h in (Hq, Hkv, Hkv))
+
+        def run(rows):
+            units = (ctx + rows + 127) // 128
+            assert (2 * Hkv * ((rows * G + 1) // 2) * units + 64 * units <= {64: 1152, 128: 640, 256: 1024}[D]) == (rows < long)
+            out = torch.full((1, 1, rows, Hq, D), float("nan"), device="cuda")
+            ws = torch.empty(kvg.kvg_prefill_workspace_bytes(cache, seqs, 1, rows), dtype=torch.uint8, device="cuda")
+            kvg.kvg_prefill_attn(cache, seqs, kvg.rope(), 0, 1, rows, *(x[:, :, :rows].contiguous() for x in (q, k, v)), 3.0 * D ** -0.5, out, ws)
+            return out
+
+        small = [(rows, run(rows)) for rows in (1, 2, 5, 7)]
+        together = run(long)
+        assert torch.isfinite(together).all()
+        for rows, out in small:
+            assert torch.equal(out, together[:, :, :rows]), (ctx, rows)
+
+
 # The comparison's single pass: a wave, 4 and 16 waves a row, rows read as vectors and element by element, fewer elements
 # than lanes, references that have to be raised (spread > e^300), infinities.
 @pytest.mark.parametrize("rows,V,scale", [(1, 1, 1.0), (3, 7, 1.0), (2, 64, 1.0), (3, 4095, 5.0), (2, 4100, 5.0),
