@@ -237,7 +237,6 @@ int attn_f32(const kvg_cache* c, const kvg_seqs* s, const kvg_rope* r, int32_t l
   return st == KVG_OK ? hip_status(kvg::launch_prefill_f32(a, form, stream)) : st;
 }
 
-// Workspace of the decode kernels: the split partials.
 // bf16 and fp8 caches take the bf16 matrix cores.  8 query heads per KV head (2 layers x 3 x 300 rows
 // over 1.6k keys) took 1,153 us on the vector ALUs, which read every key again for every row,
 // 114 us on MFMA.
@@ -285,25 +284,27 @@ DecodeGrid decode_grid(const kvg_cache* c, const kvg_seqs* s, int32_t layer0, in
 // 41; 8 (592): 56 and 63.  Not below two units' keys: a wave per split then has few more keys than a wave per
 // unit, and one split needs no merge (4 layers x 8 sequences over 200 keys, head_dim 128: 12.7 us against 17.4; over 300
 // keys 16.1 and 17.4, but 24 layers of one sequence at head_dim 256 24.3 and 21.2).  A windowed layer's splits are
-// those its window can touch.
+// those its window can touch.  Beside shared splits, which keep their one partial, where no layer has a window and
+// from one unit's keys on, for the merge is there anyway (one 12B-class layer, 4 sequences: 4,600 keys of which 4,096
+// shared, 63 us with a wave per own split, 43; 30,100 of 30,000, 88 and 73; 16 sequences, 1,204 of 1,104, 46 and 44).
 int solo_waves(const kvg_cache* c) {
   return 256 * (kvg::kLdsBytes / (2 * kvg::decode_stage_bytes(c->head_dim * (int)elem_bytes(c))));
 }
 bool decode_solo(const kvg_cache* c, const kvg_seqs* s, const DecodeGrid& grid) {
-  const int waves = solo_waves(c);
-  return c->dtype != KVG_F32 && shared_splits(c, s) == 0 && s->max_ctx_len >= 2 * kvg::kUnit && grid.items * 4 <= waves &&
-         n_split_max(s, 1) <= waves / 4;
+  const int waves = solo_waves(c), shared = shared_splits(c, s);
+  return c->dtype != KVG_F32 && (shared == 0 || grid.n_split_win == 0) && s->max_ctx_len - shared * kSplit >= (shared > 0 ? 1 : 2) * kvg::kUnit &&
+         grid.items * 4 <= waves && n_split_max(s, 1) <= waves / 4;
 }
 
 struct DecodeWs {
   size_t ml, acc, q, total;
 };
 
-// Split partials (`per_split` of each), and the rotated bf16 queries of the shared-split kernel when
-// it runs.
-DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, size_t per_split = 1) {
+// Split partials (units: of the units of the splits that are not shared), and the rotated bf16 queries of the
+// shared-split kernel when it runs.
+DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, bool units = false) {
   DecodeWs w;
-  const size_t ns = (size_t)n_split_max(s, 1) * per_split;
+  const size_t ns = units ? kvg::unit_slots(n_split_max(s, 1), shared_splits(c, s)) : n_split_max(s, 1);
   const size_t heads = (size_t)n_layers * s->batch * c->n_q_heads;
   w.ml = align_up(heads * ns * 2 * sizeof(float));
   w.acc = align_up(heads * ns * c->head_dim * sizeof(float));
@@ -312,15 +313,23 @@ DecodeWs decode_ws(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers, size
   return w;
 }
 
-// What the size query returns: enough for a call of this size, and for a wave per unit wherever a
+// What a call needs: enough for its size, and, without shared splits, for a wave per unit wherever a
 // call no larger than this one takes it: four partials per split of every row, which with
 // windowed layers (whose rows hold more splits than their windows have) exceed the resident
 // waves.  The same with and without windows, so one workspace serves caches of one shape.
-size_t decode_ws_bytes(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
+size_t decode_ws_needed(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
   const size_t unit_bytes = (size_t)(c->n_q_heads / c->n_kv_heads) * (c->head_dim + 2) * sizeof(float);
   const size_t layout = (size_t)n_layers * s->batch * c->n_kv_heads * n_split_max(s, 1) * 4;
   const size_t units = c->dtype == KVG_F32 ? 0 : std::min<size_t>(4 * (size_t)solo_waves(c), layout);
   return std::max(decode_ws(c, s, n_layers).total, units * unit_bytes + 2 * kAlign);
+}
+
+// What the size query returns: beside shared splits, room for a wave per unit of the others too.
+size_t decode_ws_bytes(const kvg_cache* c, const kvg_seqs* s, int32_t n_layers) {
+  const int shared = shared_splits(c, s);
+  const int64_t own = (int64_t)n_layers * s->batch * c->n_kv_heads * (n_split_max(s, 1) - shared);
+  const size_t needed = decode_ws_needed(c, s, n_layers);
+  return shared > 0 && own * 4 <= solo_waves(c) ? std::max(needed, decode_ws(c, s, n_layers, true).total) : needed;
 }
 
 // One plane of rotated bf16 queries (the workspace holds a hi and a lo plane); with shared
@@ -647,16 +656,19 @@ int decode_attn_check(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_ro
 }
 
 size_t decode_attn_ws_bytes(const kvg_cache* cache, const kvg_seqs* seqs, int32_t n_layers) {
-  return decode_ws_bytes(cache, seqs, n_layers);
+  return decode_ws_needed(cache, seqs, n_layers);
 }
 
 int decode_attn_launch(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope, int32_t layer0,
                        int32_t n_layers, const void* q_raw, const void* k_raw, const void* v_raw, float scale,
                        float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
-  const DecodeWs w = decode_ws(cache, seqs, n_layers);
-  if (ws == nullptr || ws_bytes < decode_ws_bytes(cache, seqs, n_layers)) return KVG_E_WORKSPACE;
+  if (ws == nullptr || ws_bytes < decode_ws_needed(cache, seqs, n_layers)) return KVG_E_WORKSPACE;
   const int n_split = n_split_max(seqs, 1);
   const DecodeGrid grid = decode_grid(cache, seqs, layer0, n_layers);
+  // the bytes are the same either way: a workspace without room for the units' partials (windowed layers, whose
+  // rows hold more splits than their windows touch) takes a wave per split
+  const bool solo = decode_solo(cache, seqs, grid) && ws_bytes >= decode_ws(cache, seqs, n_layers, true).total;
+  const DecodeWs w = decode_ws(cache, seqs, n_layers, solo);
   const int64_t n_blocks = grid.items;
   const int64_t n_rows = (int64_t)n_layers * seqs->batch * cache->n_q_heads;
   if (!fits_grid(n_blocks, 256) || !fits_grid(n_rows, 256) || !append_fits(seqs, 1)) return KVG_E_SHAPE;
@@ -699,11 +711,7 @@ int decode_attn_launch(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_r
   a.n_split_full = grid.n_split_full;
   a.n_split_win = grid.n_split_win;
   std::memcpy(a.layer_order, grid.order, sizeof(a.layer_order));
-  // the bytes are the same either way: a workspace whose rows hold too many splits for four
-  // partials each (windowed layers) takes a wave per split
-  const DecodeWs wu = decode_ws(cache, seqs, n_layers, 4);
-  a.solo = decode_solo(cache, seqs, grid) && ws_bytes >= wu.total;
-  if (a.solo) a.part_acc = reinterpret_cast<float*>(base + wu.ml);
+  a.solo = solo;
   a.pairing = rope->pairing;
   std::memcpy(a.theta, rope_theta(rope->base, cache->head_dim), sizeof(double) * (cache->head_dim / 2));
   if (fill_windows(cache, layer0, n_layers, a.window) != KVG_OK) return KVG_E_SHAPE;
@@ -747,7 +755,7 @@ int decode_attn_launch(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_r
     const int waves = (seqs->batch + 31) / 32 * a.group;                 // 32 sequences of one head per wave
     const int nw = kvg::prefill_mfma_waves(cache->head_dim);
     p.n_qt = (waves + nw - 1) / nw;
-    p.n_split_max = n_split;
+    p.n_split_max = solo ? kvg::unit_slots(n_split, a.n_shared_split) : n_split;
     p.n_shared_split = a.n_shared_split;
     p.shared_keys = kSplit;
     std::memcpy(p.window, a.window, sizeof(p.window));

@@ -599,7 +599,8 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(const DecodeArgs
 // and weights are worked out once, in LDS; the lane groups then bring kMergeChunk splits' values
 // at a time (every partial requested at once), and one lane per element sums them in order.
 constexpr int kMergeChunk = 32;
-template <bool kSolo, int kMergeThreads>
+// kBeside: (kSolo) beside shared splits, which have one partial.
+template <bool kSolo, int kMergeThreads, bool kBeside = false>
 __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const DecodeArgs a) {
   constexpr int U = kSolo ? 4 : 1;                         // partials per split
   const int64_t row_head = blockIdx.x;
@@ -608,16 +609,21 @@ __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const Decod
   const int D = a.D;
   const int groups = kMergeThreads / D;
   const int tid = threadIdx.x, d = tid % D, gi = tid / D;
-  const float* ml = a.part_ml + row_head * a.n_split_max * U * 2;
-  const float* acc = a.part_acc + row_head * a.n_split_max * U * D + d;
+  const int n_sh = kBeside ? a.n_shared_split : 0;
+  const int n_slots = kSolo ? unit_slots(a.n_split_max, n_sh) : a.n_split_max;
+  const float* ml = a.part_ml + row_head * n_slots * 2;
+  const float* acc = a.part_acc + row_head * n_slots * D + d;
   const int ctx = a.ctx_lens[b];
   if (ctx < 0 || ctx > a.max_ctx_len) return;
   const int win = layer_window(a, l);
   const int lo = window_start(win, ctx + 1);
   const int n_split = split_count(ctx + 1, lo);
-  if (!kSolo && n_split == 1 && !(win == 0 && a.n_shared_split > 0)) return;   // written by the split kernel
+  const bool shared = kSolo ? kBeside : win == 0 && a.n_shared_split > 0;
+  if (!kSolo && n_split == 1 && !shared) return;           // written by the split kernel
   const int n_unit = min((ctx - split_base(lo)) / kUnit + 1, 4 * n_split);   // units that hold keys (kSolo)
-  if (kSolo && n_unit == 1) return;                        // written by the split kernel
+  if (kSolo && n_unit == 1 && !shared) return;             // written by the split kernel
+  auto slot_of = [&](int s) { return kSolo ? unit_slot(s, n_sh) : s; };
+  auto has_unit = [&](int s, int u) { return s >= n_sh && s * 4 + u < n_unit; };   // kSolo, u > 0
   extern __shared__ float s_mem[];
   float* s_m = s_mem;                                      // [split] reference, then weight
   float* s_l = s_m + a.n_split_max;                        // [split] sum
@@ -627,14 +633,14 @@ __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const Decod
 
   float mx = -INFINITY;
   for (int s = tid; s < n_split; s += kMergeThreads) {
-    float2 p = *reinterpret_cast<const float2*>(ml + s * U * 2);
+    float2 p = *reinterpret_cast<const float2*>(ml + slot_of(s) * 2);
     if constexpr (kSolo) {
       float2 pu[3];
 #pragma unroll
-      for (int u = 1; u < 4; ++u) pu[u - 1] = *reinterpret_cast<const float2*>(ml + min(s * 4 + u, n_unit - 1) * 2);
+      for (int u = 1; u < 4; ++u) pu[u - 1] = *reinterpret_cast<const float2*>(ml + (slot_of(s) + (has_unit(s, u) ? u : 0)) * 2);
 #pragma unroll
       for (int u = 1; u < 4; ++u) {
-        const bool in = s * 4 + u < n_unit;
+        const bool in = has_unit(s, u);
         const float m_new = fmaxf(p.x, in ? pu[u - 1].x : p.x);
         const float f_me = merge_factor(p.x, m_new);
         const float f_o = in ? merge_factor(pu[u - 1].x, m_new) : 0.0f;
@@ -668,7 +674,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const Decod
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int s = min(s0 + k * groups, n_split - 1);
-          av[k][u] = acc[(int64_t)(kSolo ? min(s * 4 + u, n_unit - 1) : s) * D];
+          av[k][u] = acc[(int64_t)(slot_of(s) + (u > 0 && has_unit(s, u) ? u : 0)) * D];
         }
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
@@ -677,7 +683,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_splits_kernel(const Decod
         if constexpr (kSolo) {
           const float* f = s_u + min(s, n_split - 1) * 6;
 #pragma unroll
-          for (int u = 1; u < 4; ++u) v = s * 4 + u < n_unit ? fmaf(v, f[2 * (u - 1)], av[k][u] * f[2 * (u - 1) + 1]) : v;
+          for (int u = 1; u < 4; ++u) v = has_unit(s, u) ? fmaf(v, f[2 * (u - 1)], av[k][u] * f[2 * (u - 1) + 1]) : v;
         }
         if (s < min(c0 + kMergeChunk, n_split)) s_o[(s - c0) * D + d] = v;
       }
@@ -793,7 +799,9 @@ hipError_t launch_decode(const DecodeArgs& a, int dtype, hipStream_t stream) {
   if (a.n_split_max == 1 && a.n_shared_split == 0 && !a.solo) return hipSuccess;   // every row is written
   const int64_t n_rows = (int64_t)a.n_layers * a.batch * a.Hq;
   const dim3 grid((unsigned)n_rows);
-  if (a.solo && a.n_split_max <= kMergeFewSplits)
+  if (a.solo && a.n_shared_split > 0)
+    merge_splits_kernel<true, 1024, true><<<grid, 1024, merge_lds(a), stream>>>(a);
+  else if (a.solo && a.n_split_max <= kMergeFewSplits)
     merge_splits_kernel<true, 256><<<grid, 256, merge_lds(a), stream>>>(a);
   else if (a.solo)
     merge_splits_kernel<true, 1024><<<grid, 1024, merge_lds(a), stream>>>(a);

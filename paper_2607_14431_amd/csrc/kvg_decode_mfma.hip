@@ -523,7 +523,7 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
       for (int d = 0; d < ND; ++d)
         *reinterpret_cast<f32x4*>(op + 16 * d) = (f32x4){o[d][0] / lu, o[d][1] / lu, o[d][2] / lu, o[d][3] / lu};
     } else if (col < G) {
-      const int64_t pidx = ((head0 + col) * a.n_split_max + s) * 4 + unit0;
+      const int64_t pidx = (head0 + col) * unit_slots(a.n_split_max, a.n_shared_split) + unit_slot(s, a.n_shared_split) + unit0;
 #pragma unroll
       for (int d = 0; d < ND; ++d) *reinterpret_cast<f32x4*>(a.part_acc + pidx * D + 16 * d + 4 * grp) = o[d];
       if (grp == 0) *reinterpret_cast<float2*>(a.part_ml + pidx * 2) = make_float2(m, lu);

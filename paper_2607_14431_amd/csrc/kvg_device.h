@@ -185,10 +185,15 @@ struct DecodeArgs {
   // are windowed).
   int32_t n_full, n_split_full, n_split_win;
   uint8_t layer_order[kMaxWindowLayers];
-  int32_t solo;               // a wave per 128-key unit: four partials per split in part_acc / part_ml
+  int32_t solo;               // a wave per 128-key unit: four partials per split in part_acc / part_ml (unit_slot)
   double theta[kMaxHalfDim];
   int32_t window[kMaxWindowLayers];
 };
+
+// solo: partials per row, and the first of split s: one for each shared split (no layer has a window then), four
+// for the others
+__host__ __device__ inline int unit_slots(int n_split_max, int n_shared) { return n_shared + 4 * (n_split_max - n_shared); }
+__host__ __device__ inline int unit_slot(int s, int n_shared) { return s < n_shared ? s : n_shared + 4 * (s - n_shared); }
 
 // Work item w of a decode grid, the sequence fastest: layer of the launch, KV head, split of the
 // grid, sequence.

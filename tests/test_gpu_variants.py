@@ -232,6 +232,52 @@ def test_decode_wave_per_unit_is_wave_per_split(dtype, D, window, B):
         assert torch.equal(want, decode([b], ctxs[b]).view(torch.int32)), f"context {ctxs[b]} in a call of its length"
 
 
+# A shared window: the other splits of a small call take a wave per unit, of a larger one a wave per split (each row has
+# a partial per shared split, four or one per other split).  Same bytes, for own keys of no whole unit to three splits.
+@pytest.mark.parametrize("dtype,D,Hq,Hkv", [("bf16", 256, 4, 2), ("bf16", 128, 8, 2), ("fp8", 256, 2, 2), ("fp8", 64, 8, 2)])
+def test_decode_beside_shared_splits(dtype, D, Hq, Hkv):
+    import torch
+
+    from gpu_helpers import TORCH_DTYPE
+    from paper_2607_14431_amd import kvg
+    L, B, shared = 48, 4, 1100 // 16 * 16
+    ctxs = [2600, shared + 1, 1500, 1024 + 200]
+    n_sh, per = shared // 16, max(ctxs) // 16 + 1
+    g = torch.Generator(device="cuda").manual_seed(D)
+    n_pages = n_sh + B * (per - n_sh)
+    cache = kvg.Cache.allocate(L, n_pages, Hq, Hkv, D, TORCH_DTYPE[dtype])
+    for pool in (cache.k_pool, cache.v_pool):
+        pool.copy_((torch.randn(pool.shape, generator=g, device="cuda") * 0.5).to(pool.dtype))
+    perm = torch.randperm(n_pages, generator=g, device="cuda").to(torch.int32)
+    tables = torch.stack([torch.cat([perm[:n_sh], perm[n_sh + b * (per - n_sh):n_sh + (b + 1) * (per - n_sh)]]) for b in range(B)])
+    seqs = kvg.Seqs(tables, torch.tensor(ctxs, dtype=torch.int32, device="cuda"), torch.zeros(B, dtype=torch.int64, device="cuda"),
+                    max(ctxs), shared)
+    plain = kvg.Seqs(seqs.block_tables, seqs.ctx_lens, seqs.start_pos, max(ctxs))
+    raw = [torch.randn((L, B, 1, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv)]
+
+    def decode(l0, n, ws_bytes=None, s=seqs):
+        out = torch.full((n, B, 1, Hq, D), float("nan"), device="cuda")
+        ws = torch.empty(ws_bytes or kvg.kvg_decode_workspace_bytes(cache, s, n), dtype=torch.uint8, device="cuda")
+        kvg.kvg_decode_attn(cache, s, kvg.rope(), l0, n, *(t[l0:l0 + n] for t in raw), D ** -0.5, out, ws)
+        return out
+
+    own = (max(ctxs) + 512) // 512 - shared // 512
+    limit = 1280 if D * cache.k_pool.element_size() >= 256 else 2560
+    assert 2 * B * Hkv * own * 4 <= limit < L * B * Hkv * own * 4
+    together = decode(0, L)
+    assert torch.isfinite(together).all()
+    for l0 in (0, 7, L - 2):
+        assert torch.equal(decode(l0, 2), together[l0:l0 + 2])
+    # room for one partial a split only
+    rows, splits = 2 * B * Hq, (max(ctxs) + 512) // 512
+    up = lambda x: -(-x // 256) * 256
+    small = max(up(rows * splits * 8) + up(rows * splits * D * 4) + 2 * up(rows * D * 2), kvg.kvg_decode_workspace_bytes(cache, plain, 2))
+    assert torch.equal(decode(7, 2, small), together[7:9])
+    # attended per sequence: the shared splits' bf16 weights apart (2^-9 each)
+    alone = decode(7, 2, s=plain)
+    assert ((alone - together[7:9]).norm() / alone.norm()).item() < 4e-3
+
+
 # Two waves per 64 leaves (up to 512 x 64 leaves of equal length): one set and two sets a workgroup, partial
 # sets, one and several blocks; a ragged last leaf and one leaf too many take a lane per leaf
 @pytest.mark.parametrize("n,leaf,short", [(1, 64, 0), (65, 128, 0), (65, 128, 9), (16_384, 64, 0), (16_385, 64, 0),
