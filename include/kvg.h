@@ -14,7 +14,8 @@
  *  - All pointers named *_dev, and every pointer inside kvg_cache / kvg_seqs, are
  *    device pointers unless stated.  The caller allocates and owns all memory
  *    (pools, tables, payloads, outputs, workspaces).  The library allocates no
- *    device memory and keeps no state between calls; calls are re-entrant.
+ *    device memory, and nothing but a thread's table of its last rotary base's powers (and
+ *    kvg_decode_attn_noalloc's scratch array) outlives a call; calls are re-entrant.
  *  - `stream` is a hipStream_t (NULL = the null stream).  Kernels are enqueued on
  *    it and the call returns after enqueueing; results are visible after the
  *    caller synchronises the stream.  Apart from kvg_artifact_seal and
@@ -31,6 +32,10 @@
  *    workspace extents the arguments describe: block-table entries outside
  *    [0, n_pages) and context lengths outside [0, max_ctx_len] are skipped (the
  *    affected outputs are then unspecified), never dereferenced.
+ *  - Cached and raw values are expected to be finite.  An Inf or NaN makes the outputs of the
+ *    rows that see its token Inf or NaN, and of no others, with one exception: a prefill of a
+ *    bf16 or fp8 cache with at most 4 query heads per KV head weighs the values of tokens that a
+ *    row does not see by 0, and 0 times such a value is NaN for the rows of the same tile.
  *  - Reduction orders depend only on logical token indices, never on physical
  *    page ids, batch size, chunking of other sequences or the device's CU count,
  *    so the fresh path and the graft path produce identical bytes.  One exception is
@@ -59,7 +64,7 @@ typedef enum {
   KVG_E_ALIGN = -6,       /* block start not page aligned, or a buffer not 16-byte aligned  */
   KVG_E_CORRUPT = -7,     /* artifact header inconsistent, or payload differs from its digest */
   KVG_E_HIP = -8,         /* a HIP launch or runtime call failed                           */
-  KVG_E_WORKSPACE = -9    /* workspace smaller than the size query returned               */
+  KVG_E_WORKSPACE = -9    /* workspace too small (the size query's bytes are enough)       */
 } kvg_status;
 
 /* Storage dtype of a cache.  FP8_E4M3 is OCP FP8 E4M3 (1 sign, 4 exponent bits with bias
@@ -265,7 +270,8 @@ size_t kvg_prefill_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs,
  * with the fp32 query; P rounded to bf16; fp8 rows widened to bf16 exactly).  With 8 query heads per
  * KV head P keeps a bf16 remainder for the first 64 keys (head_dim 64 in fp8: 256) and in layers
  * with windows of at most 64 keys (rows of 128 bytes 128, of 64 bytes 256), and is exact for rows of
- * at most 64 keys.  fp32 caches use fp32 matrix arithmetic.
+ * at most 64 keys.  fp32 caches use fp32 arithmetic, on the matrix cores or, in small calls, on the
+ * vector ALUs in the same order.
  * q_raw_dev: [n_layers][batch][chunk_len][n_q_heads][head_dim] of the raw dtype (the cache
  * dtype, bf16 for an fp8 cache), pre-rotation;
  * k_raw_dev, v_raw_dev as kvg_append; out_dev: [n_layers][batch][chunk_len][n_q_heads]
@@ -296,7 +302,8 @@ size_t kvg_decode_workspace_bytes(const kvg_cache* cache, const kvg_seqs* seqs, 
  * score and each weighted sum is the sum of both products; the weights of a row of at most 64 keys
  * have a third part, which makes them exact); fp32 caches use fp32 vector arithmetic.  Two
  * launches: the split kernel (which also rotates the queries and appends the new token) and the
- * combine kernel.  Layouts as kvg_prefill_attn with chunk_len = 1.
+ * combine kernel, if max_ctx_len + 1 tokens are more than one range.  Layouts as kvg_prefill_attn
+ * with chunk_len = 1.
  * ws_dev: kvg_decode_workspace_bytes() bytes of scratch (contents undefined after the call).
  * Errors: as kvg_prefill_attn. */
 int kvg_decode_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope* rope,

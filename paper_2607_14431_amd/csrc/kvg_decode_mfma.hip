@@ -3,8 +3,8 @@
 // Work item = (layer, sequence, KV head g, split s of kSplit = 512 keys), one wave each.  The
 // split is four units of 128 keys (a window's last one up to 15 keys longer: split_base); each unit
 // starts from an empty softmax state, and the units of a split are merged in order.  Splits are
-// combined in ascending order by the merge kernels.  Everything is a function of the row's own length and window, so a sequence's bytes depend neither
-// on its batch nor on the pages' places.
+// combined in ascending order by the merge kernels.  Everything is a function of the row's own length
+// and window, so a sequence's bytes depend neither on its batch nor on the pages' places.
 //
 // What bounds it: HBM, when the launch fills the chip.  Keys and values go from the pages straight
 // into LDS (buffer_load ... lds, whole (page, head) slabs, 1 KiB of consecutive bytes per
@@ -17,10 +17,12 @@
 // 8-15, so a weight keeps 16 significant bits at no cost), and O^T += V^T P^T takes one MFMA per
 // 16 dimensions with V read transposed from LDS (ds_read_b64_tr).  On the vector ALUs (16-lane teams,
 // one dot product per key and head) a pair of keys took ~200 instructions in a row, which bound
-// every launch that left CUs idle.
+// every launch that left CUs idle.  A wave alone is slower than a workgroup of those was (20 us for 512
+// keys of 512-byte rows), so a launch's last round weighs more here: 1,728 splits 152 us against 147 there.
 //
-// kSolo: a wave per unit instead of per split, for launches that leave CUs idle; the four units of a split leave four partials, which merge_splits_kernel merges with
-// the same operations in the same order, so the bytes are the same.
+// kSolo: a wave per unit instead of per split, for launches that leave CUs idle; the four units of a
+// split leave four partials, which merge_splits_kernel merges with the same operations in the
+// same order, so the bytes are the same.
 #include "kvg_launch.h"
 #include "kvg_mfma.h"
 #include "kvg_rows.h"
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(64, kSolo ? 1 : 2) void decode_mfma_kernel(const De
   // being loaded; K rows, then V rows
   auto stage_mem = [&](auto st) -> uint4* { return stage_memory<decltype(st)::value, kStageBytes>(); };
 
-  // ---- work item (the order of decode_kernel: sequence fastest; with a shared window runs of 64
+  // ---- work item (the order of the fp32 decode: sequence fastest; with a shared window runs of 64
   // items go to one XCD)
   int64_t w = blockIdx.x;
   int unit0 = 0;
