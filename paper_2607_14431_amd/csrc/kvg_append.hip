@@ -104,7 +104,8 @@ __device__ __forceinline__ void store_vec_f32(float* dst, const float* x) {
                                                            __float_as_uint(x[e + 2]), __float_as_uint(x[e + 3])));
 }
 
-template <typename T>
+// kAhead: a thread's first item of each kind is requested together with the others' (see below).
+template <typename T, bool kAhead>
 __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
   using R = typename RawOf<T>::type;                     // raw input type
   constexpr int E = Elem<R>::kPerVec;                    // elements per item vector
@@ -139,7 +140,9 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
   // A thread's first item of each kind, requested together and before the layer's stores, the first
   // layer's before the angles: each kind waiting for its own loads took 10 us of a 512-row chunk
   // with 16 + 8 + 8 heads x 256 instead of 7, and 630 instead of 617 of a 3,950-token block's 48 layers.  Requesting
-  // the next layer's ahead of this one's stores costs registers and with them wavefronts: 641.
+  // the next layer's ahead of this one's stores costs registers and with them wavefronts: 641.  The first
+  // items alone cost two wavefronts of eight a SIMD, which is more than they give where a token has few
+  // (launch_append_t).
   struct First {
     RawItem k, q;
     uint4 v;
@@ -152,7 +155,8 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
     if (t0 < n_q) f.q = load_rot(a.q_raw, a.Hq, l, t0);
     return f;
   };
-  First cur = fetch(l_begin);
+  First cur;
+  if constexpr (kAhead) cur = fetch(l_begin);
 
   __shared__ float cs[2 * kMaxHalfDim];
   for (int p = threadIdx.x; p < half; p += blockDim.x) {
@@ -170,7 +174,7 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
 
     // keys: rotate, round, store through the block table
     for (int it = t0; it < n_k; it += blockDim.x) {
-      const RawItem raw = it == t0 ? cur.k : load_rot(a.k_raw, a.Hkv, l, it);
+      const RawItem raw = kAhead && it == t0 ? cur.k : load_rot(a.k_raw, a.Hkv, l, it);
       const int h = it / items_per_row;
       const int e0 = (it - h * items_per_row) * E;
       RotItem<R> r;
@@ -181,7 +185,7 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
     }
     // values: copy (rounded to the storage type when it differs from the raw type)
     for (int it = t0; it < n_v; it += blockDim.x) {
-      const uint4 raw = it == t0 ? cur.v : load_v(l, it);
+      const uint4 raw = kAhead && it == t0 ? cur.v : load_v(l, it);
       const int h = it / vec_per_row;
       const int e0 = (it - h * vec_per_row) * E;
       T* dst = vpool + (((int64_t)page * a.Hkv + h) * kPage + row) * D + e0;
@@ -195,7 +199,7 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
       }
     }
     for (int it = t0; it < n_q; it += blockDim.x) {
-      const RawItem raw = it == t0 ? cur.q : load_rot(a.q_raw, a.Hq, l, it);
+      const RawItem raw = kAhead && it == t0 ? cur.q : load_rot(a.q_raw, a.Hq, l, it);
       const int h = it / items_per_row;
       const int e0 = (it - h * items_per_row) * E;
       RotItem<R> r;
@@ -214,18 +218,30 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendArgs a) {
       store_vec_f32<R>(q + e0, r.x[0]);
       if (a.pairing == 0) store_vec_f32<R>(q + e0 + half, r.x[1]);
     }
-    if (l + 1 < l_end) cur = fetch(l + 1);
+    if constexpr (kAhead) {
+      if (l + 1 < l_end) cur = fetch(l + 1);
+    }
   }
 }
 
 }  // namespace
 
-hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t stream) {
+// kAhead with the queries of a prefill, and from 129 16-byte vectors of values a token on.  48 layers of 1,000 tokens,
+// us with / without: fp32, 2 heads x 64 (32 vectors) 48 / 43; bf16, 8 x 64 (64) 64 / 57, 8 x 256 (256) 147 / 149.
+template <typename T>
+void launch_append_t(const AppendArgs& a, hipStream_t stream) {
   const dim3 grid(a.batch * a.chunk, (a.n_layers + a.layers_per_block - 1) / a.layers_per_block);
+  if (a.q_raw != nullptr || a.Hkv * a.D > 128 * Elem<typename RawOf<T>::type>::kPerVec)
+    append_kernel<T, true><<<grid, 256, 0, stream>>>(a);
+  else
+    append_kernel<T, false><<<grid, 256, 0, stream>>>(a);
+}
+
+hipError_t launch_append(const AppendArgs& a, int dtype, hipStream_t stream) {
   switch (dtype) {
-    case kDtypeF32: append_kernel<float><<<grid, 256, 0, stream>>>(a); break;
-    case kDtypeBf16: append_kernel<uint16_t><<<grid, 256, 0, stream>>>(a); break;
-    case kDtypeFp8: append_kernel<uint8_t><<<grid, 256, 0, stream>>>(a); break;
+    case kDtypeF32: launch_append_t<float>(a, stream); break;
+    case kDtypeBf16: launch_append_t<uint16_t>(a, stream); break;
+    case kDtypeFp8: launch_append_t<uint8_t>(a, stream); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

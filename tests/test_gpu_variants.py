@@ -278,6 +278,34 @@ def test_decode_beside_shared_splits(dtype, D, Hq, Hkv):
     assert ((alone - together[7:9]).norm() / alone.norm()).item() < 4e-3
 
 
+# An append of many values a token requests a thread's first items together, of few one after the other: a head's rows
+# are the same bytes among others and alone.  More items than lanes, layers of several to a workgroup.
+@pytest.mark.parametrize("dtype", ["bf16", "fp8", "f32"])
+@pytest.mark.parametrize("D,Hkv", [(64, 40), (128, 9), (256, 17)])
+@pytest.mark.parametrize("pairing", [0, 1])
+def test_append_of_a_head_among_others(dtype, D, Hkv, pairing):
+    import torch
+
+    from gpu_helpers import INT_VIEW, TORCH_DTYPE
+    from paper_2607_14431_amd import kvg
+    L, n = 7, 1500                                    # L n > 8192: two layers a workgroup
+    n_pages = (n + 15) // 16
+    g = torch.Generator(device="cuda").manual_seed(D)
+    table = torch.randperm(n_pages, generator=g, device="cuda").to(torch.int32)[None]
+    seqs = kvg.Seqs(table, torch.zeros(1, dtype=torch.int32, device="cuda"), torch.full((1,), 33, dtype=torch.int64, device="cuda"), 0)
+    wide = kvg.Cache.allocate(L, n_pages, Hkv, Hkv, D, TORCH_DTYPE[dtype])
+    k, v = (torch.randn((L, 1, n, Hkv, D), generator=g, device="cuda").to(wide.raw_dtype) for _ in range(2))
+    assert Hkv * D * k.element_size() > 128 * 16 >= D * k.element_size()
+    kvg.kvg_append(wide, seqs, kvg.rope(10000.0, pairing), 0, L, n, k, v)
+    for h in (0, 1, Hkv // 2, Hkv - 1):
+        one = kvg.Cache.allocate(L, n_pages, 1, 1, D, TORCH_DTYPE[dtype])
+        kvg.kvg_append(one, seqs, kvg.rope(10000.0, pairing), 0, L, n, *(t[:, :, :, h:h + 1].contiguous() for t in (k, v)))
+        for a, b in ((wide.k_pool, one.k_pool), (wide.v_pool, one.v_pool)):
+            for page in (0, n // 32):                 # whole pages of the sequence
+                at = int(table[0, page])
+                assert torch.equal(a.view(INT_VIEW[dtype])[:, at, h], b.view(INT_VIEW[dtype])[:, at, 0]), (h, page)
+
+
 # Two waves per 64 leaves (up to 512 x 64 leaves of equal length): one set and two sets a workgroup, partial
 # sets, one and several blocks; a ragged last leaf and one leaf too many take a lane per leaf
 @pytest.mark.parametrize("n,leaf,short", [(1, 64, 0), (65, 128, 0), (65, 128, 9), (16_384, 64, 0), (16_385, 64, 0),
