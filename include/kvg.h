@@ -316,9 +316,9 @@ int kvg_decode_attn(const kvg_cache* cache, const kvg_seqs* seqs, const kvg_rope
  * same computation as kvg_decode_attn (same kernels, same bytes), with the workspace taken
  * from a fixed device array of KVG_NOALLOC_SCRATCH_BYTES bytes that the library holds on every
  * device it runs on until the process ends (its address is looked up once per device, on the
- * first call there).  The call itself allocates nothing.  Calls whose workspace
- * (kvg_decode_workspace_bytes) exceeds the array return KVG_E_WORKSPACE before launching
- * anything.  All calls on one device share the array and keep no state in it between calls:
+ * first call there).  The call itself allocates nothing.  Calls whose least
+ * workspace (at most kvg_decode_workspace_bytes) exceeds the array return KVG_E_WORKSPACE
+ * before launching anything.  All calls on one device share the array and keep no state in it between calls:
  * calls that overlap on one device (several streams or threads) race and must be serialised
  * by the caller.  Errors: as kvg_decode_attn, and KVG_E_HIP when the array's address cannot
  * be taken. */

@@ -12,8 +12,7 @@ absolute multiples of 512), so:
   * sequential composition holds: graft A at [0, |A|), prefill B on top in chunks, deposit
     A || B, and the result equals the fresh monolithic computation of A || B byte for byte.
 
-Covered paths: bf16 MFMA prefill (group 2, D 256 and 128), bf16 VALU prefill (group 8),
-fp32 VALU prefill and fp8 caches, each also with sliding-window layers beside global ones (a windowed row
+Covered paths: bf16 prefill (group 2, D 256 and 128; group 8), fp32 prefill and fp8 caches, each also with sliding-window layers beside global ones (a windowed row
 skips the key tiles and decode splits below its window, which depend on where its chunk
 starts; the bytes must not).  Chunk sizes cross page (16) and key-tile (64) boundaries."""
 
